@@ -105,10 +105,14 @@ TPILU_API tpilu_status tpilu_ctx_set_watchdog(tpilu_ctx ctx, uint32_t timeout_us
  * gives the same bits; it only changes speed.  Used to test that claim. */
 TPILU_API tpilu_status tpilu_ctx_set_grid(tpilu_ctx ctx, int32_t waves);
 
-/* Launch shape of the single-instance triangular solves: 0 = automatic
- * (lane per row when a triangle's rows hold at most 40 entries on average
- * and a dependency level at least max(64, 16 x that average) rows, else a
- * wavefront per row), 1 = a wavefront per row (on the whole device or on
+/* Launch shape of the single-instance triangular solves: 0 = automatic (the
+ * shape of the smallest time estimated from the pattern's structure: both
+ * sweeps on one CU with x in its LDS for small systems of short rows; a lane
+ * per row over chunks of one dependency level, on one XCD; a lane per row over
+ * blocks of 64 consecutive rows, on one XCD, for rows that depend on few of
+ * their near neighbours; else a wavefront per row, on the whole device or on
+ * one XCD.  The first three only while placement and grid are automatic too),
+ * 1 = a wavefront per row (on the whole device or on
  * one XCD, see tpilu_ctx_set_placement), 2 = one workgroup on one CU (a lane
  * per row, rows handed over through an LDS ring; measured far slower than
  * mode 1 on every workload tried, kept as the alternative shape), 3 = a lane
@@ -174,9 +178,9 @@ TPILU_API tpilu_status tpilu_ctx_set_placement(tpilu_ctx ctx, int where);
  * a wavefront takes `rows` consecutive positions of the dependency-level
  * order from the shared counter and works through them in order.  0 =
  * automatic, else 1 to 64.  Automatic: 1 for the numeric factorization
- * (its kernels overlap a row's work with the wait on earlier levels, which
- * a group would serialise); for the solves 1, 2 or 3 and for the inverses 1
- * or 2, growing with the average rows per dependency level.  Same bits for every value;
+ * and the solves (their kernels overlap a row's work with the wait on earlier
+ * levels, which a group would serialise); for the inverses 1 or 2, by the
+ * average rows per dependency level.  Same bits for every value;
  * it only changes speed.  Returns TPILU_E_INVAL outside [0, 64]. */
 TPILU_API tpilu_status tpilu_ctx_set_group(tpilu_ctx ctx, int32_t rows);
 

@@ -191,6 +191,45 @@ hipError_t launch_backward(const PatDev& P, const double* f_val, int32_t batch, 
                            double* y, Ctl* ctl, uint64_t spin_limit, int32_t grid, bool one_xcd,
                            hipStream_t s);
 
+// ---- the solves by level chunks (k_solve_level.hip) -----------------------------
+// Schedule of one direction: positions of the level order cut into chunks of
+// up to 64 that never cross a level.  rec[p] = (row, first slot of its half
+// in subtraction order, entries, hint row or -1) of position p.
+struct LevelSched {
+    const int4* rec = nullptr;   // [n]
+    const int4* head = nullptr;  // [nchunk]: first position, end, first chunk of the level, 0
+    int32_t nchunk = 0;
+    int32_t depth = 0;
+};
+// off: first position of every level (scan of the level sizes); *max_depth, *nchunk on the device
+hipError_t launch_level_sched(int32_t n, const int64_t* off, const int32_t* depth, const int32_t* max_depth,
+                              const int32_t* perm, const int64_t* rpF, const int32_t* diagF, bool backward, int4* rec,
+                              int4* head, int32_t* nchunk, hipStream_t s);
+constexpr int32_t kLdsSolveRows = 16384;  // most rows of k_solve_lds (128 KB of LDS)
+constexpr int32_t kLdsSolveHalf = 16;     // most entries of a row half there
+// sweeps: 1 forward (x nullable), 2 backward (reads x), 3 both in one launch (x nullable)
+hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& Up, int32_t max_half,
+                            const double* f_val, const int32_t* ci, const double* b, double* x, double* y, int sweeps,
+                            bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s);
+// one sweep on one XCD with grid wavefronts there (out pre-filled with kPending)
+hipError_t launch_solve_chunks(const PatDev& P, const LevelSched& L, int32_t max_half, const double* f_val,
+                               const double* in, double* out, bool backward, int32_t grid, Ctl* ctl,
+                               uint64_t spin_limit, hipStream_t s);
+
+// ---- the solves by blocks of consecutive rows (k_solve_block.hip) -----------------
+constexpr int kWinBlocks = 3;    // neighbour blocks whose values a block keeps in LDS
+constexpr int kWinEntries = 64;  // most entries of a row inside its window
+struct BlockStats {
+    unsigned long long rounds_l, rounds_u;  // half rounds of the walks inside the blocks, summed
+    int32_t max_win_l, max_win_u;           // most window entries of any row (kWinEntries + 1: more)
+};
+// wcntL / wcntU: entries of every row inside its window (bytes); *st pre-set to 0
+hipError_t launch_block_stats(int32_t n, const int64_t* rpF, const int32_t* ciF, const int32_t* diagF, uint8_t* wcntL,
+                              uint8_t* wcntU, BlockStats* st, hipStream_t s);
+// one sweep on one XCD with grid workgroups there (out pre-filled with kPending)
+hipError_t launch_solve_blocks(const PatDev& P, const uint8_t* wcnt, const double* f_val, const double* in, double* out,
+                               bool backward, int32_t grid, Ctl* ctl, uint64_t spin_limit, hipStream_t s);
+
 // ---- the solves on one CU (lane per row, hand-off through an LDS ring) ----------
 // Pq[slot] = level-order position of the row named by the slot's column
 // (forward order for strict lower slots, backward order for upper ones)

@@ -197,20 +197,17 @@ struct DeviceGuard {
 
 // Level-order positions a wavefront takes per ticket in the wavefront-per-row
 // kernels.  Every ticket is one atomic on one address (about 11 ns each,
-// serialised), which on wide levels caps how fast rows can be handed out;
-// grouping divides that traffic but runs a group's rows back to back.  The
-// numeric kernels overlap a row's work with its wait on earlier levels, so
-// there a group costs a whole row time per level (random banded n=160,000
-// ILU(2): 8.5 -> 147 ms at 2 rows): always 1.  Solves and inverses gain on wide levels (7-point 64^3,
-// ILU(1), 692 rows per level: wavefront-per-row forward 5.5 -> 3.3 ms at 3
-// rows, inverse 6.6 -> 4.0 ms at 2 rows) and lose on narrow ones.
+// serialised; eight counters share the traffic).  A group of positions divides
+// it but runs the group's rows back to back, which costs a whole row time per
+// level where a row waits on earlier levels: random banded n=160,000 ILU(2)
+// factorization 8.5 -> 147 ms at 2 rows, 27-point 50^3 ILU(1) solves (196 rows
+// per level) 1.61 -> 4.27 ms at 2.  Only the inverses gain, on wide levels
+// (7-point 64^3 ILU(1), 692 rows per level: 6.6 -> 4.0 ms at 2 rows).
 enum class RowKernel { Numeric, Solve, Inverse };
 
 int32_t row_group(RowKernel kind, int64_t n, int64_t depth) {
-    if (depth <= 0 || kind == RowKernel::Numeric) return 1;
-    const int64_t width = std::max<int64_t>(n, 1) / depth;
-    if (kind == RowKernel::Solve) return width >= 512 ? 3 : width >= 128 ? 2 : 1;
-    return width >= 512 ? 2 : 1;
+    if (depth <= 0 || kind != RowKernel::Inverse) return 1;
+    return std::max<int64_t>(n, 1) / depth >= 512 ? 2 : 1;
 }
 
 // Wavefronts of the batched kernels (a task is one row for 64 instances).
@@ -249,6 +246,9 @@ struct tpilu_pattern_s {
     int32_t* depthU = nullptr;  // and backward sweep
     int32_t* permL = nullptr;   // rows sorted by depthL: the ticket order of numeric and forward
     int32_t* permU = nullptr;   // rows sorted by depthU: the ticket order of backward
+    uint8_t *wcntL = nullptr, *wcntU = nullptr;  // entries of every row inside its window (k_solve_block.hip)
+    BlockStats bst{};
+    LevelSched lsL, lsU;        // the two level orders cut into chunks (k_solve_level.hip)
     Ctl* ctl = nullptr;
     // adjoint transposes (built on first use)
     bool have_t = false;
@@ -498,29 +498,50 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
     return TPILU_OK;
 }
 
-// Launch shape of the single-instance solves, per direction (the grid
-// argument of launch_forward / launch_backward): > 0 wavefront per row with
-// that many wavefronts (on one XCD when one_xcd), 0 one workgroup, < 0 lane
-// per row with -grid wavefronts.  Automatic choice: lane per row when the rows are short and a
-// dependency level is wide next to the row length (a lane runs a whole row
-// alone, so it needs many rows per level to beat 64 lanes on one row),
-// namely rows per level >= max(64, 16 x average entries per row half); else
-// a wavefront per row; few rows per level want fewer wavefronts (hand-offs
-// dominate), many rows more.  Measured on MI355X: 7-point 64^3 ILU(1) (692
-// rows per level, 6 entries per half) 0.8 vs 2.1 ms by lane; 27-point 90^3
-// ILU(1) (630 rows, 30 entries) 6.3 vs 8.2 ms by lane; 27-point 70^3 ILU(1)
-// (382 rows, 30 entries) 3.9 vs 4.3 ms by wavefront; 27-point 30^3 ILU(1)
-// (71 rows) 0.46 vs 1.6 ms by wavefront; random banded n=160,000 ILU(2) (82
-// entries per half) 3x faster by wavefront.
-constexpr int64_t kLaneMaxAvg = 40;    // average entries per row half at or below
-constexpr int64_t kLaneMinWidth = 64;  // rows per dependency level at or above
-constexpr int64_t kLaneWidthPerEntry = 16;  // ... and at or above this many per entry of a row half
-constexpr int32_t kLaneWaves = 128;
-
+// Launch shape of the single-instance solves, per direction.  Row: grid > 0 a
+// wavefront per row with that many wavefronts (on one XCD when one_xcd), 0 one
+// workgroup, < 0 a lane per row with -grid wavefronts.  Chunks and Blocks: one
+// XCD, grid workgroups there.
+//
+// Automatic choice: the shape of the smallest estimated time (one sweep, ns),
+// from the structure alone.  The estimates are fits to measurements on MI355X
+// (us per sweep, estimated / measured):
+//   chunks  a cost per dependency level by the longest row half (450 up to 4
+//           entries, 600 up to 8, 970 per 16 beyond) + 30 per chunk: 2-D 400^2
+//           ILU(1) 654 / 580, 7-point 64^3 ILU(1) 361 / 385, ILU(2) 816 / 827,
+//           27-point 50^3 ILU(0) 403 / 426
+//   blocks  230 per block + 118 per round of its walk, at least 0.115 per
+//           entry (one XCD's loads): random banded n=160,000 ILU(1) 1519 /
+//           1480, ILU(2) 3207 / 3200, n=10,000 ILU(2) 266 / 280, paper-scale
+//           ILU(1) (640 entries per row half) 11700 / 11800
+//   row     700 per level on one XCD, 1150 on the whole device and there at
+//           least 2.2 per row: random banded ILU(2) 8597 / 8300, 27-point
+//           50^3 ILU(1) 734 / 806, 40^3 ILU(2) 943 / 962, 7-point 110^3
+//           ILU(0) 2928 / 2990 (by chunks 605)
+enum class SolveKind { Row, Chunks, Blocks };
 struct SolveShape {
-    int32_t grid;  // 0: one CU (launch_solve_cu)
+    int32_t grid;
     bool one_xcd;
+    SolveKind kind = SolveKind::Row;
 };
+int64_t chunk_level_ns(int32_t half) {
+    return half <= 4 ? 450 : half <= 8 ? 600 : 970 * std::max<int64_t>(1, ((int64_t)half + 15) / 16);
+}
+constexpr int64_t kChunkNs = 30;
+constexpr int64_t kBlockNs = 230, kBlockRoundNs = 118;
+constexpr double kBlockEntryNs = 0.115;
+constexpr int64_t kRowLevelXcdNs = 700, kRowLevelNs = 1150;
+constexpr double kRowNs = 2.2;
+constexpr int32_t kLaneWaves = 128;
+// workgroups of the block kernel on its XCD (random banded n=160,000 ILU(2),
+// both sweeps: 16 / 24 / 28 / 32 / 40: 8.8 / 6.6 / 6.4 / 6.4 / 6.7 ms)
+constexpr int32_t kBlockGroups = 28;
+// Both substitutions in one launch on one compute unit: small systems of
+// short rows, as long as its loads (about 1 ns per entry of F for both sweeps)
+// take less than the levels would through the L2 (2-D 127 x 127 ILU(2) 0.20
+// against 0.45 ms by chunks, 7-point 25^3 ILU(2) 0.38 / 0.50; 27-point 25^3
+// ILU(0) 0.49 / 0.33 stays with the chunks).
+constexpr int64_t kLdsEntryNs = 1;
 
 // placement of a wavefront-per-row sweep over n rows of `depth` dependency
 // levels whose row halves hold `half` entries in all (rule at kXcdMaxAvg)
@@ -528,6 +549,15 @@ bool solve_on_xcd(tpilu_ctx ctx, int64_t n, int64_t half, int64_t depth) {
     if (ctx->placement != 0) return ctx->placement == 2;
     const int64_t width = n / std::max<int64_t>(depth, 1);
     return (width < kNarrowWidth && half <= kXcdMaxAvg * n) || (width < 64 && half < 64 * n);
+}
+
+// nothing asked for: the shape is the library's choice
+bool solve_auto(tpilu_ctx ctx) { return ctx->solver == 0 && ctx->placement == 0 && !ctx->grid_override; }
+
+bool solve_in_lds(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch) {
+    const int32_t half = std::max(pat->st.max_lrow, pat->st.max_upart);
+    return batch == 1 && solve_auto(ctx) && pat->n <= kLdsSolveRows && half <= kLdsSolveHalf &&
+           pat->nnz_f * kLdsEntryNs <= ((int64_t)pat->depth_l + pat->depth_u) * chunk_level_ns(half);
 }
 
 SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool backward) {
@@ -538,17 +568,29 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
     const int64_t n = std::max<int64_t>(pat->n, 1);
     const int64_t half = backward ? pat->nnz_f - (int64_t)pat->st.nnz_l - pat->n : (int64_t)pat->st.nnz_l;
     const int64_t depth = std::max<int64_t>(1, backward ? pat->depth_u : pat->depth_l);
-    int mode = ctx->solver;
-    if (mode == 0) {
-        const int64_t width = n / depth;
-        const bool lanes = half <= kLaneMaxAvg * n && width >= kLaneMinWidth &&
-                           width * n >= kLaneWidthPerEntry * half;
-        mode = lanes ? 3 : 1;
-    }
-    if (mode == 2) return {0, false};
-    if (mode == 3) return {-(ctx->grid_override ? ctx->grid_override : kLaneWaves), false};
     const int64_t width = n / depth;
     const bool one_xcd = solve_on_xcd(ctx, n, half, depth);
+    if (solve_auto(ctx)) {
+        const int32_t longest = backward ? pat->st.max_upart : pat->st.max_lrow;
+        const int64_t blocks = (n + 63) / 64;
+        const int64_t t_row = one_xcd ? depth * kRowLevelXcdNs
+                                      : std::max(depth * kRowLevelNs, (int64_t)((double)n * kRowNs));
+        const int64_t t_chunks =
+            depth * chunk_level_ns(longest) + (backward ? pat->lsU : pat->lsL).nchunk * kChunkNs;
+        const int64_t rounds2 = (int64_t)(backward ? pat->bst.rounds_u : pat->bst.rounds_l);
+        const int64_t t_blocks = (backward ? pat->bst.max_win_u : pat->bst.max_win_l) > kWinEntries
+                                     ? INT64_MAX
+                                     : std::max(blocks * kBlockNs + rounds2 * kBlockRoundNs / 2,
+                                                (int64_t)((double)half * kBlockEntryNs));
+        if (t_blocks < t_row && t_blocks <= t_chunks) return {kBlockGroups, true, SolveKind::Blocks};
+        // chunks in work at a time: the ones of about eight levels (7-point 64^3
+        // ILU(1), 11 chunks a level: 24 / 48 / 96 wavefronts 0.91 / 0.84 / 0.77 ms;
+        // ILU(2), 6 a level: 1.65 / 1.69 / 1.73 ms)
+        if (t_chunks < t_row)
+            return {(int32_t)std::min<int64_t>(96, std::max<int64_t>(24, 8 * (width / 64))), true, SolveKind::Chunks};
+    }
+    if (ctx->solver == 2) return {0, false};
+    if (ctx->solver == 3) return {-(ctx->grid_override ? ctx->grid_override : kLaneWaves), false};
     if (ctx->grid_override) return {ctx->grid_override, one_xcd};
     if (width < kNarrowWidth) return {kSolveWavesNarrow, one_xcd};
     if (width < 64 && half < 64 * n) return {kSolveWavesMid, one_xcd};
@@ -557,9 +599,29 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
 
 // forward = false: x already holds L~^-1 b (the batched factorization with
 // the forward substitution fused in); only the backward sweep runs
+// keep_x: the caller wants x (the one-launch shape stores it only then).
 tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val, int32_t batch,
                            const double* b, double* y, double* x, bool reset, Ctl* ctl, bool timed = true,
-                           bool forward = true) {
+                           bool forward = true, bool keep_x = false) {
+    if (solve_in_lds(ctx, pat, batch)) {
+        const int32_t half = std::max(pat->st.max_lrow, pat->st.max_upart);
+        auto go = [&](double* xp, int sweeps, bool rs) {
+            return launch_solve_lds((int32_t)pat->n, pat->lsL, pat->lsU, half, f_val, pat->ciF, b, xp, y, sweeps, rs,
+                                    ctl, ctx->trace, ctx->stream);
+        };
+        if (!ctx->timing || !timed) {
+            HIPCHK(ctx, go(keep_x ? x : nullptr, 3, reset));
+            return TPILU_OK;
+        }
+        // timed: a launch per sweep, so that each has its own time
+        {
+            TimedLaunch tl(ctx, TPILU_KERNEL_FORWARD);
+            HIPCHK(ctx, go(x, 1, reset));
+        }
+        TimedLaunch tl(ctx, TPILU_KERNEL_BACKWARD);
+        HIPCHK(ctx, go(x, 2, false));
+        return TPILU_OK;
+    }
     SolveShape gf = solve_shape(ctx, pat, batch, false), gb = solve_shape(ctx, pat, batch, true);
     // the one-CU shape needs the dependency positions; without them (never
     // built, and this call may not allocate) the wavefront-per-row shape runs
@@ -575,6 +637,12 @@ tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val
         TimedLaunch tl(ctx, TPILU_KERNEL_FORWARD, timed);
         if (gf.grid == 0)
             HIPCHK(ctx, launch_solve_cu(P, pat->dep_pos, f_val, b, x, false, ctl, ctx->spin_limit, ctx->stream));
+        else if (gf.kind == SolveKind::Blocks)
+            HIPCHK(ctx, launch_solve_blocks(P, pat->wcntL, f_val, b, x, false, gf.grid, ctl, ctx->spin_limit,
+                                            ctx->stream));
+        else if (gf.kind == SolveKind::Chunks)
+            HIPCHK(ctx, launch_solve_chunks(P, pat->lsL, pat->st.max_lrow, f_val, b, x, false, gf.grid, ctl,
+                                            ctx->spin_limit, ctx->stream));
         else
             HIPCHK(ctx, launch_forward(P, f_val, batch, b, x, ctl, ctx->spin_limit, gf.grid, gf.one_xcd,
                                        ctx->stream));
@@ -584,6 +652,12 @@ tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val
         TimedLaunch tl(ctx, TPILU_KERNEL_BACKWARD, timed);
         if (gb.grid == 0)
             HIPCHK(ctx, launch_solve_cu(P, pat->dep_pos, f_val, x, y, true, ctl, ctx->spin_limit, ctx->stream));
+        else if (gb.kind == SolveKind::Blocks)
+            HIPCHK(ctx, launch_solve_blocks(P, pat->wcntU, f_val, x, y, true, gb.grid, ctl, ctx->spin_limit,
+                                            ctx->stream));
+        else if (gb.kind == SolveKind::Chunks)
+            HIPCHK(ctx, launch_solve_chunks(P, pat->lsU, pat->st.max_upart, f_val, x, y, true, gb.grid, ctl,
+                                            ctx->spin_limit, ctx->stream));
         else
             HIPCHK(ctx, launch_backward(P, f_val, batch, x, y, ctl, ctx->spin_limit, gb.grid, gb.one_xcd,
                                         ctx->stream));
@@ -633,6 +707,10 @@ struct LevelSpec {
     int32_t* depth;
     int32_t* perm;
     int32_t* max_depth;
+    // chunks of the level order (null: not wanted), with room for n positions
+    int4* rec = nullptr;
+    int4* head = nullptr;
+    int32_t* nchunk = nullptr;  // host, set by finish_levels
 };
 
 // Enqueue the level computation on stream s without waiting for it: the
@@ -682,6 +760,9 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
         int64_t* stmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(std::max(n, 1)));
         if (!hist || !off || !stmp) return fail(ctx, TPILU_E_NOMEM, "level order");
         HIPCHK(ctx, launch_level_order(n, js[q].depth, std::max(n, 1), hist, off, stmp, js[q].perm, s));
+        if (js[q].rec)
+            HIPCHK(ctx, launch_level_sched(n, off, js[q].depth, dmax + 16 * q, js[q].perm, pat->rpF, pat->diagF, js[q].desc != 0,
+                                           js[q].rec, js[q].head, dmax + 16 * q + 1, s));
     }
     return TPILU_OK;
 }
@@ -691,7 +772,10 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
 tpilu_status finish_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js, int njobs, const int32_t* dmax) {
     int32_t dm[32] = {0};
     HIPCHK(ctx, hipMemcpy(dm, dmax, sizeof(dm), hipMemcpyDeviceToHost));
-    for (int q = 0; q < njobs; ++q) *js[q].max_depth = dm[16 * q];
+    for (int q = 0; q < njobs; ++q) {
+        *js[q].max_depth = dm[16 * q];
+        if (js[q].nchunk) *js[q].nchunk = dm[16 * q + 1];
+    }
     return read_ctl(ctx, pat, nullptr, false);
 }
 
@@ -1144,6 +1228,13 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         HIPCHK(ctx, hipMemcpyAsync(dst, &z, sizeof(z), hipMemcpyHostToDevice, s));
     }
     HIPCHK(ctx, launch_stats(ni, P->rpF, P->diagF, dst, s));
+    P->wcntL = (uint8_t*)P->take((size_t)n * 2);
+    BlockStats* bdst = (BlockStats*)T.get(sizeof(BlockStats));
+    if (!P->wcntL || !bdst) return bail(fail(ctx, TPILU_E_NOMEM, "block windows"));
+    P->wcntU = P->wcntL + n;
+    HIPCHK(ctx, launch_fill_i32((int32_t*)bdst, sizeof(BlockStats) / 4, 0, s));
+    HIPCHK(ctx, launch_block_stats(ni, P->rpF, P->ciF, P->diagF, P->wcntL, P->wcntU, bdst, s));
+    HIPCHK(ctx, hipMemcpyAsync(&P->bst, bdst, sizeof(BlockStats), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipMemcpyAsync(&P->st, dst, sizeof(PatStats), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipMemcpyAsync(&vs, vstat, sizeof(vs), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
@@ -1157,8 +1248,17 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->permU = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
     if (!P->depthL || !P->depthU || !P->permL || !P->permU) return bail(fail(ctx, TPILU_E_NOMEM, "levels"));
     const int64_t nl_ = (int64_t)P->st.nnz_l, nu_ = nnzf - nl_ - n;
-    const LevelSpec ljobs[2] = {{DepGraph{P->rpF, P->ciF, P->diagF, 0}, 0, nl_, P->depthL, P->permL, &P->depth_l},
-                                {DepGraph{P->rpF, P->ciF, P->diagF, 1}, 1, nu_, P->depthU, P->permU, &P->depth_u}};
+    LevelSpec ljobs[2] = {{DepGraph{P->rpF, P->ciF, P->diagF, 0}, 0, nl_, P->depthL, P->permL, &P->depth_l},
+                          {DepGraph{P->rpF, P->ciF, P->diagF, 1}, 1, nu_, P->depthU, P->permU, &P->depth_u}};
+    for (int q = 0; q < 2; ++q) {
+        LevelSched& L = q == 0 ? P->lsL : P->lsU;
+        ljobs[q].rec = (int4*)P->take(sizeof(int4) * (size_t)n);
+        ljobs[q].head = (int4*)P->take(sizeof(int4) * (size_t)n);  // at most one chunk per position
+        if (!ljobs[q].rec || !ljobs[q].head) return bail(fail(ctx, TPILU_E_NOMEM, "level chunks"));
+        ljobs[q].nchunk = &L.nchunk;
+        L.rec = ljobs[q].rec;
+        L.head = ljobs[q].head;
+    }
     AuxJoin aux_join;
     int32_t* ldmax = nullptr;
     {
@@ -1265,6 +1365,8 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     {
         tpilu_status ls = finish_levels(ctx, P, ljobs, 2, ldmax);
         if (ls != TPILU_OK) return bail(ls);
+        P->lsL.depth = P->depth_l;
+        P->lsU.depth = P->depth_u;
     }
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);
@@ -1377,7 +1479,7 @@ extern "C" TPILU_API tpilu_status tpilu_apply(tpilu_ctx ctx, tpilu_pattern pat, 
         st = build_dep_positions(ctx, pat);
         if (st) return st;
     }
-    return enqueue_apply(ctx, pat, f_val, batch, b, y, x, true, pat->ctl);
+    return enqueue_apply(ctx, pat, f_val, batch, b, y, x, true, pat->ctl, true, true, x_out != nullptr);
 }
 
 extern "C" TPILU_API tpilu_status tpilu_apply_noalloc(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val,
