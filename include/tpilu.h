@@ -156,7 +156,8 @@ TPILU_API tpilu_status tpilu_ctx_set_fused(tpilu_ctx ctx, int on);
  * than 64 short ones, and a row half at most 128 entries on average),
  * 1 = the whole device, 2 = one XCD (then also the batched factorization
  * and solves, and the dependency-level computation of tpilu_symbolic, one XCD
- * per dependency graph, when its nodes have long dependency lists).  On one
+ * per dependency graph, when its nodes have long dependency lists; by blocks
+ * of 64 rows that computation runs so unless placement is 1).  On one
  * XCD, grid wavefronts are
  * launched per XCD; the first workgroup to start names its XCD and the
  * workgroups of the other XCDs exit at once.  Values are then handed from

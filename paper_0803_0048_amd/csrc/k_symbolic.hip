@@ -1128,6 +1128,174 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
     }
 }
 
+// Block of 64 consecutive nodes per workgroup, a lane per node, for rows of F
+// that depend on few of their near neighbours: the blocks follow each other in
+// the sweep's order, so the chain has n / 64 hand-offs through one XCD's L2
+// instead of one per level.  As in the substitutions by blocks (which also
+// count the window entries, wcnt), far dependencies are taken in lockstep from
+// memory, 8 loads in flight; those in the kWinBlocks nearest blocks and the
+// block itself stand in LDS, where a second wavefront puts the neighbours'
+// levels as they come.  The maximum does not depend on order, so a lane walks
+// four strided parts of its window at a time.  Bound by one hand-off and the walk of
+// each block.  Random banded n=160,000 ILU(2), both DAGs, beside the update
+// schedule: 16.2 ms by a wavefront per node, 6.6 ms here (the whole of Phase I
+// 27.6 -> 22.6 ms; ILU(1) 11.2 -> 9.3, ILU(0) 6.9 -> 4.0 ms).
+// The two DAGs of a launch take alternate workgroups, which the dispatcher
+// deals to the XCDs in turn: each elects an XCD of its own.
+constexpr int kDepthSlots = 4;
+constexpr int kDepthOuter = 8;
+typedef __attribute__((address_space(3))) volatile int32_t LdsLevel;
+
+template <bool kBackward>
+__device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const uint8_t* __restrict__ wcnt, Ctl* ctl,
+                                             uint64_t limit, int32_t* cw, LdsLevel* lw, uint32_t* sh_ticket) {
+    const int32_t* __restrict__ ci = J.G.idx;
+    const int lane = lane_id();
+    const bool walker = uniform((int32_t)(threadIdx.x / kWave)) == 0;
+    const int32_t nb = (n + kWave - 1) / kWave;
+    // window-local place of the block itself and of its neighbours
+    constexpr int kOwn = kBackward ? 0 : kWinBlocks * kWave;
+    constexpr int kNear = kBackward ? kWave : 0;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) *sh_ticket = atomicAdd(&J.tctl->ticket, 1u);
+        if (walker)
+#pragma unroll
+            for (int u = 0; u <= kWinBlocks; ++u) lw[u * kWave + lane] = -1;
+        __syncthreads();
+        const uint32_t t = __builtin_amdgcn_readfirstlane(*sh_ticket);
+        if (t >= (uint32_t)nb) break;
+        const int32_t b = kBackward ? nb - 1 - (int32_t)t : (int32_t)t;
+        const int32_t base = b * kWave, i = base + lane;
+        const bool has = i < n;
+        const int32_t wbase = base - kOwn;  // node of window place 0
+        uint32_t polls = 0;
+        uint64_t t0 = 0;
+        if (!walker) {
+#pragma unroll
+            for (int u = 0; u < kWinBlocks; ++u) {
+                // farthest block first: it is complete first
+                const int32_t o = kNear + (kBackward ? kWinBlocks - 1 - u : u) * kWave + lane;
+                const int32_t r = wbase + o;
+                int32_t v = r >= 0 && r < n ? -1 : 0;
+                for (;;) {
+                    const bool pend = v < 0;
+                    if (!__any(pend)) break;
+                    if (pend) {
+                        v = ld_level(J.depth + r);
+                        if (v >= 0) lw[o] = v;
+                    }
+                    if (wait_expired(polls, t0, ctl, limit)) {
+                        if (v < 0) lw[o] = 0;  // the walk ends; the status tells
+                        break;
+                    }
+                }
+            }
+            continue;
+        }
+        int32_t q = 0, z = 0, w = 0;
+        if (has) {
+            const int32_t d = J.G.diag[i];
+            q = (int32_t)(kBackward ? J.G.ptr[i + 1] - 1 : J.G.ptr[i]);
+            z = kBackward ? q - d : d - q;
+            w = wcnt[i];
+        }
+        const int32_t outer = z - w;
+        int32_t wmax = w, omax = outer;
+        for (int off = 32; off > 0; off >>= 1) {
+            wmax = max(wmax, __shfl_xor(wmax, off));
+            omax = max(omax, __shfl_xor(omax, off));
+        }
+        wmax = uniform(wmax);
+        const int32_t rounds = (uniform(omax) + kDepthOuter - 1) / kDepthOuter;
+        for (int32_t k0 = 0; k0 < wmax; k0 += 8) {
+            int32_t c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = k0 + u < w ? ci[kBackward ? q - (outer + k0 + u) : q + outer + k0 + u] : i;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) cw[(k0 + u) * kWave + lane] = c[u] - wbase;
+        }
+        // outer dependencies, the last ones of every row in the last round
+        int32_t best = 0;
+        bool stop = false;
+        const int32_t pad = rounds * kDepthOuter - outer;
+        for (int32_t k0 = 0; k0 < rounds * kDepthOuter && !stop; k0 += kDepthOuter) {
+            int32_t c[kDepthOuter], v[kDepthOuter];
+#pragma unroll
+            for (int k = 0; k < kDepthOuter; ++k) {
+                const int32_t x = k0 + k - pad;
+                c[k] = x >= 0 ? ci[kBackward ? q - x : q + x] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < kDepthOuter; ++k) v[k] = k0 + k >= pad ? ld_level(J.depth + c[k]) : 0;
+            for (;;) {
+                bool pend = false;
+#pragma unroll
+                for (int k = 0; k < kDepthOuter; ++k) pend |= v[k] < 0;
+                if (!__any(pend)) break;
+                if (wait_expired(polls, t0, ctl, limit)) {
+                    stop = true;
+                    break;
+                }
+#pragma unroll
+                for (int k = 0; k < kDepthOuter; ++k)
+                    if (v[k] < 0) v[k] = ld_level(J.depth + c[k]);
+            }
+            polls = 0;
+#pragma unroll
+            for (int k = 0; k < kDepthOuter; ++k) best = max(best, v[k]);
+        }
+        int32_t e[kDepthSlots], c[kDepthSlots];
+#pragma unroll
+        for (int u = 0; u < kDepthSlots; ++u) {
+            e[u] = u;
+            c[u] = u < w ? cw[u * kWave + lane] : kOwn + lane;
+        }
+        bool done = !has;
+        uint64_t left = __ballot(has);
+        if (!stop) do {
+            int32_t cn[kDepthSlots], v[kDepthSlots];
+#pragma unroll
+            for (int u = 0; u < kDepthSlots; ++u) cn[u] = cw[(e[u] + kDepthSlots) * kWave + lane];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < kDepthSlots; ++u) v[u] = lw[c[u]];
+            bool more = false;
+#pragma unroll
+            for (int u = 0; u < kDepthSlots; ++u) {
+                const bool ok = e[u] < w && v[u] >= 0;
+                best = max(best, ok ? v[u] : 0);
+                e[u] += ok ? kDepthSlots : 0;
+                more |= e[u] < w;
+                c[u] = ok && e[u] < w ? cn[u] : c[u];
+            }
+            const bool fin = !done && !more;
+            const uint64_t m = __ballot(fin);
+            if (m && fin) {
+                jitter((uint32_t)i);
+                lw[kOwn + lane] = best + 1;
+                __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            done = done || fin;
+            left &= ~m;
+        } while (left);
+        if (stop && !done) __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+}
+
+__global__ __launch_bounds__(128) void k_depth_blocks(int32_t n, LevelJob j0, LevelJob j1, Ctl* ctl,
+                                                      uint64_t spin_limit) {
+    // entries + one slot round past the last + the fill's rounding
+    __shared__ int32_t cw[(kWinEntries + 2 * kDepthSlots) * kWave];
+    __shared__ int32_t lwsh[(kWinBlocks + 1) * kWave];
+    __shared__ uint32_t sh_ticket;
+    const LevelJob J = (blockIdx.x & 1) ? j1 : j0;
+    if (!xcd_member(J.tctl)) return;
+    LdsLevel* lw = (LdsLevel*)lwsh;
+    if (J.desc) depth_blocks<true>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket);
+    else depth_blocks<false>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket);
+}
+
 // Rows sorted by level (counting sort): hist, scan (shared scan kernel),
 // scatter.  The order inside a level is whatever the atomics give; any
 // order that lists every level before the next is a valid schedule, and the
@@ -1155,6 +1323,13 @@ hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_level_scatter, dim3((n + 255) / 256), dim3(256), 0, s, n, depth, off,
                        hist + max_depth, perm);
+    return hipGetLastError();
+}
+
+hipError_t launch_depth_blocks(int32_t n, const LevelJob& j0, const LevelJob& j1, Ctl* ctl, uint64_t spin_limit,
+                               int32_t grid, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_depth_blocks, dim3(grid * kXcds), dim3(2 * kWave), 0, s, n, j0, j1, ctl, spin_limit);
     return hipGetLastError();
 }
 

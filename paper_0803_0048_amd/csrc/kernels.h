@@ -103,6 +103,7 @@ struct LevelJob {
     int desc;
     int32_t* depth;
     Ctl* tctl;
+    const uint8_t* wcnt = nullptr;  // window entries of every node (rows of F only; k_block_stats)
 };
 // level of every node (1 + max level of its dependencies) for one job, or two
 // independent jobs in one launch (alternate wavefronts; j1 may be null).
@@ -111,6 +112,10 @@ struct LevelJob {
 // those of one XCD per job working).  Abort and watchdog state live in ctl.
 hipError_t launch_depth(int32_t n, const LevelJob& j0, const LevelJob* j1, Ctl* ctl, uint64_t spin_limit,
                         int32_t grid, bool one_xcd, hipStream_t s);
+// the same for both DAGs of F (j0 forward, j1 backward, wcnt set and at most
+// kWinEntries), by blocks of 64 consecutive nodes: grid workgroups per XCD
+hipError_t launch_depth_blocks(int32_t n, const LevelJob& j0, const LevelJob& j1, Ctl* ctl, uint64_t spin_limit,
+                               int32_t grid, hipStream_t s);
 // perm = nodes sorted by level (counting sort); levels are 1 .. max_depth
 // (depth[i] >= 1); hist needs 2 * max_depth ints
 hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth, int32_t* hist,

@@ -536,6 +536,7 @@ constexpr int32_t kLaneWaves = 128;
 // workgroups of the block kernel on its XCD (random banded n=160,000 ILU(2),
 // both sweeps: 16 / 24 / 28 / 32 / 40: 8.8 / 6.6 / 6.4 / 6.4 / 6.7 ms)
 constexpr int32_t kBlockGroups = 28;
+constexpr int32_t kLevelBlockGroups = 28;  // the same for the levels by blocks
 // Both substitutions in one launch on one compute unit: small systems of
 // short rows, as long as its loads (about 1 ns per entry of F for both sweeps)
 // take less than the levels would through the L2 (2-D 127 x 127 ILU(2) 0.20
@@ -695,6 +696,18 @@ tpilu_status build_dep_positions(tpilu_ctx ctx, tpilu_pattern pat) {
     return TPILU_OK;
 }
 
+// Levels by blocks of 64 consecutive rows: when a block's rows wait on few of
+// each other (random banded ILU(2): 9 rounds a block).  Where rows wait on
+// their direct predecessor (stencils; counted as 64 rounds) the blocks run
+// their chains one after the other: 2-D 400^2 ILU(1) 33 ms against 5.2 ms for
+// all of Phase I, 27-point 50^3 ILU(1) 15.2 against 12.5.
+constexpr int64_t kLevelBlockRounds = 16;
+bool levels_by_blocks(tpilu_ctx ctx, tpilu_pattern pat) {
+    const int64_t blocks = (pat->n + 63) / 64;
+    return ctx->placement != 1 && std::max(pat->bst.max_win_l, pat->bst.max_win_u) <= kWinEntries &&
+           (int64_t)std::max(pat->bst.rounds_l, pat->bst.rounds_u) <= 2 * kLevelBlockRounds * blocks;
+}
+
 // Levels of one or two dependency DAGs (computed in one launch, so their
 // chains overlap) and their nodes sorted by level (the ticket order of the
 // kernels that walk them).  deps = number of edges: with long dependency
@@ -711,6 +724,7 @@ struct LevelSpec {
     int4* rec = nullptr;
     int4* head = nullptr;
     int32_t* nchunk = nullptr;  // host, set by finish_levels
+    const uint8_t* wcnt = nullptr;  // window entries, when the levels go by blocks
 };
 
 // Enqueue the level computation on stream s without waiting for it: the
@@ -741,7 +755,7 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     LevelJob jb[2];
     for (int q = 0; q < njobs; ++q) {
         HIPCHK(ctx, launch_fill_i32(js[q].depth, n, -1, s));
-        jb[q] = LevelJob{js[q].G, js[q].desc, js[q].depth, q == 0 ? pat->ctl : ctl2};
+        jb[q] = LevelJob{js[q].G, js[q].desc, js[q].depth, q == 0 ? pat->ctl : ctl2, js[q].wcnt};
     }
     HIPCHK(ctx, launch_fill_pending(nullptr, 0, pat->ctl, true, s));
     HIPCHK(ctx, launch_fill_pending(nullptr, 0, ctl2, false, s));
@@ -751,7 +765,10 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     // same XCDs then slow down (6.2 -> 11 ms), and Phase I as a whole gains
     // nothing (27.2 vs 30.1 ms; 27-point 50^3 ILU(3) 50.1 vs 53.0 ms)
     const bool lv_xcd = grid > 0 && ctx->placement == 2;
-    HIPCHK(ctx, launch_depth(n, jb[0], njobs > 1 ? &jb[1] : nullptr, pat->ctl, ctx->spin_limit, grid, lv_xcd, s));
+    if (js[0].wcnt)
+        HIPCHK(ctx, launch_depth_blocks(n, jb[0], jb[1], pat->ctl, ctx->spin_limit, kLevelBlockGroups, s));
+    else
+        HIPCHK(ctx, launch_depth(n, jb[0], njobs > 1 ? &jb[1] : nullptr, pat->ctl, ctx->spin_limit, grid, lv_xcd, s));
     HIPCHK(ctx, launch_fill_i32(dmax, 32, 0, s));
     for (int q = 0; q < njobs; ++q) {
         HIPCHK(ctx, launch_max_i32(js[q].depth, n, dmax + 16 * q, s));
@@ -1258,6 +1275,10 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         ljobs[q].nchunk = &L.nchunk;
         L.rec = ljobs[q].rec;
         L.head = ljobs[q].head;
+    }
+    if (levels_by_blocks(ctx, P)) {
+        ljobs[0].wcnt = P->wcntL;
+        ljobs[1].wcnt = P->wcntU;
     }
     AuxJoin aux_join;
     int32_t* ldmax = nullptr;

@@ -134,3 +134,20 @@ def test_special_values(shape):
     assert torch.isnan(x[A.n // 3])
     T.apply(pat, f, torch.ones_like(bad))
     T.check(pat)
+
+
+@pytest.mark.parametrize("n,k", [(64, 1), (700, 2), (1984, 1), (1985, 2), (4097, 2), (20000, 1)])
+def test_levels_by_blocks(n, k):
+    """The depths that the blocks of 64 rows find are those of a sequential walk."""
+    A = inputs.random_banded(n, 3, band=min(n // 2, 300 + n // 2))
+    rp, ci, _, _, _ = oracle.ilu(A, k)
+    lo, up = np.zeros(n, np.int64), np.zeros(n, np.int64)
+    for i in range(n):
+        c = ci[rp[i]:rp[i + 1]]
+        lo[i] = 1 + max(lo[c[c < i]], default=0)
+    for i in range(n - 1, -1, -1):
+        c = ci[rp[i]:rp[i + 1]]
+        up[i] = 1 + max(up[c[c > i]], default=0)
+    dev = torch.device("cuda")
+    info = T.symbolic(torch.from_numpy(A.rowptr).to(dev), torch.from_numpy(A.col).to(dev), k).info
+    assert (info["depth_l"], info["depth_u"]) == (lo.max(), up.max())
