@@ -143,6 +143,7 @@ struct SymWs {
 };
 
 constexpr int32_t kSymSortMax = 512;  // longest row the sorting network orders
+constexpr int32_t kSymRankMax = 256;  // longest row ordered by counting smaller columns
 
 // exclusive prefix sum over the wavefront's lanes
 __device__ __forceinline__ int32_t wave_excl_sum(int32_t v, int32_t& total) {
@@ -218,7 +219,8 @@ __device__ __forceinline__ void sym_emit_sorted(int32_t i, const int64_t* __rest
     }
 }
 
-__device__ __forceinline__ void sym_row(int32_t i, const int64_t* __restrict__ rpA,
+// false: the row does not fit in the maps
+__device__ __forceinline__ bool sym_row(int32_t i, const int64_t* __restrict__ rpA,
                                         const int32_t* __restrict__ ciA, int32_t k, int mode,
                                         int32_t* __restrict__ cnt, const int64_t* __restrict__ rpF,
                                         int32_t* __restrict__ ciF, uint8_t* __restrict__ lvF,
@@ -291,23 +293,20 @@ __device__ __forceinline__ void sym_row(int32_t i, const int64_t* __restrict__ r
         cur = nxt;
     }
     wave_sync();
-    if (uniform(W.ctr[2])) {
-        if (mode == 0 && lane == 0) cnt[i] = -1;
-        return;
-    }
+    if (uniform(W.ctr[2])) return false;
     if (W.bm_bits) {
         int32_t mine = 0;
         for (uint32_t sl = lane; sl <= W.emask; sl += kWave) mine += W.ek[sl] != kEmpty;
         for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
         if (mode == 0) {
             if (lane == 0) cnt[i] = mine;
-            return;
+            return true;
         }
         // long rows: through the bitmap; short ones: the sorting network
         // below costs less than a pass over the column range
         if (mine > kSymSortMax) {
             sym_emit_sorted(i, rpF, ciF, lvF, diagF, W);
-            return;
+            return true;
         }
     }
     // compact the row
@@ -323,7 +322,31 @@ __device__ __forceinline__ void sym_row(int32_t i, const int64_t* __restrict__ r
     const int32_t len = uniform(W.ctr[3]);
     if (mode == 0) {
         if (lane == 0) cnt[i] = len;
-        return;
+        return true;
+    }
+    // short rows: every lane counts the columns smaller than its own, four to
+    // a broadcast read.  (The network below takes len log^2 len / 64 dependent
+    // exchanges: random banded n=160,000 ILU(2), rows of 164 entries, fill
+    // pass of the 1,024-entry tier 6.0 ms; by counting, in the smaller tiers,
+    // 2.0 ms.)
+    if (W.bm_bits && len <= kSymRankMax) {
+        if (lane < 3 && len + lane < ((len + 3) & ~3)) W.ok[len + lane] = kBig;
+        wave_sync();
+        const int64_t base = rpF[i];
+        for (int32_t e0 = 0; e0 < len; e0 += kWave) {
+            const int32_t key = e0 + lane < len ? W.ok[e0 + lane] : kBig;
+            int32_t r = 0;
+            for (int32_t x = 0; x < len; x += 4) {
+                const int4 o = *reinterpret_cast<const int4*>(W.ok + x);
+                r += (o.x < key) + (o.y < key) + (o.z < key) + (o.w < key);
+            }
+            if (key != kBig) {
+                ciF[base + r] = key;
+                lvF[base + r] = static_cast<uint8_t>(min(W.ol[e0 + lane], 255));
+                if (key == i) diagF[i] = static_cast<int32_t>(base + r);
+            }
+        }
+        return true;
     }
     // sort (column, level) by column: bitonic network over the next power of
     // two, padded with kBig (it fits: the map's capacity is a power of two)
@@ -356,40 +379,55 @@ __device__ __forceinline__ void sym_row(int32_t i, const int64_t* __restrict__ r
         lvF[base + e] = static_cast<uint8_t>(min(W.ol[e], 255));
         if (key == i) diagF[i] = static_cast<int32_t>(base + e);
     }
+    return true;
 }
 
-// kEnd: capacity of the endpoint map (and of the compacted row)
-template <int kEnd>
-__global__ __launch_bounds__(64) void k_sym_rows_lds(int32_t n, const int64_t* __restrict__ rpA,
+// A tier's LDS maps: kEnd the capacity of the endpoint map (and of the
+// compacted row), kFront of the frontier maps and lists.  A wavefront clears
+// its maps for every row and walks A's rows with dependent loads, so the
+// smallest maps that hold a row are the fastest twice over: least to clear,
+// most wavefronts on a CU (kSymWaves).  7-point 64^3 ILU(1), count + fill:
+// 3.5 ms with 1,024-entry maps for every row, 0.65 here; random banded
+// n=160,000 ILU(2) 8.7 -> 3.3 ms.  The compacted row and the bitmap of
+// the long rows take the place of the frontier maps, which are done by then.
+// In the count pass a row that does not fit goes to the next tier's list.
+template <int kEnd, int kFront>
+__global__ __launch_bounds__(64) void k_sym_rows_lds(const int64_t* __restrict__ rpA,
                                                      const int32_t* __restrict__ ciA, int32_t k,
-                                                     const int32_t* __restrict__ row_list,
-                                                     int32_t n_rows, int mode,
-                                                     int32_t* __restrict__ cnt,
+                                                     SymLists lists, int mode, int32_t* __restrict__ cnt,
                                                      const int64_t* __restrict__ rpF,
                                                      int32_t* __restrict__ ciF,
                                                      uint8_t* __restrict__ lvF,
-                                                     int32_t* __restrict__ diagF,
-                                                     const uint8_t* __restrict__ tier_of, int tier) {
+                                                     int32_t* __restrict__ diagF, int tier) {
+    constexpr int kOut = kEnd > 4 * kFront ? 2 * kEnd : 0;  // (column, level) when the frontier space is too small
     __shared__ int32_t ek[kEnd], ev[kEnd];
-    __shared__ int32_t bk[kSymFrontCap], bv[kSymFrontCap], ck[kSymFrontCap], cv[kSymFrontCap];
-    __shared__ int32_t f0v[kSymFrontCap], f0m[kSymFrontCap], f1v[kSymFrontCap], f1m[kSymFrontCap];
-    __shared__ int32_t ok[kEnd], ol[kEnd];
+    __shared__ __attribute__((aligned(16))) int32_t front[8 * kFront];
+    __shared__ __attribute__((aligned(16))) int32_t outsh[kOut ? kOut : 4];
     __shared__ int32_t ctr[4];
     SymWs W;
-    W.ek = ek; W.ev = ev; W.bk = bk; W.bv = bv; W.ck = ck; W.cv = cv;
-    W.fv[0] = f0v; W.fm[0] = f0m; W.fv[1] = f1v; W.fm[1] = f1m;
-    W.ok = ok; W.ol = ol; W.ctr = ctr;
-    W.emask = kEnd - 1; W.fmask = kSymFrontCap - 1; W.fcap = kSymFrontCap;
+    W.ek = ek; W.ev = ev;
+    W.bk = front; W.bv = front + kFront; W.ck = front + 2 * kFront; W.cv = front + 3 * kFront;
+    W.fv[0] = front + 4 * kFront; W.fm[0] = front + 5 * kFront;
+    W.fv[1] = front + 6 * kFront; W.fm[1] = front + 7 * kFront;
+    W.ok = kOut ? outsh : front;
+    W.ol = W.ok + kEnd;
+    W.ctr = ctr;
+    W.emask = kEnd - 1; W.fmask = kFront - 1; W.fcap = kFront;
     W.eprobe = kProbeMax;
-    W.bm = reinterpret_cast<uint32_t*>(ok);
+    W.bm = reinterpret_cast<uint32_t*>(W.ok);
     W.bm_bits = (uint32_t)kEnd * 32u;
+    const int32_t* list = lists.rows + (size_t)tier * lists.n;
+    const int32_t n_rows = lists.count[tier];
     for (int32_t r = blockIdx.x; r < n_rows; r += gridDim.x) {
-        int32_t i = row_list ? row_list[r] : r;
-        if (mode == 1 && tier_of && tier_of[i] != tier) continue;  // built by another tier
-        sym_row(i, rpA, ciA, k, mode, cnt, rpF, ciF, lvF, diagF, W);
+        const int32_t i = list[r];
+        if (mode == 1 && lists.tier_of[i] != tier) continue;  // built by a later tier
+        const bool fits = sym_row(i, rpA, ciA, k, mode, cnt, rpF, ciF, lvF, diagF, W);
+        if (!fits && mode == 0 && lane_id() == 0) {
+            lists.rows[(size_t)(tier + 1) * lists.n + atomicAdd(&lists.count[tier + 1], 1)] = i;
+            lists.tier_of[i] = static_cast<uint8_t>(tier + 1);
+        }
         wave_sync();
     }
-    (void)n;
 }
 
 __host__ __device__ size_t sym_global_scratch_ints(int32_t n, uint32_t gcap) {
@@ -399,15 +437,12 @@ __host__ __device__ size_t sym_global_scratch_ints(int32_t n, uint32_t gcap) {
 
 __global__ __launch_bounds__(64) void k_sym_rows_global(int32_t n, const int64_t* __restrict__ rpA,
                                                         const int32_t* __restrict__ ciA, int32_t k,
-                                                        const int32_t* __restrict__ row_list,
-                                                        int32_t n_rows, int mode,
-                                                        int32_t* __restrict__ cnt,
+                                                        SymLists lists, int mode, int32_t* __restrict__ cnt,
                                                         const int64_t* __restrict__ rpF,
                                                         int32_t* __restrict__ ciF,
                                                         uint8_t* __restrict__ lvF,
                                                         int32_t* __restrict__ diagF,
-                                                        int32_t* gscratch, uint32_t gcap,
-                                                        const uint8_t* __restrict__ tier_of) {
+                                                        int32_t* gscratch, uint32_t gcap) {
     int32_t* base = gscratch + (size_t)blockIdx.x * sym_global_scratch_ints(n, gcap);
     SymWs W;
     W.ek = base; W.ev = base + gcap;
@@ -421,30 +456,29 @@ __global__ __launch_bounds__(64) void k_sym_rows_global(int32_t n, const int64_t
     W.eprobe = gcap;  // sized for any row (gcap >= 2n + 2): never gives up
     W.bm = nullptr;
     W.bm_bits = 0;
+    const int32_t* list = lists.rows + (size_t)kSymGlobal * lists.n;
+    const int32_t n_rows = lists.count[kSymGlobal];
     for (int32_t r = blockIdx.x; r < n_rows; r += gridDim.x) {
-        int32_t i = row_list ? row_list[r] : r;
-        if (mode == 1 && tier_of && tier_of[i] != 2) continue;
-        sym_row(i, rpA, ciA, k, mode, cnt, rpF, ciF, lvF, diagF, W);
+        sym_row(list[r], rpA, ciA, k, mode, cnt, rpF, ciF, lvF, diagF, W);
         wave_sync();
     }
 }
 
-hipError_t launch_sym_rows(int tier, int32_t n, const int64_t* rpA, const int32_t* ciA,
-                           int32_t k, const int32_t* row_list, int32_t n_rows, int mode,
-                           int32_t* cnt, const int64_t* rpF, int32_t* ciF, uint8_t* lvF,
-                           int32_t* diagF, const uint8_t* tier_of, int32_t* gscratch, uint32_t gcap,
-                           int32_t grid, hipStream_t s) {
-    if (n_rows <= 0) return hipSuccess;
-    if (tier == 2) {
-        hipLaunchKernelGGL(k_sym_rows_global, dim3(grid), dim3(64), 0, s, n, rpA, ciA, k,
-                           row_list, n_rows, mode, cnt, rpF, ciF, lvF, diagF, gscratch, gcap, tier_of);
-    } else if (tier == 1) {
-        hipLaunchKernelGGL(k_sym_rows_lds<kSymEndCapLong>, dim3(grid), dim3(64), 0, s, n, rpA, ciA, k,
-                           row_list, n_rows, mode, cnt, rpF, ciF, lvF, diagF, tier_of, 1);
-    } else {
-        hipLaunchKernelGGL(k_sym_rows_lds<kSymEndCap>, dim3(grid), dim3(64), 0, s, n, rpA, ciA, k,
-                           row_list, n_rows, mode, cnt, rpF, ciF, lvF, diagF, tier_of, 0);
-    }
+hipError_t launch_sym_rows(int tier, int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t k,
+                           const SymLists& lists, int mode, int32_t* cnt, const int64_t* rpF, int32_t* ciF,
+                           uint8_t* lvF, int32_t* diagF, int32_t* gscratch, uint32_t gcap, int32_t grid,
+                           hipStream_t s) {
+    if (n <= 0 || grid <= 0) return hipSuccess;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, s, rpA, ciA, k, lists, mode, cnt, rpF, ciF, lvF, diagF, tier);
+    };
+    if (tier == 0) go(k_sym_rows_lds<128, 64>);
+    else if (tier == 1) go(k_sym_rows_lds<512, 256>);
+    else if (tier == kSymMid) go(k_sym_rows_lds<1024, 512>);
+    else if (tier == kSymLong) go(k_sym_rows_lds<4096, 512>);
+    else
+        hipLaunchKernelGGL(k_sym_rows_global, dim3(grid), dim3(64), 0, s, n, rpA, ciA, k, lists, mode, cnt, rpF, ciF,
+                           lvF, diagF, gscratch, gcap);
     return hipGetLastError();
 }
 
@@ -452,10 +486,11 @@ hipError_t launch_sym_rows(int tier, int32_t n, const int64_t* rpA, const int32_
 // sum over stored a_ih, h < i, of the entries of row h right of h: every
 // position of level <= 1 of row i is one of those terms (Def. 2.3 with one
 // interior vertex), so for k = 1 it bounds the row's length, counting
-// duplicates.  Rows whose bound passes `limit` go straight to the larger
-// maps of tier 1: built in tier 0 they would only fill its map and be given
-// up.  The routing only changes where a row is built, never what it holds
-// (a row tier 1 cannot hold still goes on to the global tier).
+// duplicates (k = 0: the row's length itself).  For k > 1 the length is
+// guessed as ub k^2 / 2.  Rows whose ub passes the capacity of tier kSymMid
+// go straight to the larger maps: built there they would only fill its map
+// and be given up.  The routing only changes where a row is built, never what
+// it holds (a row that a tier cannot hold goes on to the next).
 __global__ void k_row_upper(int32_t n, const int64_t* __restrict__ rpA, const int32_t* __restrict__ ciA,
                             int32_t* __restrict__ nup) {
     const int32_t h = blockIdx.x * blockDim.x + threadIdx.x;
@@ -470,54 +505,47 @@ __global__ void k_row_upper(int32_t n, const int64_t* __restrict__ rpA, const in
     nup[h] = (int32_t)(end - lo);
 }
 
-__global__ void k_route_rows(int32_t n, const int64_t* __restrict__ rpA, const int32_t* __restrict__ ciA,
-                             const int32_t* __restrict__ nup, int64_t limit, int32_t* __restrict__ list0,
-                             int32_t* __restrict__ list1, int32_t* __restrict__ counts, uint8_t* __restrict__ tier_of) {
+// most expected entries of a row that starts in a tier: half of tier 0's map,
+// seven eighths of tier 1's (for k > 1 twice that, the guess being high for
+// stencils), and kSymMid's limit on ub
+constexpr int64_t kSymRoute0 = 64, kSymRoute1 = 448, kSymRouteMid = (1024 - 1024 / 8) * 5 / 4;
+
+__global__ __launch_bounds__(256) void k_route_rows(int32_t n, const int64_t* __restrict__ rpA,
+                                                    const int32_t* __restrict__ ciA,
+                                                    const int32_t* __restrict__ nup, int32_t k, SymLists lists) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t a0 = rpA[i], a1 = rpA[i + 1];
-    int64_t ub = a1 - a0;
-    for (int64_t p = a0; p < a1 && ub <= limit; ++p) {
-        const int32_t h = ciA[p];
-        if (h >= i) break;
-        ub += nup[h];
+    int tier = -1;
+    if (i < n) {
+        const int64_t a0 = rpA[i], a1 = rpA[i + 1];
+        int64_t ub = a1 - a0;
+        for (int64_t p = a0; k > 0 && p < a1 && ub <= kSymRouteMid; ++p) {
+            const int32_t h = ciA[p];
+            if (h >= i) break;
+            ub += nup[h];
+        }
+        const int64_t guess = k > 1 ? ub * min(k, 64) * min(k, 64) / 2 : ub;
+        tier = ub > kSymRouteMid ? kSymLong
+               : guess <= kSymRoute0 ? 0
+               : guess <= (k > 1 ? 2 * kSymRoute1 : kSymRoute1) ? 1 : kSymMid;
+        lists.tier_of[i] = static_cast<uint8_t>(tier);
     }
-    if (ub > limit) {
-        list1[atomicAdd(&counts[1], 1)] = i;
-        tier_of[i] = 1;
-    } else {
-        list0[atomicAdd(&counts[0], 1)] = i;
+    // one atomic per wavefront and tier
+    for (int t = 0; t <= kSymLong; ++t) {
+        const uint64_t m = __ballot(tier == t);
+        if (!m) continue;
+        int32_t at = 0;
+        if (lane_id() == __builtin_ctzll(m)) at = atomicAdd(&lists.count[t], __popcll(m));
+        at = __shfl(at, __builtin_ctzll(m));
+        if (tier == t)
+            lists.rows[(size_t)t * lists.n + at + __popcll(m & ((1ull << lane_id()) - 1ull))] = i;
     }
 }
 
-hipError_t launch_route_rows(int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t* nup, int64_t limit,
-                             int32_t* list0, int32_t* list1, int32_t* counts, uint8_t* tier_of, hipStream_t s) {
+hipError_t launch_route_rows(int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t* nup, int32_t k,
+                             const SymLists& lists, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_row_upper, dim3((n + 255) / 256), dim3(256), 0, s, n, rpA, ciA, nup);
-    hipLaunchKernelGGL(k_route_rows, dim3((n + 255) / 256), dim3(256), 0, s, n, rpA, ciA, nup, limit, list0, list1,
-                       counts, tier_of);
-    return hipGetLastError();
-}
-
-int64_t sym_route_limit() { return (int64_t)(kSymEndCap - kSymEndCap / 8) * 5 / 4; }
-
-__global__ void k_collect_overflow(int32_t n_rows, const int32_t* __restrict__ list,
-                                   const int32_t* __restrict__ cnt, int32_t* row_list, int32_t* n_over,
-                                   uint8_t* tier_of, int tier) {
-    const int32_t r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rows) return;
-    const int32_t i = list ? list[r] : r;
-    if (cnt[i] < 0) {
-        row_list[atomicAdd(n_over, 1)] = i;
-        tier_of[i] = static_cast<uint8_t>(tier);
-    }
-}
-
-hipError_t launch_collect_overflow(int32_t n_rows, const int32_t* list, const int32_t* cnt, int32_t* row_list,
-                                   int32_t* n_over, uint8_t* tier_of, int tier, hipStream_t s) {
-    if (n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_collect_overflow, dim3((n_rows + 255) / 256), dim3(256), 0, s, n_rows, list, cnt,
-                       row_list, n_over, tier_of, tier);
+    if (k > 0) hipLaunchKernelGGL(k_row_upper, dim3((n + 255) / 256), dim3(256), 0, s, n, rpA, ciA, nup);
+    hipLaunchKernelGGL(k_route_rows, dim3((n + 255) / 256), dim3(256), 0, s, n, rpA, ciA, nup, k, lists);
     return hipGetLastError();
 }
 
@@ -613,19 +641,28 @@ hipError_t launch_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* tmp,
 }
 
 // ------------------------------------------------------------------------------------
-// A -> F slot map: merge of two sorted rows, one thread per row
+// A -> F slot map: sixteen lanes per row, each searching its entries in the
+// sorted row of F (a thread merging two whole rows read them lane by lane in
+// lines of its own: 0.24 ms against 0.035 at random banded n=160,000 ILU(2))
 // ------------------------------------------------------------------------------------
-__global__ void k_a2f(int32_t n, const int64_t* __restrict__ rpA, const int32_t* __restrict__ ciA,
-                      const int64_t* __restrict__ rpF, const int32_t* __restrict__ ciF,
-                      int32_t* __restrict__ a2f, uint32_t* status) {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+constexpr int kA2fLanes = 16;
+__global__ __launch_bounds__(256) void k_a2f(int32_t n, const int64_t* __restrict__ rpA,
+                                             const int32_t* __restrict__ ciA, const int64_t* __restrict__ rpF,
+                                             const int32_t* __restrict__ ciF, int32_t* __restrict__ a2f,
+                                             uint32_t* status) {
+    const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kA2fLanes;
     if (i >= n) return;
-    int64_t q = rpF[i], qe = rpF[i + 1];
-    for (int64_t p = rpA[i]; p < rpA[i + 1]; ++p) {
-        int32_t c = ciA[p];
-        while (q < qe && ciF[q] < c) ++q;
-        if (q < qe && ciF[q] == c) {
-            a2f[p] = static_cast<int32_t>(q);
+    const int64_t qb = rpF[i], qe = rpF[i + 1], pe = rpA[i + 1];
+    for (int64_t p = rpA[i] + threadIdx.x % kA2fLanes; p < pe; p += kA2fLanes) {
+        const int32_t c = ciA[p];
+        int64_t lo = qb, hi = qe;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (ciF[mid] < c) lo = mid + 1;
+            else hi = mid;
+        }
+        if (lo < qe && ciF[lo] == c) {
+            a2f[p] = static_cast<int32_t>(lo);
         } else {
             a2f[p] = -1;
             atomicOr(status, kValBadCol);
@@ -635,8 +672,8 @@ __global__ void k_a2f(int32_t n, const int64_t* __restrict__ rpA, const int32_t*
 
 hipError_t launch_a2f(int32_t n, const int64_t* rpA, const int32_t* ciA, const int64_t* rpF,
                       const int32_t* ciF, int32_t* a2f, uint32_t* status, hipStream_t s) {
-    hipLaunchKernelGGL(k_a2f, dim3((n + 255) / 256), dim3(256), 0, s, n, rpA, ciA, rpF, ciF, a2f,
-                       status);
+    const int64_t blocks = ((int64_t)n * kA2fLanes + 255) / 256;
+    hipLaunchKernelGGL(k_a2f, dim3((unsigned)blocks), dim3(256), 0, s, n, rpA, ciA, rpF, ciF, a2f, status);
     return hipGetLastError();
 }
 
@@ -943,21 +980,37 @@ hipError_t launch_tsched(int32_t n, const int64_t* rpF, const int32_t* diagF, co
 // ------------------------------------------------------------------------------------
 // pattern statistics
 // ------------------------------------------------------------------------------------
-__global__ void k_stats(int32_t n, const int64_t* __restrict__ rpF,
-                        const int32_t* __restrict__ diagF, PatStats* st) {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int64_t rs = rpF[i], re = rpF[i + 1], d = diagF[i];
-    atomicMax(&st->max_row, static_cast<int32_t>(re - rs));
-    atomicMax(&st->max_lrow, static_cast<int32_t>(d - rs));
-    atomicMax(&st->max_upart, static_cast<int32_t>(re - d - 1));
-    atomicAdd(&st->nnz_l, static_cast<unsigned long long>(d - rs));
+// (one atomic per wavefront and quantity, not per row: those took 0.12 ms at
+// 160,000 rows, on one address)
+__global__ __launch_bounds__(256) void k_stats(int32_t n, const int64_t* __restrict__ rpF,
+                                               const int32_t* __restrict__ diagF, PatStats* st) {
+    int32_t mrow = 0, ml = 0, mu = 0;
+    int64_t nl = 0;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t rs = rpF[i], re = rpF[i + 1], d = diagF[i];
+        mrow = max(mrow, static_cast<int32_t>(re - rs));
+        ml = max(ml, static_cast<int32_t>(d - rs));
+        mu = max(mu, static_cast<int32_t>(re - d - 1));
+        nl += d - rs;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        mrow = max(mrow, __shfl_xor(mrow, off));
+        ml = max(ml, __shfl_xor(ml, off));
+        mu = max(mu, __shfl_xor(mu, off));
+        nl += __shfl_xor(nl, off);
+    }
+    if (lane_id() == 0) {
+        atomicMax(&st->max_row, mrow);
+        atomicMax(&st->max_lrow, ml);
+        atomicMax(&st->max_upart, mu);
+        atomicAdd(&st->nnz_l, static_cast<unsigned long long>(nl));
+    }
 }
 
 hipError_t launch_stats(int32_t n, const int64_t* rpF, const int32_t* diagF, PatStats* st,
                         hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_stats, dim3((n + 255) / 256), dim3(256), 0, s, n, rpF, diagF, st);
+    hipLaunchKernelGGL(k_stats, dim3(std::min((n + 255) / 256, 64)), dim3(256), 0, s, n, rpF, diagF, st);
     return hipGetLastError();
 }
 
@@ -1373,7 +1426,7 @@ __global__ void k_max_i32(const int32_t* __restrict__ p, int64_t n, int32_t* out
 
 hipError_t launch_max_i32(const int32_t* p, int64_t n, int32_t* out, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
+    int blocks = (int)std::min<int64_t>((n + 255) / 256, 64);  // an atomic per wavefront, on one address
     hipLaunchKernelGGL(k_max_i32, dim3(blocks), dim3(256), 0, s, p, n, out);
     return hipGetLastError();
 }

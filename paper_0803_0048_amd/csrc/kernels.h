@@ -15,32 +15,31 @@ constexpr uint32_t kValBadRowptr = 1u, kValBadCol = 2u, kValUnsorted = 4u, kValN
 hipError_t launch_validate(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci,
                            uint32_t* status, hipStream_t s);
 
-// LDS capacities of the symbolic paths: tier 0 for rows of up to about a
-// thousand entries, tier 1 (80 KB of LDS per wavefront) up to about four
-// thousand; longer rows use maps in global memory (tier 2)
-constexpr int kSymEndCap = 1024;      // endpoint map (row of F being built), tier 0
-constexpr int kSymEndCapLong = 4096;  // the same, tier 1
-constexpr int kSymFrontCap = 512;     // frontier maps and lists
+// Tiers of the symbolic row construction by the size of the LDS maps: 0 and 1
+// for rows of up to about a hundred and four hundred entries, kSymMid a
+// thousand, kSymLong (80 KB of LDS per wavefront) four thousand; longer rows
+// use maps in global memory (kSymGlobal)
+constexpr int kSymMid = 2, kSymLong = 3, kSymGlobal = 4, kSymTiers = 5;
+// The rows of each tier (device memory): rows[tier * n ..], their number, and
+// the tier that builds a row.
+struct SymLists {
+    int32_t* rows;
+    int32_t* count;  // [kSymTiers]
+    uint8_t* tier_of;
+    int32_t n;
+};
 
-// Count (mode 0) or fill (mode 1) the level-<=k pattern of rows [0, n) (or of
-// the rows in row_list when non-null) with the maps of `tier`; a row that
-// does not fit gets cnt = -1 (mode 0).  In mode 1 a row is only built by the
-// tier that tier_of (nullable: tier 0 for all) records for it.
-hipError_t launch_sym_rows(int tier, int32_t n, const int64_t* rpA, const int32_t* ciA,
-                           int32_t k, const int32_t* row_list, int32_t n_rows, int mode,
-                           int32_t* cnt, const int64_t* rpF, int32_t* ciF, uint8_t* lvF,
-                           int32_t* diagF, const uint8_t* tier_of, int32_t* gscratch, uint32_t gcap,
-                           int32_t grid, hipStream_t s);
+// Count (mode 0) or fill (mode 1) the level-<=k pattern of a tier's rows; a
+// row that does not fit (mode 0) moves to the next tier's list.  In mode 1 a
+// row is only built by the tier that tier_of records for it.
+hipError_t launch_sym_rows(int tier, int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t k,
+                           const SymLists& lists, int mode, int32_t* cnt, const int64_t* rpF, int32_t* ciF,
+                           uint8_t* lvF, int32_t* diagF, int32_t* gscratch, uint32_t gcap, int32_t grid,
+                           hipStream_t s);
 __host__ __device__ size_t sym_global_scratch_ints(int32_t n, uint32_t gcap);  // per block
-
-// rows (of `list`, or 0..n_rows-1) with cnt < 0 -> row_list, *n_over; tier_of[row] = tier
-// rows whose one-step bound passes `limit` into list1 (and tier_of 1),
-// the others into list0; counts[0], counts[1] are their running sizes (pre-set)
-hipError_t launch_route_rows(int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t* nup, int64_t limit,
-                             int32_t* list0, int32_t* list1, int32_t* counts, uint8_t* tier_of, hipStream_t s);
-int64_t sym_route_limit();
-hipError_t launch_collect_overflow(int32_t n_rows, const int32_t* list, const int32_t* cnt, int32_t* row_list,
-                                   int32_t* n_over, uint8_t* tier_of, int tier, hipStream_t s);
+// every row to the tier that its one-step bound suggests (counts pre-zeroed)
+hipError_t launch_route_rows(int32_t n, const int64_t* rpA, const int32_t* ciA, int32_t* nup, int32_t k,
+                             const SymLists& lists, hipStream_t s);
 
 // exclusive scan of int32 counts into int64 offsets out[0..n], out[n] = total
 hipError_t launch_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* tmp, hipStream_t s);

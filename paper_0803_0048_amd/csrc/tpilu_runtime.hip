@@ -137,6 +137,8 @@ constexpr int64_t kNarrowWidth = 32;   // n / depth below this: narrow
 // 2-D 64 x 64 ILU(1) 0.18 / 0.19 vs 0.14 / 0.16; Table 3 scale ILU(1) (40
 // rows per level, 640 entries per half) 5.2 / 6.0 vs 12.0 / 12.2.
 constexpr int64_t kXcdMaxAvg = 128;
+// wavefronts per CU that the LDS of a tier of the symbolic construction allows
+constexpr int32_t kSymWaves[] = {32, 12, 6, 2};
 constexpr int64_t kLevelLaneMax = 14;  // level computation: lane per node below this many dependencies
 constexpr int64_t kLevelWideMax = 60;  // wavefront per node: the wide window below this, else the narrow one
 constexpr int32_t kLevelWavesWide = 768;
@@ -1155,48 +1157,30 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     // ---- a2: level-of-fill pattern, count pass
     TmpBufs T{P->al, {}};
     int32_t* cnt = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);
-    int32_t* list0 = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);      // rows tier 0 builds first
-    int32_t* over_list = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);  // rows for tier 1
-    int32_t* over2_list = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);  // rows past tier 1
-    int32_t* over_n = (int32_t*)T.get(64);
-    uint8_t* tier_of = (uint8_t*)T.get((size_t)n + 4);
+    SymLists lists{};
+    lists.n = ni;
+    lists.rows = (int32_t*)T.get(sizeof(int32_t) * (size_t)n * kSymTiers);
+    lists.count = (int32_t*)T.get(64);
+    lists.tier_of = (uint8_t*)T.get((size_t)n);
     int64_t* scan_tmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(n));
-    if (!cnt || !list0 || !over_list || !over2_list || !over_n || !tier_of || !scan_tmp)
+    if (!cnt || !lists.rows || !lists.count || !lists.tier_of || !scan_tmp)
         return bail(fail(ctx, TPILU_E_NOMEM, "symbolic scratch"));
-    HIPCHK(ctx, launch_fill_i32((int32_t*)tier_of, (n + 4) / 4, 0, s));
-    HIPCHK(ctx, launch_fill_i32(over_n, 4, 0, s));
-    const int sym_grid = std::min<int64_t>(n, (int64_t)ctx->num_cu * 4);
-    // rows whose one-step bound already passes tier 0's capacity start in
-    // tier 1 (over_list[0, n_pred)); the rest (list0) start in tier 0
-    int32_t n0 = ni;
-    if (k >= 1) {
-        HIPCHK(ctx, launch_route_rows(ni, P->rpA, P->ciA, cnt, sym_route_limit(), list0, over_list, over_n + 2,
-                                      tier_of, s));
-        int32_t rc[2] = {0, 0};
-        HIPCHK(ctx, hipMemcpyAsync(rc, over_n + 2, sizeof(rc), hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipStreamSynchronize(s));
-        n0 = rc[0];
-        HIPCHK(ctx, hipMemcpyAsync(over_n, over_n + 3, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    }
-    const int32_t* l0 = k >= 1 ? list0 : nullptr;
-    trace("symbolic: count pass, rows starting in tier 0", n, n0);
-    HIPCHK(ctx, launch_sym_rows(0, ni, P->rpA, P->ciA, k, l0, n0, 0, cnt, nullptr, nullptr,
-                                nullptr, nullptr, nullptr, nullptr, 0, std::min(std::max(n0, 1), sym_grid), s));
-    HIPCHK(ctx, launch_collect_overflow(n0, l0, cnt, over_list, over_n, tier_of, 1, s));
-    int32_t n_over = 0, n_over2 = 0;
-    HIPCHK(ctx, hipMemcpyAsync(&n_over, over_n, sizeof(n_over), hipMemcpyDeviceToHost, s));
+    HIPCHK(ctx, launch_fill_i32(lists.count, 16, 0, s));
+    HIPCHK(ctx, launch_route_rows(ni, P->rpA, P->ciA, cnt, k, lists, s));
+    // the tiers follow each other without a look at their lists' lengths: a
+    // row that does not fit in one is built by the next
+    trace("symbolic: count pass, rows", n);
+    auto sym_grid = [&](int tier) { return (int32_t)std::min<int64_t>(n, (int64_t)ctx->num_cu * kSymWaves[tier]); };
+    for (int tier = 0; tier <= kSymLong; ++tier)
+        HIPCHK(ctx, launch_sym_rows(tier, ni, P->rpA, P->ciA, k, lists, 0, cnt, nullptr, nullptr, nullptr, nullptr,
+                                    nullptr, 0, sym_grid(tier), s));
+    int32_t ntier[kSymTiers] = {0};
+    HIPCHK(ctx, hipMemcpyAsync(ntier, lists.count, sizeof(ntier), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
-    if (n_over > 0) {
-        // long rows: the same construction with four times the map capacity
-        HIPCHK(ctx, launch_sym_rows(1, ni, P->rpA, P->ciA, k, over_list, n_over, 0, cnt, nullptr, nullptr,
-                                    nullptr, nullptr, nullptr, nullptr, 0, std::min(n_over, sym_grid), s));
-        HIPCHK(ctx, launch_collect_overflow(n_over, over_list, cnt, over2_list, over_n + 1, tier_of, 2, s));
-        HIPCHK(ctx, hipMemcpyAsync(&n_over2, over_n + 1, sizeof(n_over2), hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipStreamSynchronize(s));
-    }
-    P->long_rows = n_over - n_over2;
+    const int32_t n_over2 = ntier[kSymGlobal];
+    P->long_rows = ntier[kSymLong] - n_over2;
     P->overflow_rows = n_over2;
-    trace("symbolic: long rows, overflow rows", n_over - n_over2, n_over2);
+    trace("symbolic: long rows, overflow rows", P->long_rows, n_over2);
     int32_t* gscr = nullptr;
     uint32_t gcap = 0;
     int ggrid = 0;
@@ -1205,8 +1189,8 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         ggrid = std::min(n_over2, 32);
         gscr = (int32_t*)T.get(sizeof(int32_t) * sym_global_scratch_ints(ni, gcap) * (size_t)ggrid);
         if (!gscr) return bail(fail(ctx, TPILU_E_NOMEM, "symbolic global scratch"));
-        HIPCHK(ctx, launch_sym_rows(2, ni, P->rpA, P->ciA, k, over2_list, n_over2, 0, cnt, nullptr, nullptr,
-                                    nullptr, nullptr, nullptr, gscr, gcap, ggrid, s));
+        HIPCHK(ctx, launch_sym_rows(kSymGlobal, ni, P->rpA, P->ciA, k, lists, 0, cnt, nullptr, nullptr, nullptr,
+                                    nullptr, gscr, gcap, ggrid, s));
     }
     P->rpF = (int64_t*)P->take(sizeof(int64_t) * (size_t)(n + 1));
     if (!P->rpF) return bail(fail(ctx, TPILU_E_NOMEM, "rowptr"));
@@ -1226,14 +1210,12 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     if (!P->ciF || !P->lvF || !P->diagF || !P->a2f || !P->lsd || !P->sptr)
         return bail(fail(ctx, TPILU_E_NOMEM, "pattern arrays"));
     // fill pass
-    HIPCHK(ctx, launch_sym_rows(0, ni, P->rpA, P->ciA, k, l0, n0, 1, cnt, P->rpF, P->ciF, P->lvF,
-                                P->diagF, tier_of, nullptr, 0, std::min(std::max(n0, 1), sym_grid), s));
-    if (n_over > 0)
-        HIPCHK(ctx, launch_sym_rows(1, ni, P->rpA, P->ciA, k, over_list, n_over, 1, cnt, P->rpF, P->ciF,
-                                    P->lvF, P->diagF, tier_of, nullptr, 0, std::min(n_over, sym_grid), s));
-    if (n_over2 > 0)
-        HIPCHK(ctx, launch_sym_rows(2, ni, P->rpA, P->ciA, k, over2_list, n_over2, 1, cnt, P->rpF, P->ciF,
-                                    P->lvF, P->diagF, tier_of, gscr, gcap, ggrid, s));
+    for (int tier = 0; tier < kSymTiers; ++tier) {
+        if (ntier[tier] == 0) continue;
+        const int32_t grid = tier == kSymGlobal ? ggrid : std::min(ntier[tier], sym_grid(tier));
+        HIPCHK(ctx, launch_sym_rows(tier, ni, P->rpA, P->ciA, k, lists, 1, cnt, P->rpF, P->ciF, P->lvF, P->diagF, gscr,
+                                    gcap, grid, s));
+    }
     // A -> F map
     HIPCHK(ctx, launch_fill_i32((int32_t*)vstat, 16, 0, s));
     HIPCHK(ctx, launch_a2f(ni, P->rpA, P->ciA, P->rpF, P->ciF, P->a2f, vstat, s));
