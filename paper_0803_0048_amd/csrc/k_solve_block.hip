@@ -91,8 +91,8 @@ __device__ __forceinline__ void block_stats(int32_t n, const int64_t* __restrict
     }
     for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off));
     if (lane == 0) {
-        atomicAdd(rounds, sum);
-        atomicMax(max_win, most);
+        if (sum) atomicAdd(rounds, sum);
+        if (most) atomicMax(max_win, most);
     }
 }
 
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64) void k_block_stats(int32_t n, const int64_t* __
 hipError_t launch_block_stats(int32_t n, const int64_t* rpF, const int32_t* ciF, const int32_t* diagF, uint8_t* wcntL,
                               uint8_t* wcntU, BlockStats* st, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int grid = std::min((n + kWave - 1) / kWave, 4096);
+    const int grid = std::min((n + kWave - 1) / kWave, 1024);  // two atomics a wavefront, on one address
     hipLaunchKernelGGL(k_block_stats, dim3(grid, 2), dim3(64), 0, s, n, rpF, ciF, diagF, wcntL, wcntU, st);
     return hipGetLastError();
 }

@@ -682,19 +682,29 @@ hipError_t launch_a2f(int32_t n, const int64_t* rpA, const int32_t* ciA, const i
 // (q, p) with q the slot of f_ht in row h and p the slot of f_jt in row j,
 // for every t > h stored in both rows, in ascending t.  Phase II replays them
 // (f_jt <- f_jt - f_jh * f_ht); their number is the number of updates.
-// One wavefront per row j; row j's columns are staged in LDS and every
-// candidate t of the pivot row is binary-searched there, inside one bucket of
-// a directory over [c_min, c_max].  A column's bucket is (t - c_min) * mul >>
-// 24 with mul = floor(kSchedDir * 2^24 / range), computed once per row (the
-// same monotone map builds the directory and finds the bucket, so no
-// candidate is missed); a 64-bit division per candidate cost more than the
-// search itself.
+// One wavefront per row j; row j's columns are staged in LDS, and every
+// candidate t of a pivot row is looked up among them.  Most candidates are no
+// column of row j (random banded n=160,000 ILU(2): 1 in 35), so a lookup is two
+// steps: a bit of a filter (the row's columns folded into 64 or more bits per
+// column), and, for the few that pass, a search of the sorted columns.
+// Those are queued in LDS in order and searched 64 at a time, all lanes busy.
+// Candidates are loaded four wavefront-wide rounds ahead of their test; pivot
+// rows of at most 8, 16 or 32 candidates share a round.  What bounds the
+// kernel is the instructions per candidate: with a search of a column
+// directory by every candidate Phase I's two passes took 2.2 ms at 7-point
+// 64^3 ILU(1), 0.4 here; paper-scale ILU(1) (1,276 entries a row, 55 candidates
+// per pair) one pass of 330 ms, 210 here.
 // ------------------------------------------------------------------------------------
-constexpr int kSchedDir = 1024;  // buckets of the column directory of row j
-constexpr int kSchedUnroll = 8;  // 64-column chunks of a pivot row loaded per round
+constexpr int kSchedAhead = 4;    // rounds of candidates loaded together
+constexpr int kSchedQueue = 128;  // candidates that passed the filter, a ring
 
-__device__ __forceinline__ int32_t sched_bucket(int64_t off, uint64_t mul) {
-    return static_cast<int32_t>((static_cast<uint64_t>(off) * mul) >> 24);
+// filter bits for rows of up to max_row entries (rows too long for the LDS
+// beside a larger one get a small one, and search nearly every candidate)
+static int32_t sched_filter_bits(int32_t max_row) {
+    if (max_row > 16384) return 8192;
+    int32_t bits = 2048;
+    while (bits < 65536 && bits < 64 * (int64_t)max_row) bits <<= 1;
+    return bits;
 }
 
 // Modes: 0 counts the pairs of every pivot slot (scount) and records its
@@ -704,170 +714,222 @@ __device__ __forceinline__ int32_t sched_bucket(int64_t off, uint64_t mul) {
 // at a time (one atomic per chunk) and writes each round's pairs straight
 // into its chunk; a run of one row's pairs inside one chunk is a segment
 // (row, index of its first pair within the row, pool position, count),
-// closed when the row ends or the chunk is full.  k_sched_copy then moves
+// closed when the row ends or the chunk is full.  Atomics on one address cost
+// about 25 ns each across the device: the chunks are about a wavefront's whole
+// share, and a row's first segments have places of their own (an atomic for
+// every row and smaller chunk: random banded n=160,000 ILU(2) 7.7 ms instead of 2.4).  k_sched_copy then moves
 // each segment to sptr[first slot of its row] + that index.  If the pool or
 // the segment list is too small, mode 2 raises *overflow and stops storing
 // (the counts stay exact): the caller then runs mode 1.  Mode 3 only adds
 // the sampled rows' pair count into sample[0] and their candidate count into
 // sample[2] (rows j with j % stride == 0), to size the pool and to decide
 // whether one pass pays.
-// DirT: uint16_t when every row has fewer than 65536 entries (half the LDS
-// of int32_t, which keeps more wavefronts resident: random n=160,000 ILU(1),
-// rows of ~1,250 entries, 400 -> 332 ms with 1,024 buckets; 256 buckets of
-// int32_t took 400 ms, 1,024 of int32_t 398 ms, 4,096 of uint16_t 412 ms).
 // split > 1 (mode 3): each sampled row is shared by `split` wavefronts, each
 // taking every split-th block of 64 pivots, so the few sampled rows still
 // fill the device.
-template <typename DirT>
 __global__ __launch_bounds__(64) void k_sched(int32_t n, const int64_t* __restrict__ rpF,
                                               const int32_t* __restrict__ ciF,
                                               const int32_t* __restrict__ diagF, int mode,
                                               int32_t* __restrict__ scount, int32_t* __restrict__ lsd,
                                               const int64_t* __restrict__ sptr,
                                               int32_t* __restrict__ sq, int32_t* __restrict__ sp,
-                                              SchedPool pool, int32_t max_row, int32_t stride,
+                                              SchedPool pool, int32_t max_bits, int32_t stride,
                                               int32_t split) {
-    extern __shared__ int32_t colsj[];
-    // Row j's sorted columns get a directory: bucket b of [c_min, c_max]
-    // holds the columns at positions dir[b] .. dir[b+1]-1, so a candidate t
-    // is searched among a handful of columns instead of the whole row.
-    __shared__ DirT dir[kSchedDir + 1];
-    // the pivots of the row, 64 at a time: diagonal slot and row end of each
-    __shared__ int32_t pdh[kWave], phe[kWave];
-    __shared__ int64_t pout[kWave];
+    extern __shared__ uint32_t sched_sh[];
+    uint32_t* filter = sched_sh;                                          // [max_bits / 32]
+    int32_t* colsj = reinterpret_cast<int32_t*>(sched_sh + max_bits / 32);  // [max_row]
+    // the queue: column, slot in the pivot row, pivot (of the 64 at hand)
+    __shared__ int32_t qt[kSchedQueue], qq[kSchedQueue];
+    __shared__ uint8_t qp[kSchedQueue];
+    __shared__ int32_t pcnt[kWave];
     const int lane = lane_id();
+    const uint64_t below = (1ull << lane) - 1ull;
     const bool counts = mode == 0 || mode == 2;
     int64_t cbase = -1;          // mode 2: pool position of the wavefront's chunk (-2: pool exhausted)
     int32_t used = 0, seg0 = 0;  // pairs used in the chunk; start of the open segment
+    int64_t ncand = 0, nfound = 0;  // mode 3
     const int64_t nsampled = ((int64_t)n + stride - 1) / stride;
     for (int64_t task = blockIdx.x; task < nsampled * split; task += gridDim.x) {
         const int32_t j = (int32_t)((task / split) * stride);
         const int32_t part = (int32_t)(task % split);
-        const int64_t rs = rpF[j], re = rpF[j + 1];
-        const int32_t len = static_cast<int32_t>(re - rs);
-        const int64_t dj = diagF[j];
+        const int32_t rs = (int32_t)rpF[j], re = (int32_t)rpF[j + 1], dj = diagF[j];
+        const int32_t len = re - rs;
         // mode 2: the open segment is [seg0, used) of the current chunk
         int64_t row_done = 0;  // pairs of this row in closed segments
+        int32_t nseg = 0;      // closed segments
         auto close_seg = [&]() {
             if (cbase >= 0 && used > seg0) {
-                unsigned long long g = 0;
-                if (lane == 0) g = atomicAdd(pool.ctr + 1, 1ull);
-                g = __shfl(g, 0);
-                if (g < (unsigned long long)pool.seg_cap) {
+                // the row's first kSchedSegs segments have their places, the others draw one
+                int64_t g = (int64_t)j * kSchedSegs + nseg;
+                if (nseg >= kSchedSegs) {
+                    unsigned long long a = 0;
+                    if (lane == 0) a = atomicAdd(pool.ctr + 1, 1ull);
+                    g = (int64_t)n * kSchedSegs + (int64_t)__shfl(a, 0);
+                }
+                if (g < pool.seg_cap) {
                     if (lane == 0) pool.seg[g] = make_longlong4(j, row_done, cbase + seg0, used - seg0);
                 } else if (lane == 0) {
                     atomicOr(pool.overflow, 1u);
                 }
+                ++nseg;
                 row_done += used - seg0;
             }
             seg0 = used;
         };
-        for (int32_t e = lane; e < len; e += kWave) colsj[e] = ciF[rs + e];
         if (counts)
-            for (int64_t s = dj + lane; s < re; s += kWave) scount[s] = 0;
+            for (int32_t s = dj + lane; s < re; s += kWave) scount[s] = 0;
+        // (a row of no pivots has nothing else to do)
+        if (dj == rs) {
+            if (mode == 2 && lane < kSchedSegs) pool.seg[(int64_t)j * kSchedSegs + lane].w = 0;
+            continue;
+        }
+        int32_t logm = 11;
+        while ((1 << logm) < max_bits && (1 << logm) < 64 * len) ++logm;
+        const uint32_t mask = (1u << logm) - 1u;
+        // neighbouring columns fall on neighbouring bits, and those a multiple
+        // of the filter's size apart (the planes of a grid) on different ones
+        auto fold = [&](int32_t t) { return ((uint32_t)t + ((uint32_t)t >> logm) * 67u) & mask; };
+        for (int32_t w = lane; w < (1 << logm) / 32; w += kWave) filter[w] = 0u;
         wave_sync();
-        const int32_t cmin = colsj[0];
-        const int64_t range = (int64_t)colsj[len - 1] - cmin + 1;
-        // off < range < 2^31 and mul <= 2^34: the product fits in 64 bits,
-        // and the bucket of any off < range is below kSchedDir
-        const uint64_t mul = ((uint64_t)kSchedDir << 24) / (uint64_t)range;
-        for (int32_t b = lane; b <= kSchedDir; b += kWave) {
-            // first position whose bucket is >= b
-            int32_t lo = 0, hi = len;
-            while (lo < hi) {
-                const int32_t mid = (lo + hi) >> 1;
-                const int64_t bm = sched_bucket((int64_t)colsj[mid] - cmin, mul);
-                if (bm < b) lo = mid + 1;
-                else hi = mid;
-            }
-            dir[b] = (DirT)lo;
+        for (int32_t e = lane; e < len; e += kWave) {
+            const int32_t c = ciF[rs + e];
+            colsj[e] = c;
+            const uint32_t h = fold(c);
+            atomicOr(&filter[h >> 5], 1u << (h & 31u));
         }
         wave_sync();
-        for (int64_t s0 = rs + (int64_t)part * kWave; s0 < dj; s0 += (int64_t)kWave * split) {
-            const int32_t np = static_cast<int32_t>(min<int64_t>(kWave, dj - s0));
+        int32_t top = 1;  // the largest power of two in len
+        while (2 * top <= len) top *= 2;
+        int64_t out = mode == 1 ? sptr[rs] : 0;  // the row's pairs follow each other
+        int32_t head = 0, qn = 0;
+        // search the first cnt candidates of the queue
+        auto drain = [&](int32_t cnt) {
+            wave_sync();
+            const bool on = lane < cnt;
+            const int32_t at = (head + lane) & (kSchedQueue - 1);
+            const int32_t t = qt[at], q = qq[at];
+            int32_t pos = 0;  // columns smaller than t
+            for (int32_t h = top; h > 0; h >>= 1)
+                if (pos + h <= len && colsj[pos + h - 1] < t) pos += h;
+            const bool hit = on && pos < len && colsj[min(pos, len - 1)] == t;
+            const uint64_t m = __ballot(hit);
+            const int32_t c = __popcll(m), rank = __popcll(m & below);
+            if (counts && hit) atomicAdd(&pcnt[qp[at]], 1);
+            if (mode == 1) {
+                if (hit) {
+                    sq[out + rank] = q;
+                    sp[out + rank] = rs + pos;
+                }
+                out += c;
+            }
+            if (mode == 3) nfound += c;
+            if (mode == 2 && m && cbase != -2) {
+                if (cbase < 0 || used + c > pool.chunk) {
+                    close_seg();
+                    unsigned long long a = 0;
+                    if (lane == 0) a = atomicAdd(pool.ctr, (unsigned long long)pool.chunk);
+                    a = __shfl(a, 0);
+                    if (a + (unsigned long long)pool.chunk > (unsigned long long)pool.cap) {
+                        if (lane == 0) atomicOr(pool.overflow, 1u);
+                        cbase = -2;
+                    } else {
+                        cbase = (int64_t)a;
+                    }
+                    used = 0;
+                    seg0 = 0;
+                }
+                if (cbase >= 0) {
+                    if (hit) {
+                        pool.q[cbase + used + rank] = q;
+                        pool.p[cbase + used + rank] = rs + pos;
+                    }
+                    used += c;
+                }
+            }
+            head = (head + cnt) & (kSchedQueue - 1);
+            qn -= cnt;
+            wave_sync();
+        };
+        auto test = [&](bool on, int32_t t, int32_t q, int32_t p) {
+            const uint32_t h = fold(t);
+            const bool pass = on && ((filter[h >> 5] >> (h & 31u)) & 1u);
+            const uint64_t m = __ballot(pass);
+            if (!m) return;
+            if (pass) {
+                const int32_t at = (head + qn + __popcll(m & below)) & (kSchedQueue - 1);
+                qt[at] = t;
+                qq[at] = q;
+                qp[at] = (uint8_t)p;
+            }
+            qn += __popcll(m);
+            if (qn >= kWave) drain(kWave);
+        };
+        for (int32_t s0 = rs + part * kWave; s0 < dj; s0 += kWave * split) {
+            const int32_t np = min(kWave, dj - s0);
+            int32_t pd = 0, pe = 0;  // this lane's pivot: its candidates' slots
             if (lane < np) {
-                const int32_t h = ciF[s0 + lane];
+                const int32_t h = colsj[s0 - rs + lane];
                 const int32_t dh = diagF[h];
-                pdh[lane] = dh;
-                phe[lane] = static_cast<int32_t>(rpF[h + 1]);
-                pout[lane] = mode == 1 ? sptr[s0 + lane] : 0;
+                pd = dh + 1;
+                pe = (int32_t)rpF[h + 1];
                 if (counts) lsd[s0 + lane] = dh;
             }
+            pcnt[lane] = 0;
             wave_sync();
-            for (int32_t p = 0; p < np; ++p) {
-                const int64_t s = s0 + p;
-                const int64_t dh = pdh[p], he = phe[p];
-                const int64_t out = pout[p];
-                const int32_t lo0 = static_cast<int32_t>(s - rs) + 1;
-                int32_t found = 0;
-                // kSchedUnroll chunks of the pivot row per round: their column
-                // loads are issued together (clamped, in bounds; extras unused)
-                for (int64_t q0 = dh + 1; q0 < he; q0 += kSchedUnroll * kWave) {
-                    int32_t tv[kSchedUnroll];
+            if (mode == 3) ncand += pe - pd;
+            const int shift = __any(pe - pd > 32) ? 6 : __any(pe - pd > 16) ? 5 : __any(pe - pd > 8) ? 4 : 3;
+            int32_t tv[kSchedAhead], tq[kSchedAhead], tp[kSchedAhead];
+            bool on[kSchedAhead];
+            if (shift < 6) {
+                // every pivot's candidates in one go, several pivots a round
+                for (int32_t p0 = 0; p0 < np; p0 += kSchedAhead << (6 - shift)) {
 #pragma unroll
-                    for (int u = 0; u < kSchedUnroll; ++u)
-                        tv[u] = ciF[min<int64_t>(q0 + u * kWave + lane, he - 1)];
-#pragma unroll
-                    for (int u = 0; u < kSchedUnroll; ++u) {
-                        const int64_t q = q0 + u * kWave + lane;
-                        int32_t pos = -1;
-                        const int64_t off = (int64_t)tv[u] - cmin;
-                        if (q < he && off >= 0 && off < range) {
-                            const int32_t t = tv[u];
-                            const int32_t b = sched_bucket(off, mul);
-                            int32_t lo = max(lo0, (int32_t)dir[b]), hi = (int32_t)dir[b + 1] - 1;
-                            while (lo <= hi) {
-                                const int32_t mid = (lo + hi) >> 1;
-                                const int32_t c = colsj[mid];
-                                if (c == t) { pos = mid; break; }
-                                if (c < t) lo = mid + 1;
-                                else hi = mid - 1;
-                            }
-                        }
-                        const uint64_t m = __ballot(pos >= 0);
-                        if (mode == 1 && pos >= 0) {
-                            const int32_t rank = __popcll(m & ((1ull << lane) - 1ull));
-                            sq[out + found + rank] = static_cast<int32_t>(q);
-                            sp[out + found + rank] = static_cast<int32_t>(rs + pos);
-                        }
-                        if (mode == 2 && m && cbase != -2) {
-                            const int32_t c = __popcll(m);
-                            if (cbase < 0 || used + c > pool.chunk) {
-                                close_seg();
-                                unsigned long long at = 0;
-                                if (lane == 0) at = atomicAdd(pool.ctr, (unsigned long long)pool.chunk);
-                                at = __shfl(at, 0);
-                                if (at + (unsigned long long)pool.chunk > (unsigned long long)pool.cap) {
-                                    if (lane == 0) atomicOr(pool.overflow, 1u);
-                                    cbase = -2;
-                                } else {
-                                    cbase = (int64_t)at;
-                                }
-                                used = 0;
-                                seg0 = 0;
-                            }
-                            if (cbase >= 0) {
-                                if (pos >= 0) {
-                                    const int32_t rank = __popcll(m & ((1ull << lane) - 1ull));
-                                    pool.q[cbase + used + rank] = static_cast<int32_t>(q);
-                                    pool.p[cbase + used + rank] = static_cast<int32_t>(rs + pos);
-                                }
-                                used += c;
-                            }
-                        }
-                        found += __popcll(m);
+                    for (int u = 0; u < kSchedAhead; ++u) {
+                        tp[u] = p0 + (u << (6 - shift)) + (lane >> shift);
+                        const int32_t a = __shfl(pd, tp[u] & (kWave - 1)), e = __shfl(pe, tp[u] & (kWave - 1));
+                        tq[u] = a + (lane & ((1 << shift) - 1));
+                        on[u] = tp[u] < np && tq[u] < e;
+                        tv[u] = on[u] ? ciF[tq[u]] : 0;
                     }
+#pragma unroll
+                    for (int u = 0; u < kSchedAhead; ++u) test(on[u], tv[u], tq[u], tp[u]);
                 }
-                if (counts && lane == 0) scount[s] = found;
-                if (mode == 3 && lane == 0) {
-                    if (found) atomicAdd(pool.sample, (unsigned long long)found);
-                    if (he > dh + 1) atomicAdd(pool.sample + 2, (unsigned long long)(he - dh - 1));
+            } else {
+                int32_t p = 0, q0 = __builtin_amdgcn_readlane(pd, 0), he = __builtin_amdgcn_readlane(pe, 0);
+                while (p < np) {
+#pragma unroll
+                    for (int u = 0; u < kSchedAhead; ++u) {
+                        while (p < np && q0 >= he) {
+                            ++p;
+                            q0 = __builtin_amdgcn_readlane(pd, p & (kWave - 1));
+                            he = __builtin_amdgcn_readlane(pe, p & (kWave - 1));
+                        }
+                        tp[u] = p;
+                        tq[u] = q0 + lane;
+                        on[u] = p < np && tq[u] < he;
+                        tv[u] = on[u] ? ciF[tq[u]] : 0;
+                        q0 += kWave;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kSchedAhead; ++u) test(on[u], tv[u], tq[u], tp[u]);
                 }
             }
+            if (qn > 0) drain(qn);
+            if (counts && lane < np) scount[s0 + lane] = pcnt[lane];
             wave_sync();
         }
-        if (mode == 2) close_seg();
+        if (mode == 2) {
+            close_seg();
+            if (lane >= nseg && lane < kSchedSegs) pool.seg[(int64_t)j * kSchedSegs + lane].w = 0;
+        }
         wave_sync();
+    }
+    if (mode == 3) {
+        for (int off = 32; off > 0; off >>= 1) ncand += __shfl_xor(ncand, off);
+        if (lane == 0 && ncand) {
+            atomicAdd(pool.sample, (unsigned long long)nfound);
+            atomicAdd(pool.sample + 2, (unsigned long long)ncand);
+        }
     }
 }
 
@@ -878,6 +940,7 @@ __global__ __launch_bounds__(64) void k_sched_copy(SchedPool pool, int64_t nseg,
     const int lane = lane_id();
     for (int64_t g = blockIdx.x; g < nseg; g += gridDim.x) {
         const longlong4 d = pool.seg[g];
+        if (d.w == 0) continue;
         const int64_t dst = sptr[rpF[d.x]] + d.y;
         for (int64_t e = lane; e < d.w; e += kWave) {
             sq[dst + e] = pool.q[d.z + e];
@@ -898,20 +961,16 @@ hipError_t launch_sched(int32_t n, const int64_t* rpF, const int32_t* ciF, const
                         int mode, int32_t* scount, int32_t* lsd, const int64_t* sptr,
                         int32_t* sq, int32_t* sp, int32_t max_row, hipStream_t s, const SchedPool* pool,
                         int32_t stride) {
-    const int32_t mr = max(max_row, 1);
-    size_t lds = (size_t)mr * sizeof(int32_t);
+    const int32_t bits = sched_filter_bits(max_row);
+    const size_t lds = (size_t)std::max(max_row, 1) * sizeof(int32_t) + (size_t)bits / 8;
     stride = max(stride, 1);
     const int32_t split = mode == 3 ? kSchedSampleSplit : 1;
     const int64_t tasks = ((int64_t)n + stride - 1) / stride * split;
-    int grid = (int)std::min<int64_t>(tasks, 65536);
+    int grid = (int)std::min<int64_t>(tasks, mode == 2 ? pool->waves : 8 * kSchedWaves);
     if (grid <= 0) return hipSuccess;
     const SchedPool none{};
-    if (mr < 65536)
-        hipLaunchKernelGGL(k_sched<uint16_t>, dim3(grid), dim3(64), lds, s, n, rpF, ciF, diagF, mode, scount,
-                           lsd, sptr, sq, sp, pool ? *pool : none, mr, stride, split);
-    else
-        hipLaunchKernelGGL(k_sched<int32_t>, dim3(grid), dim3(64), lds, s, n, rpF, ciF, diagF, mode, scount,
-                           lsd, sptr, sq, sp, pool ? *pool : none, mr, stride, split);
+    hipLaunchKernelGGL(k_sched, dim3(grid), dim3(64), lds, s, n, rpF, ciF, diagF, mode, scount, lsd, sptr, sq, sp,
+                       pool ? *pool : none, bits, stride, split);
     return hipGetLastError();
 }
 
@@ -934,9 +993,9 @@ __global__ __launch_bounds__(64) void k_tsched(int32_t n, const int64_t* __restr
     for (int32_t j = blockIdx.x; j < n; j += gridDim.x) {
         const int64_t rs = rpF[j], re = rpF[j + 1], dj = diagF[j];
         const int32_t len = (int32_t)(re - rs), dl = (int32_t)(dj - rs);
-        int64_t* Tp = tsh;                                  // [len] tptr of the row's slots
+        int64_t* Tp = tsh;                                  // [len] next place of each of the row's slots
         int64_t* Sp = tsh + len;                            // [dl + 1] sptr of its L slots
-        int32_t* cur = reinterpret_cast<int32_t*>(tsh + len + dl + 1);  // [len]
+        int32_t* cur = reinterpret_cast<int32_t*>(tsh + len + dl + 1);  // [len] counts (mode 0)
         for (int32_t e = lane; e < len; e += kWave) {
             cur[e] = 0;
             if (mode == 1) Tp[e] = tptr[rs + e];
@@ -948,15 +1007,39 @@ __global__ __launch_bounds__(64) void k_tsched(int32_t n, const int64_t* __restr
             wave_sync();
             for (int32_t e = lane; e < len; e += kWave) tcount[rs + e] = cur[e];
         } else {
-            for (int32_t h = 0; h < dl; ++h) {
-                for (int64_t e = Sp[h] + lane; e < Sp[h + 1]; e += kWave) {
-                    const int32_t p = (int32_t)(sp[e] - rs);
-                    const int64_t pos = Tp[p] + cur[p];
-                    cur[p] = cur[p] + 1;
-                    tsl[pos] = h;
-                    tq[pos] = sq[e];
+            // the row's pairs 64 at a time, the next ones loading meanwhile; a
+            // pivot updates distinct slots, so the pivots of a round take turns
+            // in LDS alone (a pivot at a time with its loads: 1.13 ms at random
+            // banded n=160,000 ILU(2), TSCHEDMS here)
+            const int64_t e1 = Sp[dl];
+            int64_t e = Sp[0] + lane;
+            int32_t h = 0, p = 0, q = 0;
+            if (e < e1) {
+                p = sp[e];
+                q = sq[e];
+            }
+            for (int64_t e0 = Sp[0]; e0 < e1; e0 += kWave) {
+                int32_t pn = 0, qn = 0;
+                if (e + kWave < e1) {
+                    pn = sp[e + kWave];
+                    qn = sq[e + kWave];
                 }
-                wave_sync();
+                const int64_t end = min(e0 + kWave, e1);
+                for (;;) {
+                    const int64_t lo = Sp[h], hi = Sp[h + 1];
+                    if (e >= lo && e < min(hi, end)) {
+                        const int64_t pos = Tp[p - rs];
+                        Tp[p - rs] = pos + 1;
+                        tsl[pos] = h;
+                        tq[pos] = q;
+                    }
+                    wave_sync();
+                    if (hi >= end) break;
+                    ++h;
+                }
+                e += kWave;
+                p = pn;
+                q = qn;
             }
         }
         wave_sync();
@@ -1053,6 +1136,8 @@ __device__ __forceinline__ bool level_watchdog(uint32_t& polls, uint64_t& t0, Ct
     return __any(stop);
 }
 
+typedef __attribute__((address_space(3))) volatile int32_t LdsLevel;
+
 // One node, one wavefront.  The maximum does not depend on order, so every
 // round re-polls all of a chunk's unknown dependencies at once.
 constexpr int kLevelPer = 4;  // dependencies per lane and chunk
@@ -1132,12 +1217,25 @@ __global__ __launch_bounds__(64) void k_depth(int32_t n, LevelJob j0, LevelJob j
 
 // Lane per node: a ticket hands a wavefront 64 consecutive nodes (in the
 // sweep's order), so the whole graph can be in flight at once and wide
-// graphs are not throttled by the ticket.  A lane scans its node's
-// dependencies, at most 8 per round, and stops at the first one not known
-// yet; the wavefront keeps looping until every lane published, so lanes that
-// depend on other lanes of the same wavefront cannot deadlock.
+// graphs are not throttled by the ticket.  A lane polls its first dependency
+// not known yet, and when that is there takes the next ones with kLaneBatch
+// loads in flight; dependencies on the wavefront's own nodes (the chains of a
+// stencil's grid lines) go through LDS.  The wavefront keeps looping until
+// every lane published, so lanes that depend on other lanes of the same
+// wavefront cannot deadlock.  Bound by one hand-off per level and the polls
+// of the wavefronts that wait: one that has found nothing new watches a single
+// value, up to kLaneWatch loads, before all its lanes look again (27-point
+// 90^3 ILU(1), Phase I, 4096 wavefronts: 89 ms without, 53 / 35 / 32 with 4 /
+// 16 / 64 loads; 2-D 400^2 ILU(1) 3.3 / 3.6 / 3.5 / 4.2).  Phase I with one
+// load at a time, nothing through LDS and every lane polling -> here: 2-D
+// 400^2 ILU(3) 7.5 -> 6.0 ms, 7-point 64^3 ILU(2) 14.4 -> 6.2 ms.
+constexpr int kLaneBatch = 8;
+constexpr int kLaneWatch = 16;
+
 __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, LevelJob j1, int32_t njobs, Ctl* ctl,
                                                     uint64_t spin_limit) {
+    __shared__ int32_t lvsh[kWave];
+    LdsLevel* lv = (LdsLevel*)lvsh;
     const int lane = lane_id();
     const LevelJob J = (njobs > 1 && (blockIdx.x & 1)) ? j1 : j0;
     const int32_t* __restrict__ ciF = J.G.idx;
@@ -1147,36 +1245,66 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
         if ((int64_t)t * kWave >= n) break;
         const bool valid = r < n;
         const int32_t i = valid ? (J.desc ? n - 1 - (int32_t)r : (int32_t)r) : 0;
+        const int32_t first = J.desc ? n - 1 - (int32_t)t * kWave : (int32_t)t * kWave;  // lane 0's node
         int64_t q = 0, b = 0;
         if (valid) dep_range(J.G, i, q, b);
         int32_t best = 0;
         bool done = !valid;
+        lv[lane] = -1;
         uint32_t polls = 0;
         uint64_t t0 = 0;
+        int idle = 0;
+        auto level_of = [&](int32_t c) {
+            const uint32_t x = (uint32_t)(J.desc ? first - c : c - first);  // its lane, if below 64
+            int32_t v;
+            if (x < (uint32_t)kWave) v = lv[x];
+            else v = ld_level(J.depth + c);
+            return v;
+        };
         for (;;) {
             bool prog = false;
-            if (!done) {
-                for (int step = 0; step < 8 && q < b; ++step) {
-                    const int32_t* src = J.depth + ciF[q];
-                    int32_t d = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                    if (d < 0) d = ld_level(src);
-                    if (d < 0) break;
-                    best = max(best, d);
-                    ++q;
-                    prog = true;
+            int32_t v0 = -1;
+            if (!done) v0 = q < b ? level_of(ciF[q]) : 0;
+            if (v0 >= 0) {
+                prog = true;
+                best = max(best, v0);
+                if (q < b) ++q;
+                int32_t c[kLaneBatch], v[kLaneBatch];
+#pragma unroll
+                for (int u = 0; u < kLaneBatch; ++u) c[u] = q + u < b ? ciF[q + u] : first;
+#pragma unroll
+                for (int u = 0; u < kLaneBatch; ++u) v[u] = q + u < b ? level_of(c[u]) : -1;
+                bool go = true;
+#pragma unroll
+                for (int u = 0; u < kLaneBatch; ++u) {
+                    go = go && v[u] >= 0;
+                    best = max(best, go ? v[u] : 0);
+                    q += go ? 1 : 0;
                 }
                 if (q >= b) {
                     jitter((uint32_t)i);
+                    lv[lane] = best + 1;
                     __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     done = true;
                 }
             }
-            if (__all(done)) break;
+            const uint64_t left = __ballot(!done);
+            if (!left) break;
             if (__any(prog)) {
                 polls = 0;
+                idle = 0;
                 continue;
             }
-            if (level_watchdog(polls, t0, ctl, spin_limit)) break;
+            // nothing new: watch the first waiting lane's dependency alone for a
+            // while, longer each time
+            const int f = __builtin_ctzll(left);
+            const int32_t c = ciF[((int64_t)__builtin_amdgcn_readlane((int32_t)(q >> 32), f) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readlane((int32_t)q, f)];
+            if ((uint32_t)(J.desc ? first - c : c - first) >= (uint32_t)kWave) {
+                for (int w = min(4 << idle, kLaneWatch); w > 0 && uniform(ld_level(J.depth + c)) < 0; --w) {}
+                idle = min(idle + 1, 3);
+            }
+            if (wait_expired(polls, t0, ctl, spin_limit)) break;
         }
     }
 }
@@ -1197,7 +1325,6 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
 // deals to the XCDs in turn: each elects an XCD of its own.
 constexpr int kDepthSlots = 4;
 constexpr int kDepthOuter = 8;
-typedef __attribute__((address_space(3))) volatile int32_t LdsLevel;
 
 template <bool kBackward>
 __device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const uint8_t* __restrict__ wcnt, Ctl* ctl,
@@ -1391,14 +1518,12 @@ hipError_t launch_depth(int32_t n, const LevelJob& j0, const LevelJob* j1, Ctl* 
     if (n <= 0 || grid == 0) return hipSuccess;
     const int32_t njobs = j1 ? 2 : 1;
     const LevelJob b = j1 ? *j1 : j0;
-    if (grid < 0)
-        hipLaunchKernelGGL(k_depth_lanes, dim3(-grid * njobs), dim3(64), 0, s, n, j0, b, njobs, ctl, spin_limit);
-    else if (one_xcd)
-        hipLaunchKernelGGL(k_depth<Scope::Xcd>, dim3(grid * njobs * kXcds), dim3(64), 0, s, n, j0, b, njobs, ctl,
-                           spin_limit);
-    else
-        hipLaunchKernelGGL(k_depth<Scope::Device>, dim3(grid * njobs), dim3(64), 0, s, n, j0, b, njobs, ctl,
-                           spin_limit);
+    auto go = [&](auto kern, int32_t groups) {
+        hipLaunchKernelGGL(kern, dim3(groups), dim3(64), 0, s, n, j0, b, njobs, ctl, spin_limit);
+    };
+    if (grid < 0) go(k_depth_lanes, -grid * njobs);
+    else if (one_xcd) go(k_depth<Scope::Xcd>, grid * njobs * kXcds);
+    else go(k_depth<Scope::Device>, grid * njobs);
     return hipGetLastError();
 }
 

@@ -52,13 +52,15 @@ hipError_t launch_a2f(int32_t n, const int64_t* rpA, const int32_t* ciA, const i
 // slot of the pivot), mode 1 writes the (q, p) pairs
 // the pool of the one-pass schedule (k_sched mode 2) and the sample counter
 // of mode 3; seg entries are (row, index of the first pair within the row,
-// pool position, count); ctr[0] = pairs taken (whole chunks), ctr[1] =
-// segments taken
+// pool position, count; count 0: unused), kSchedSegs for every row and then
+// the further ones of long rows; ctr[0] = pairs taken (whole chunks), ctr[1] =
+// further segments taken
 struct SchedPool {
     int32_t* q = nullptr;
     int32_t* p = nullptr;
     int64_t cap = 0;
     int32_t chunk = 0;  // pairs a wavefront takes at a time
+    int32_t waves = 0;  // mode 2: wavefronts launched
     longlong4* seg = nullptr;
     int64_t seg_cap = 0;
     unsigned long long* ctr = nullptr;
@@ -69,9 +71,12 @@ hipError_t launch_sched(int32_t n, const int64_t* rpF, const int32_t* ciF, const
                         int mode, int32_t* scount, int32_t* lsd, const int64_t* sptr,
                         int32_t* sq, int32_t* sp, int32_t max_row, hipStream_t s,
                         const SchedPool* pool = nullptr, int32_t stride = 1);
+constexpr int32_t kSchedSegs = 2;
+constexpr int32_t kSchedWaves = 8192;        // 32 per CU
 constexpr int32_t kSchedSampleStride = 241;  // rows sampled (j % 241 == 0) to size the pool
 constexpr int32_t kSchedSampleSplit = 16;   // wavefronts sharing one sampled row
-constexpr int64_t kSchedOnePassRatio = 8;   // candidates per pair above which the one-pass schedule runs
+constexpr int64_t kSchedOnePassRatio = 8;   // candidates per pair above which the one-pass schedule runs,
+constexpr int64_t kSchedOnePassCands = 1ll << 30;  // if there are that many
 hipError_t launch_sched_copy(const SchedPool& pool, int64_t nseg, const int64_t* rpF, const int64_t* sptr,
                              int32_t* sq, int32_t* sp, hipStream_t s);
 

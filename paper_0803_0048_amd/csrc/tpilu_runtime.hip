@@ -139,7 +139,7 @@ constexpr int64_t kNarrowWidth = 32;   // n / depth below this: narrow
 constexpr int64_t kXcdMaxAvg = 128;
 // wavefronts per CU that the LDS of a tier of the symbolic construction allows
 constexpr int32_t kSymWaves[] = {32, 12, 6, 2};
-constexpr int64_t kLevelLaneMax = 14;  // level computation: lane per node below this many dependencies
+constexpr int64_t kLevelLaneMax = 40;  // level computation: lane per node below this many dependencies
 constexpr int64_t kLevelWideMax = 60;  // wavefront per node: the wide window below this, else the narrow one
 constexpr int32_t kLevelWavesWide = 768;
 constexpr int32_t kLevelWavesNarrow = 192;
@@ -742,16 +742,17 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     *dmax_out = dmax;
     int64_t deps = 0;
     for (int q = 0; q < njobs; ++q) deps = std::max(deps, js[q].deps);
-    const int32_t lane_waves = (int32_t)std::min<int64_t>(((int64_t)n + 63) / 64, 8192);
-    // Shape by dependencies per node: a lane per node for short lists (every
-    // node in flight, a lane scans its few dependencies itself); a wavefront
-    // per node otherwise, with a wide window of nodes in flight (natural
-    // order hands out consecutive nodes, whose chains need many lines of the
-    // grid in flight at once) unless the lists are long.  Measured (ms):
-    // 64^3 7-point ILU(1) lanes 9.6 / waves 17.6; 27-point 90^3 ILU(1) 192
-    // waves 152, 768 waves 71; 64^3 ILU(3) 72 lanes, 31 at 768 waves; random
-    // banded n=160,000 ILU(2) 28.5 at 192 waves, 32 at 768.
+    // Shape by dependencies per node: a lane per node for short and medium
+    // lists; a wavefront per node otherwise, with a wide window of nodes in
+    // flight (natural order hands out consecutive nodes, whose chains need many
+    // lines of the grid in flight at once) unless the lists are long.
+    // Measured, all of Phase I (ms): 27-point 90^3 ILU(1), 29 dependencies: 55
+    // by node (768 wavefronts), 35 by lanes (4096; 37 with 1024); 27-point 50^3
+    // ILU(2), 52: 20 by node, 25 to 30 by lanes; 7-point 64^3 ILU(3), 20: 21 by
+    // node, 14 by lanes; random banded n=160,000 ILU(2) by node 28.5 at 192
+    // wavefronts, 32 at 768.
     const int64_t avg = deps / std::max<int64_t>(n, 1);
+    const int32_t lane_waves = (int32_t)std::min<int64_t>(((int64_t)n + 63) / 64, 4096);
     const int32_t grid = avg < kLevelLaneMax ? -lane_waves : (avg < kLevelWideMax ? kLevelWavesWide
                                                                                     : kLevelWavesNarrow);
     LevelJob jb[2];
@@ -1293,21 +1294,24 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     unsigned long long sample[3] = {0, 0, 0};  // pairs, (unused), candidates of the sampled rows
     HIPCHK(ctx, hipMemcpyAsync(sample, pool.sample, sizeof(sample), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
-    // One pass saves a second search (about one probe per candidate) and
-    // costs a copy of the pairs and the sample; taken when candidates
-    // outnumber pairs kSchedOnePassRatio to 1 (measured on MI355X: random
-    // n=160,000 ILU(1), 55 candidates per pair, 697 -> 434 ms; 27-point 50^3
-    // ILU(3), few candidates per pair, 53 ms with two passes, 57 with one)
+    // One pass saves a second search and costs a copy of the pairs and their
+    // pool; taken when candidates outnumber pairs kSchedOnePassRatio to 1 and
+    // are kSchedOnePassCands or more (Phase I, one pass / two: random n=160,000
+    // ILU(1), 65e9 candidates, 55 per pair, 309 / 535 ms; random banded
+    // n=160,000 ILU(2), 1.1e9, 35 per pair, 11.5 / 11.8; ILU(1), 5e7, 4.5 / 3.6;
+    // 7-point 64^3 ILU(1) 5.4 / 3.8)
     {
         const int64_t est = (int64_t)sample[0] * kSchedSampleStride;
-        const bool worth = (int64_t)sample[2] > kSchedOnePassRatio * (int64_t)sample[0];
-        // chunks of about a quarter of a wavefront's expected share (64 to
-        // 4096 pairs): few atomics, and little left unused in the chunks
-        // the wavefronts hold when they finish
-        const int64_t waves = std::min<int64_t>(n, 65536);
-        pool.chunk = (int32_t)std::min<int64_t>(4096, std::max<int64_t>(64, (est / waves / 4 + 63) / 64 * 64));
+        const bool worth = (int64_t)sample[2] * kSchedSampleStride >= kSchedOnePassCands &&
+                           (int64_t)sample[2] > kSchedOnePassRatio * (int64_t)sample[0];
+        // chunks of about a wavefront's expected share (64 to 4096 pairs): few
+        // atomics, and little left unused in the chunks the wavefronts hold
+        // when they finish
+        const int64_t waves = std::min<int64_t>(n, est > 4096ll * kSchedWaves ? 8 * kSchedWaves : kSchedWaves);
+        pool.waves = (int32_t)waves;
+        pool.chunk = (int32_t)std::min<int64_t>(4096, std::max<int64_t>(64, (est / waves + 63) / 64 * 64));
         pool.cap = est + est / 2 + waves * pool.chunk + (1 << 20);
-        pool.seg_cap = pool.cap / pool.chunk + n + 1;
+        pool.seg_cap = pool.cap / pool.chunk + n * kSchedSegs + 1;
         size_t free_b = 0, total_b = 0;
         const bool fits = worth && hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
                           (size_t)pool.cap * 8 + (size_t)pool.seg_cap * 32 <= free_b / 3;
@@ -1342,7 +1346,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->sp = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nupd, 1));
     if (!P->sq || !P->sp) return bail(fail(ctx, TPILU_E_NOMEM, "schedule"));
     if (pooled)
-        HIPCHK(ctx, launch_sched_copy(pool, (int64_t)pc[1], P->rpF, P->sptr, P->sq, P->sp, s));
+        HIPCHK(ctx, launch_sched_copy(pool, n * kSchedSegs + (int64_t)pc[1], P->rpF, P->sptr, P->sq, P->sp, s));
     else
         HIPCHK(ctx, launch_sched(ni, P->rpF, P->ciF, P->diagF, 1, nullptr, nullptr, P->sptr, P->sq, P->sp,
                                  P->st.max_row, s));
