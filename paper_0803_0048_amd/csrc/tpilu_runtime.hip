@@ -187,7 +187,7 @@ struct Arena {
         size_t used, bytes;
     };
     std::vector<Chunk> chunks;
-    size_t total = 0;
+    static constexpr size_t kArenaMin = 1 << 20;
     explicit Arena(const Alloc& a = Alloc{}) : al(a) {}
     Arena(const Arena&) = delete;
     Arena& operator=(const Arena&) = delete;
@@ -196,12 +196,12 @@ struct Arena {
         void* p = al.get(bytes);
         if (!p) return false;
         chunks.push_back({static_cast<char*>(p), 0, bytes});
-        total += bytes;
         return true;
     }
-    // room for arrays of `bytes` in all (each rounded up to 256): one allocation
+    // room for arrays of `bytes` in all (each rounded up to 256) in one
+    // allocation; small ones (under 1 us each in the runtime's own heap) stay apart
     void reserve(size_t bytes) {
-        if (chunks.empty() || chunks.back().bytes - chunks.back().used < bytes) (void)chunk(bytes);
+        if (bytes >= kArenaMin) (void)chunk(bytes);
     }
     void* get(size_t bytes) {
         bytes = up(bytes);
@@ -210,9 +210,7 @@ struct Arena {
                 c->used += bytes;
                 return c->p + (c->used - bytes);
             }
-        // as much again as there is, within 64 KB and 32 MB; less if that cannot be had
-        const size_t more = std::min<size_t>(std::max<size_t>(total, 64 << 10), 32 << 20);
-        if (!(bytes < more && chunk(more)) && !chunk(bytes)) return nullptr;
+        if (!chunk(bytes)) return nullptr;
         chunks.back().used = bytes;
         return chunks.back().p;
     }
