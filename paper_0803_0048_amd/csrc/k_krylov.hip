@@ -104,40 +104,239 @@ __device__ __forceinline__ double block_scalar(const double* partial, int sqrt_i
     return sc;
 }
 
-// MGS step: h = <w, v> (from its partials); H slot <- h; w <- w - h v
-__global__ __launch_bounds__(256) void k_gm_axpy_h(int64_t n, const double* __restrict__ partial,
-                                                   double* hslot, double* __restrict__ w,
-                                                   const double* __restrict__ v) {
-    const double h = block_scalar(partial, 0);
+// The rotation that zeroes b against a: rho = sqrt(a*a + b*b) (each product
+// and the sum rounded on its own, no hypot), c = a / rho, s = b / rho, all
+// correctly rounded binary64 operations.
+struct Rotation {
+    double rho, c, s;
+};
+__device__ __forceinline__ Rotation givens_rotation(double a, double b) {
+    Rotation r;
+    r.rho = __builtin_sqrt(a * a + b * b);
+    r.c = a / r.rho;
+    r.s = b / r.rho;
+    return r;
+}
+
+// Givens, by one workgroup: apply rotations 0..j-1 to column j of H, form
+// rotation j, update g, count the iteration and decide whether the cycle stops
+// (|g_{j+1}| <= tol, maxit reached, or breakdown).  H is (m+1) x m, row-major:
+// H[i * m + j].  hn = h_{j+1,j}.  The chain runs in one thread, its operands
+// through LDS (from memory it took 3 to 5 us).
+__device__ __forceinline__ void gm_givens(const GmStep& a, double hn) {
+    constexpr int kPart = 256;
+    __shared__ double hc[kPart], rc[kPart], rsn[kPart];
+    const int t = threadIdx.x;
+    const int32_t m = a.m, j = a.j;
+    __syncthreads();  // column j of H is there
+    double run = a.H[j];
+    for (int32_t i0 = 0; i0 < j; i0 += kPart) {
+        const int32_t cnt = min(kPart, j - i0);
+        if (t < cnt) {
+            hc[t] = a.H[(int64_t)(i0 + t + 1) * m + j];
+            rc[t] = a.cs[i0 + t];
+            rsn[t] = a.sn[i0 + t];
+        }
+        __syncthreads();
+        if (t == 0)
+            for (int32_t i = 0; i < cnt; ++i) {
+                const double x = hc[i], c = rc[i], s = rsn[i];
+                hc[i] = c * run + s * x;
+                run = c * x - s * run;
+            }
+        __syncthreads();
+        if (t < cnt) a.H[(int64_t)(i0 + t) * m + j] = hc[t];
+        __syncthreads();
+    }
+    if (t != 0) return;
+    const Rotation rot = givens_rotation(run, hn);
+    a.cs[j] = rot.c;
+    a.sn[j] = rot.s;
+    a.H[(int64_t)j * m + j] = rot.rho;
+    a.H[(int64_t)(j + 1) * m + j] = 0.0;
+    const double gj = a.g[j], gn = -rot.s * gj;
+    a.g[j + 1] = gn;
+    a.g[j] = rot.c * gj;
+    const int32_t it = *a.iters;
+    const double res = __builtin_fabs(gn);
+    if (a.hist) a.hist[it] = res;
+    *a.iters = it + 1;
+    // the host's copy: read after the stream's end
+    a.flags[0] = it + 1;
+    a.flags[1] = (res <= a.tol || it + 1 >= a.maxit || hn == 0.0) ? 1 : 0;
+    a.flags[2] = (int32_t)ld_u32_coherent(&a.ctl->status);
+}
+
+// h = <w, v> (from its partials); H slot <- h; w <- w - h v; then the partials
+// of <w, vn> (vn null: of <w, w>), for the next step: a launch per MGS step.
+// Every lane of the fixed shape owns its elements, so what it subtracts is
+// what it sums next.  The loads of kGmAhead elements are in flight together
+// (64 x 256 threads are few).  n=160,000: a dot and an axpy launch 5.7 + 4.9
+// us, 5.2 here.
+constexpr int kGmAhead = 8;
+__global__ __launch_bounds__(256) void k_gm_axpy_dot(int64_t n, const double* __restrict__ pin, double* hslot,
+                                                     double* __restrict__ w, const double* __restrict__ v,
+                                                     const double* vn, double* __restrict__ pout) {
+    __shared__ double sh[4];
+    const double h = block_scalar(pin, 0);
     if (blockIdx.x == 0 && threadIdx.x == 0) *hslot = h;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-         e += (int64_t)gridDim.x * blockDim.x)
-        w[e] = w[e] - h * v[e];
+    double s = 0.0;
+    for (int64_t e0 = (int64_t)blockIdx.x * kDotThreads + threadIdx.x; e0 < n; e0 += (int64_t)kGmAhead * kDotLanes) {
+        double x[kGmAhead], y[kGmAhead], z[kGmAhead];
+#pragma unroll
+        for (int u = 0; u < kGmAhead; ++u) {
+            const int64_t e = e0 + (int64_t)u * kDotLanes;
+            x[u] = y[u] = z[u] = 0.0;
+            if (e < n) {
+                x[u] = w[e];
+                y[u] = v[e];
+                if (vn) z[u] = vn[e];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kGmAhead; ++u) {
+            const int64_t e = e0 + (int64_t)u * kDotLanes;
+            if (e < n) {
+                const double r = x[u] - h * y[u];
+                w[e] = r;
+                s = s + r * (vn ? z[u] : r);
+            }
+        }
+    }
+    s = wave_tree(s);
+    if (lane_id() == 0) sh[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double a = sh[0] + sh[1];
+        const double c = sh[2] + sh[3];
+        pout[blockIdx.x] = a + c;
+    }
 }
 
-hipError_t launch_gm_axpy_h(int64_t n, const double* partial, double* hslot, double* w,
-                            const double* v, hipStream_t s) {
-    int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
-    hipLaunchKernelGGL(k_gm_axpy_h, dim3(blocks), dim3(256), 0, s, n, partial, hslot, w, v);
-    return hipGetLastError();
-}
-
-// h_{j+1,j} = ||w||; v_{j+1} = w / h_{j+1,j} when it is not zero
-__global__ __launch_bounds__(256) void k_gm_norm_scale(int64_t n, const double* __restrict__ partial,
-                                                       double* hslot, const double* __restrict__ w,
-                                                       double* __restrict__ vnext) {
+// h_{j+1,j} = ||w||; v_{j+1} = w / h_{j+1,j} when it is not zero; block 0 also
+// applies the rotations
+__global__ __launch_bounds__(256) void k_gm_finish(GmStep a, const double* __restrict__ partial) {
     const double hn = block_scalar(partial, 1);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *hslot = hn;
-    if (hn == 0.0) return;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-         e += (int64_t)gridDim.x * blockDim.x)
-        vnext[e] = w[e] / hn;
+    double* vnext = a.V + (int64_t)(a.j + 1) * a.n;
+    if (hn != 0.0)
+        for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < a.n;
+             e += (int64_t)gridDim.x * blockDim.x)
+            vnext[e] = a.w[e] / hn;
+    if (blockIdx.x == 0) gm_givens(a, hn);
 }
 
-hipError_t launch_gm_norm_scale(int64_t n, const double* partial, double* hslot, const double* w,
-                                double* vnext, hipStream_t s) {
-    int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
-    hipLaunchKernelGGL(k_gm_norm_scale, dim3(blocks), dim3(256), 0, s, n, partial, hslot, w, vnext);
+// The fixed-shape sum of one value per lane of the shape, lanes C*1024.. being
+// +0.0 (no sum of lanes that start from +0.0 is -0.0, so adding them changes
+// nothing): thread t holds lanes t + 1024 c.  The first log2(C) strides fold
+// the C values of two lanes into one another (lane l then holds chunk l % C),
+// the strides inside the wavefront are shuffles, and every wavefront sums the
+// 16 C wavefront sums for itself after the one barrier.  All threads get the
+// sum.
+template <int C>
+__device__ __forceinline__ double gm_sum(const double (&in)[C], double* sh) {
+    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    double p[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) p[c] = in[c];
+#pragma unroll
+    for (int w = 1; w < C; w <<= 1) {
+#pragma unroll
+        for (int c = 0; c < C / (2 * w); ++c) {
+            const bool odd = (lane & w) != 0;
+            const double keep = odd ? p[2 * c + 1] : p[2 * c], send = odd ? p[2 * c] : p[2 * c + 1];
+            p[c] = keep + __shfl_xor(send, w);
+        }
+    }
+    double s = p[0];
+#pragma unroll
+    for (int w = C; w < kWave; w <<= 1) s = s + __shfl_xor(s, w);
+    if (lane < C) sh[lane * 16 + wv] = s;
+    __syncthreads();
+    if constexpr (16 * C <= kWave) {
+        s = lane < 16 * C ? sh[lane] : 0.0;
+    } else {
+        constexpr int P = 16 * C / kWave;
+        double q[P];
+#pragma unroll
+        for (int u = 0; u < P; ++u) q[u] = sh[lane * P + u];
+#pragma unroll
+        for (int w = 1; w < P; w <<= 1)
+#pragma unroll
+            for (int u = 0; u < P; u += 2 * w) q[u] = q[u] + q[u + w];
+        s = q[0];
+    }
+#pragma unroll
+    for (int w = 1; w < kWave; w <<= 1) s = s + __shfl_xor(s, w);
+    return s;
+}
+
+// A whole Arnoldi step of a small system in one workgroup: all MGS steps, the
+// norm, v_{j+1} and the rotations; w stays in registers, the next v loads
+// while the sum of this one goes through its stages.  Bound by those stages,
+// about 1.5 us each (4,096 rows, 16 columns on average: 26 us a step; with a
+// launch for every sum and every axpy about 110).
+template <int C>
+__global__ __launch_bounds__(1024) void k_gm_step(GmStep a) {
+    __shared__ double sh[2][16 * C];
+    const int t = threadIdx.x;
+    const int32_t n = (int32_t)a.n;
+    double w[C], v[C], vn[C], p[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int32_t e = t + 1024 * c;
+        w[c] = e < n ? a.w[e] : 0.0;
+        v[c] = e < n ? a.V[e] : 0.0;
+        vn[c] = 0.0;
+    }
+    for (int32_t i = 0; i <= a.j; ++i) {
+        const double* __restrict__ next = a.V + (int64_t)(i + 1) * n;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int32_t e = t + 1024 * c;
+            if (i < a.j && e < n) vn[c] = next[e];
+            p[c] = 0.0 + w[c] * v[c];
+        }
+        const double h = gm_sum<C>(p, sh[i & 1]);
+        if (t == 0) a.H[(int64_t)i * a.m + a.j] = h;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            w[c] = t + 1024 * c < n ? w[c] - h * v[c] : 0.0;
+            v[c] = vn[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) p[c] = 0.0 + w[c] * w[c];
+    const double hn = __builtin_sqrt(gm_sum<C>(p, sh[(a.j + 1) & 1]));
+    if (hn != 0.0) {
+        double* vnext = a.V + (int64_t)(a.j + 1) * n;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (t + 1024 * c < n) vnext[t + 1024 * c] = w[c] / hn;
+    }
+    gm_givens(a, hn);
+}
+
+hipError_t launch_gm_step(const GmStep& a, double* partial, hipStream_t s) {
+    if (a.n <= kGmSmall) {
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, a); };
+        if (a.n <= 1024) go(k_gm_step<1>);
+        else if (a.n <= 2048) go(k_gm_step<2>);
+        else if (a.n <= 4096) go(k_gm_step<4>);
+        else go(k_gm_step<8>);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_dot_partial(a.n, a.w, a.V, partial, s);
+    for (int32_t i = 0; e == hipSuccess && i <= a.j; ++i) {
+        // all blocks read one set of partials while they write the other
+        double *pin = partial + (i & 1) * kDotBlocks, *pout = partial + ((i + 1) & 1) * kDotBlocks;
+        const double* v = a.V + (int64_t)i * a.n;
+        hipLaunchKernelGGL(k_gm_axpy_dot, dim3(kDotBlocks), dim3(kDotThreads), 0, s, a.n, pin,
+                           a.H + (int64_t)i * a.m + a.j, a.w, v, i < a.j ? v + a.n : nullptr, pout);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
+    const int blocks = (int)std::min<int64_t>((a.n + 255) / 256, 2048);
+    hipLaunchKernelGGL(k_gm_finish, dim3(blocks), dim3(256), 0, s, a, partial + ((a.j + 1) & 1) * kDotBlocks);
     return hipGetLastError();
 }
 
@@ -163,20 +362,6 @@ hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, 
     return hipGetLastError();
 }
 
-// The rotation that zeroes b against a: rho = sqrt(a*a + b*b) (each product
-// and the sum rounded on its own, no hypot), c = a / rho, s = b / rho, all
-// correctly rounded binary64 operations.
-struct Rotation {
-    double rho, c, s;
-};
-__device__ __forceinline__ Rotation givens_rotation(double a, double b) {
-    Rotation r;
-    r.rho = __builtin_sqrt(a * a + b * b);
-    r.c = a / r.rho;
-    r.s = b / r.rho;
-    return r;
-}
-
 __global__ void k_givens_batch(int64_t n, const double* __restrict__ a, const double* __restrict__ b,
                                double* rho, double* c, double* s) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -192,42 +377,6 @@ hipError_t launch_givens_batch(int64_t n, const double* a, const double* b, doub
     if (n <= 0) return hipSuccess;
     const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096));
     hipLaunchKernelGGL(k_givens_batch, dim3(blocks), dim3(256), 0, st, n, a, b, rho, c, s);
-    return hipGetLastError();
-}
-
-// Givens: apply rotations 0..j-1 to column j of H, form rotation j with
-// rho = sqrt(a*a + b*b) (no hypot), update g, count the iteration and decide
-// whether the cycle stops (|g_{j+1}| <= tol, maxit reached, or breakdown).
-// H is (m+1) x m, row-major: H[i * m + j].
-__global__ void k_gm_givens(double* H, double* cs, double* sn, double* g, int32_t m, int32_t j,
-                            double tol, int32_t* iters, int32_t maxit, double* hist, int32_t* stop) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const double hn = H[(j + 1) * m + j];
-    for (int32_t i = 0; i < j; ++i) {
-        const double a = H[i * m + j], c = H[(i + 1) * m + j];
-        const double tau = cs[i] * a + sn[i] * c;
-        H[(i + 1) * m + j] = cs[i] * c - sn[i] * a;
-        H[i * m + j] = tau;
-    }
-    const Rotation rot = givens_rotation(H[j * m + j], H[(j + 1) * m + j]);
-    cs[j] = rot.c;
-    sn[j] = rot.s;
-    H[j * m + j] = rot.rho;
-    H[(j + 1) * m + j] = 0.0;
-    g[j + 1] = -sn[j] * g[j];
-    g[j] = cs[j] * g[j];
-    const int32_t it = *iters;
-    const double res = __builtin_fabs(g[j + 1]);
-    if (hist) hist[it] = res;
-    *iters = it + 1;
-    *stop = (res <= tol || it + 1 >= maxit || hn == 0.0) ? 1 : 0;
-}
-
-hipError_t launch_gm_givens(double* H, double* cs, double* sn, double* g, int32_t m, int32_t j,
-                            double tol, int32_t* iters, int32_t maxit, double* hist,
-                            int32_t* stop, hipStream_t s) {
-    hipLaunchKernelGGL(k_gm_givens, dim3(1), dim3(64), 0, s, H, cs, sn, g, m, j, tol, iters, maxit,
-                       hist, stop);
     return hipGetLastError();
 }
 

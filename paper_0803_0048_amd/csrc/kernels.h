@@ -262,15 +262,27 @@ hipError_t launch_dot_partial(int64_t n, const double* x, const double* y, doubl
 hipError_t launch_dot_final(const double* partial, double* out, int sqrt_it, hipStream_t s);
 
 struct GmresDev;  // defined in the Krylov unit
-hipError_t launch_gm_axpy_h(int64_t n, const double* partial, double* hslot, double* w,
-                            const double* v, hipStream_t s);
-hipError_t launch_gm_norm_scale(int64_t n, const double* partial, double* hslot, const double* w,
-                                double* vnext, hipStream_t s);
+// One Arnoldi step j on w = A M^-1 v_j: h_ij and w by modified Gram-Schmidt,
+// v_{j+1}, the rotations and the stopping test; flags (host memory mapped for
+// the device) = iterations, stop, the control block's status.
+struct GmStep {
+    int64_t n;
+    double* V;  // (m + 1) x n
+    double* w;
+    double *H, *cs, *sn, *g;
+    int32_t m, j;
+    double tol;
+    int32_t* iters;
+    int32_t maxit;
+    double* hist;
+    volatile int32_t* flags;
+    const Ctl* ctl;
+};
+constexpr int64_t kGmSmall = 8192;  // most rows whose step runs in one workgroup
+// partial: 2 x kDotBlocks
+hipError_t launch_gm_step(const GmStep& a, double* partial, hipStream_t s);
 hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, double* g0,
                            const double* r, double* v0, hipStream_t s);
-hipError_t launch_gm_givens(double* H, double* cs, double* sn, double* g, int32_t m, int32_t j,
-                            double tol, int32_t* iters, int32_t maxit, double* hist,
-                            int32_t* stop, hipStream_t s);
 // rho, c, s of the rotation of every pair (a_i, b_i), with the same device
 // code as the GMRES step
 hipError_t launch_givens_batch(int64_t n, const double* a, const double* b, double* rho, double* c, double* s,

@@ -41,10 +41,12 @@ struct tpilu_ctx_s {
     // second stream (default priority) for work that overlaps the main one
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+    int32_t* flags = nullptr;   // host memory the GMRES step reports to (a copy and its wait cost 10 us an iteration)
     double* scratch = nullptr;  // device address of the no-alloc scratch on this device
     hipError_t scratch_err = hipSuccess;
     std::string err;
     ~tpilu_ctx_s() {
+        if (flags) (void)hipHostFree(flags);
         if (aux) (void)hipStreamDestroy(aux);
         if (fork_ev) (void)hipEventDestroy(fork_ev);
         if (join_ev) (void)hipEventDestroy(join_ev);
@@ -1726,13 +1728,13 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     DeviceGuard dg(ctx->device);
     hipStream_t s = ctx->stream;
     const int32_t m = restart;
-    // workspace (doubles): V (m+1)n | w, z, t, u (n each) | partial 64 | H (m+1)m |
-    // cs m | sn m | g m+1 | yv m | scal 8 | hist max(maxit,1) | flags (2 int32)
+    // workspace (doubles): V (m+1)n | w, z, t, u (n each) | partial 2 x 64 | H (m+1)m |
+    // cs m | sn m | g m+1 | yv m | scal 8 | hist max(maxit,1) | iterations
     const size_t nn = (size_t)n;
     const size_t mh = (size_t)std::max(maxit, 1);
     const size_t o_w = (size_t)(m + 1) * nn;
     const size_t o_partial = o_w + 4 * nn;
-    const size_t o_H = o_partial + kDotBlocks;
+    const size_t o_H = o_partial + 2 * kDotBlocks;
     const size_t o_cs = o_H + (size_t)(m + 1) * m;
     const size_t o_sn = o_cs + m;
     const size_t o_g = o_sn + m;
@@ -1743,6 +1745,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     const size_t doubles = o_flags + 1;
     double* wsd = pat->grow(pat->ws_gm, sizeof(double) * doubles);
     if (!wsd) return fail(ctx, TPILU_E_NOMEM, "gmres workspace");
+    if (!ctx->flags) HIPCHK(ctx, hipHostMalloc((void**)&ctx->flags, 64, hipHostMallocMapped));
     double* V = wsd;
     double* w = wsd + o_w;
     double* z = w + nn;
@@ -1756,7 +1759,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     double* yv = wsd + o_yv;
     double* scal = wsd + o_scal;  // [0] bnorm [1] beta [2] final residual norm
     double* dhist = wsd + o_hist;
-    int32_t* iflags = reinterpret_cast<int32_t*>(wsd + o_flags);  // [0] iters [1] stop
+    int32_t* iflags = reinterpret_cast<int32_t*>(wsd + o_flags);
     const int32_t ni = (int32_t)n;
 
     HIPCHK(ctx, launch_dot_partial(n, b, b, partial, s));
@@ -1790,29 +1793,19 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
             reset = false;
             if (st) return st;
             HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
-            for (int32_t i = 0; i <= j; ++i) {
-                HIPCHK(ctx, launch_dot_partial(n, w, V + (size_t)i * nn, partial, s));
-                HIPCHK(ctx, launch_gm_axpy_h(n, partial, H + (size_t)i * m + j, w, V + (size_t)i * nn, s));
-            }
-            HIPCHK(ctx, launch_dot_partial(n, w, w, partial, s));
-            HIPCHK(ctx, launch_gm_norm_scale(n, partial, H + (size_t)(j + 1) * m + j, w,
-                                             V + (size_t)(j + 1) * nn, s));
-            HIPCHK(ctx, launch_gm_givens(H, cs, sn, g, m, j, tol, iflags, maxit, dhist, iflags + 1, s));
-            int32_t hf[2] = {0, 0};
-            uint32_t cst = 0;
-            HIPCHK(ctx, hipMemcpyAsync(hf, iflags, sizeof(hf), hipMemcpyDeviceToHost, s));
-            HIPCHK(ctx, hipMemcpyAsync(&cst, &pat->ctl->status, sizeof(cst), hipMemcpyDeviceToHost, s));
+            const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags, pat->ctl};
+            HIPCHK(ctx, launch_gm_step(step, partial, s));
             HIPCHK(ctx, hipStreamSynchronize(s));
-            it_host = hf[0];
+            it_host = ctx->flags[0];
             jj = j + 1;
             // a preconditioner wait that ran out leaves NaN iterates behind,
             // which no stopping test catches: end the solve at once
-            if (cst & kStTimeout) {
+            if ((uint32_t)ctx->flags[2] & kStTimeout) {
                 *iters = it_host;
                 *relres = NAN;
                 return read_ctl(ctx, pat, nullptr, false);
             }
-            if (hf[1]) break;
+            if (ctx->flags[1]) break;
         }
         HIPCHK(ctx, launch_gm_backsub(H, g, yv, m, jj, s));
         HIPCHK(ctx, launch_gm_combine(n, V, yv, jj, u, s));
