@@ -229,6 +229,7 @@ hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_va
 template <bool kUpper>
 __global__ __launch_bounds__(64) void k_apply_inverse_wave(PatDev P, const double* __restrict__ G,
                                                            const double* __restrict__ in, double* __restrict__ out) {
+    if (P.skip && *P.skip) return;
     const int lane = lane_id();
     for (int32_t i = blockIdx.x; i < P.n; i += gridDim.x) {
         const int64_t dj = P.diagF[i];
@@ -265,6 +266,7 @@ __global__ __launch_bounds__(64) void k_apply_inverse_tile(PatDev P, const doubl
                                                       const double* __restrict__ in, double* __restrict__ out) {
     constexpr int kTileStride = kTile + 1;  // odd stride: lanes reading their rows hit distinct banks
     __shared__ double tv[kWave * kTileStride];  // the staged products g_ij * in_j
+    if (P.skip && *P.skip) return;
     const int lane = lane_id();
     for (int64_t r0 = (int64_t)blockIdx.x * kWave; r0 < P.n; r0 += (int64_t)gridDim.x * kWave) {
         const bool has = r0 + lane < P.n;
@@ -328,6 +330,7 @@ template <bool kUpper>
 __global__ __launch_bounds__(256) void k_apply_inverse_rows(PatDev P, const double* __restrict__ G,
                                                             const double* __restrict__ in,
                                                             double* __restrict__ out) {
+    if (P.skip && *P.skip) return;
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P.n) return;
     const int64_t dj = P.diagF[i];

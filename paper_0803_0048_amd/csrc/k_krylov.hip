@@ -6,7 +6,7 @@
 // fixed shape that depends only on the vector length: 16384 lanes each sum a
 // strided subsequence in ascending order from +0.0, then lanes are combined
 // pairwise at strides 1, 2, 4, ..., 8192 (IEEE addition is commutative, so
-// which lane of a pair does the add does not matter).  The launch is
+// which lane of a pair does the add, or whether both do, does not matter).  The launch is
 // 64 blocks x 256 threads = 16384 threads; strides 1..32 are combined inside a
 // wavefront with shuffles, 64 and 128 through LDS, 256..8192 over the 64
 // block partials by whichever kernel consumes the result.  SpMV sums every
@@ -33,14 +33,28 @@ hipError_t launch_spmv(int32_t n, const int64_t* rp, const int32_t* ci, const do
     return hipGetLastError();
 }
 
-// pairwise tree inside a wavefront: lane l (l a multiple of 2w) += lane l+w
+template <int kCtrl>
+__device__ __forceinline__ double dpp_move(double v) {
+    const uint64_t u = as_u64(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, 0xf, 0xf, true);
+    return as_f64(((uint64_t)hi << 32) | lo);
+}
+
+// pairwise tree over the 16 lanes of a row, strides 1, 2, 4, 8: every lane gets
+// the sum (once the lanes of a quad, then of half a row, agree, a mirror image
+// is as good as the lane a stride away)
+__device__ __forceinline__ double row_tree(double s) {
+    s = s + dpp_move<0xB1>(s);   // lane ^ 1
+    s = s + dpp_move<0x4E>(s);   // lane ^ 2
+    s = s + dpp_move<0x141>(s);  // 7 - lane, in the half row
+    return s + dpp_move<0x140>(s);  // 15 - lane
+}
+
+// pairwise tree inside a wavefront, strides 1 .. 32 (every lane gets the sum)
 __device__ __forceinline__ double wave_tree(double s) {
-    const int lane = lane_id();
-    for (int w = 1; w < kWave; w <<= 1) {
-        const double o = __shfl_down(s, w, kWave);
-        if ((lane & (2 * w - 1)) == 0) s = s + o;
-    }
-    return s;
+    s = row_tree(s);
+    return (bcast_lane(s, 0) + bcast_lane(s, 16)) + (bcast_lane(s, 32) + bcast_lane(s, 48));
 }
 
 __global__ __launch_bounds__(256) void k_dot_partial(int64_t n, const double* __restrict__ x,
@@ -118,6 +132,15 @@ __device__ __forceinline__ Rotation givens_rotation(double a, double b) {
     return r;
 }
 
+// The step's outcome to the host, which polls flags[3] for the step's number.
+__device__ __forceinline__ void gm_report(const GmStep& a, int32_t iters, int32_t stop) {
+    if (threadIdx.x != 0) return;
+    a.flags[0] = iters;
+    a.flags[1] = stop;
+    a.flags[2] = (int32_t)ld_u32_coherent(&a.ctl->status);
+    __hip_atomic_store(const_cast<int32_t*>(a.flags) + 3, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Givens, by one workgroup: apply rotations 0..j-1 to column j of H, form
 // rotation j, update g, count the iteration and decide whether the cycle stops
 // (|g_{j+1}| <= tol, maxit reached, or breakdown).  H is (m+1) x m, row-major:
@@ -161,10 +184,9 @@ __device__ __forceinline__ void gm_givens(const GmStep& a, double hn) {
     const double res = __builtin_fabs(gn);
     if (a.hist) a.hist[it] = res;
     *a.iters = it + 1;
-    // the host's copy: read after the stream's end
-    a.flags[0] = it + 1;
-    a.flags[1] = (res <= a.tol || it + 1 >= a.maxit || hn == 0.0) ? 1 : 0;
-    a.flags[2] = (int32_t)ld_u32_coherent(&a.ctl->status);
+    const int32_t stop = (res <= a.tol || it + 1 >= a.maxit || hn == 0.0) ? 1 : 0;
+    a.iters[1] = stop;
+    gm_report(a, it + 1, stop);
 }
 
 // h = <w, v> (from its partials); H slot <- h; w <- w - h v; then the partials
@@ -172,12 +194,14 @@ __device__ __forceinline__ void gm_givens(const GmStep& a, double hn) {
 // Every lane of the fixed shape owns its elements, so what it subtracts is
 // what it sums next.  The loads of kGmAhead elements are in flight together
 // (64 x 256 threads are few).  n=160,000: a dot and an axpy launch 5.7 + 4.9
-// us, 5.2 here.
+// us, 4.7 here.
 constexpr int kGmAhead = 8;
-__global__ __launch_bounds__(256) void k_gm_axpy_dot(int64_t n, const double* __restrict__ pin, double* hslot,
+__global__ __launch_bounds__(256) void k_gm_axpy_dot(int64_t n, const int32_t* __restrict__ iters,
+                                                     const double* __restrict__ pin, double* hslot,
                                                      double* __restrict__ w, const double* __restrict__ v,
                                                      const double* vn, double* __restrict__ pout) {
     __shared__ double sh[4];
+    if (iters[1]) return;
     const double h = block_scalar(pin, 0);
     if (blockIdx.x == 0 && threadIdx.x == 0) *hslot = h;
     double s = 0.0;
@@ -216,91 +240,74 @@ __global__ __launch_bounds__(256) void k_gm_axpy_dot(int64_t n, const double* __
 // h_{j+1,j} = ||w||; v_{j+1} = w / h_{j+1,j} when it is not zero; block 0 also
 // applies the rotations
 __global__ __launch_bounds__(256) void k_gm_finish(GmStep a, const double* __restrict__ partial) {
+    if (a.iters[1]) {
+        if (blockIdx.x == 0) gm_report(a, *a.iters, 1);
+        return;
+    }
     const double hn = block_scalar(partial, 1);
     double* vnext = a.V + (int64_t)(a.j + 1) * a.n;
     if (hn != 0.0)
         for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < a.n;
              e += (int64_t)gridDim.x * blockDim.x)
             vnext[e] = a.w[e] / hn;
+    // (a block that starts after this may find the cycle stopped: v_{j+1} is then not used)
     if (blockIdx.x == 0) gm_givens(a, hn);
 }
 
-// The fixed-shape sum of one value per lane of the shape, lanes C*1024.. being
+// The fixed-shape sum of one value per lane of the shape, lanes 1024 C .. being
 // +0.0 (no sum of lanes that start from +0.0 is -0.0, so adding them changes
-// nothing): thread t holds lanes t + 1024 c.  The first log2(C) strides fold
-// the C values of two lanes into one another (lane l then holds chunk l % C),
-// the strides inside the wavefront are shuffles, and every wavefront sums the
-// 16 C wavefront sums for itself after the one barrier.  All threads get the
-// sum.
+// nothing): thread t holds lanes C t .. C t + C - 1, so the first strides are
+// its own; the strides inside the wavefront move through the VALU (shuffles
+// through LDS took twice as long), and every wavefront sums the 16 wavefront
+// sums for itself after the one barrier.  All threads get the sum.
 template <int C>
 __device__ __forceinline__ double gm_sum(const double (&in)[C], double* sh) {
-    const int lane = lane_id(), wv = threadIdx.x / kWave;
     double p[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) p[c] = in[c];
 #pragma unroll
-    for (int w = 1; w < C; w <<= 1) {
+    for (int w = 1; w < C; w <<= 1)
 #pragma unroll
-        for (int c = 0; c < C / (2 * w); ++c) {
-            const bool odd = (lane & w) != 0;
-            const double keep = odd ? p[2 * c + 1] : p[2 * c], send = odd ? p[2 * c] : p[2 * c + 1];
-            p[c] = keep + __shfl_xor(send, w);
-        }
-    }
-    double s = p[0];
-#pragma unroll
-    for (int w = C; w < kWave; w <<= 1) s = s + __shfl_xor(s, w);
-    if (lane < C) sh[lane * 16 + wv] = s;
+        for (int c = 0; c < C; c += 2 * w) p[c] = p[c] + p[c + w];
+    const double s = wave_tree(p[0]);
+    if (lane_id() == 0) sh[threadIdx.x / kWave] = s;
     __syncthreads();
-    if constexpr (16 * C <= kWave) {
-        s = lane < 16 * C ? sh[lane] : 0.0;
-    } else {
-        constexpr int P = 16 * C / kWave;
-        double q[P];
-#pragma unroll
-        for (int u = 0; u < P; ++u) q[u] = sh[lane * P + u];
-#pragma unroll
-        for (int w = 1; w < P; w <<= 1)
-#pragma unroll
-            for (int u = 0; u < P; u += 2 * w) q[u] = q[u] + q[u + w];
-        s = q[0];
-    }
-#pragma unroll
-    for (int w = 1; w < kWave; w <<= 1) s = s + __shfl_xor(s, w);
-    return s;
+    return bcast_lane(row_tree(sh[lane_id() & 15]), 0);
 }
 
 // A whole Arnoldi step of a small system in one workgroup: all MGS steps, the
 // norm, v_{j+1} and the rotations; w stays in registers, the next v loads
 // while the sum of this one goes through its stages.  Bound by those stages,
-// about 1.5 us each (4,096 rows, 16 columns on average: 26 us a step; with a
+// about 1 us each (4,096 rows, 16 columns on average: 17 us a step, 26 with the
+// sums through LDS shuffles; with a
 // launch for every sum and every axpy about 110).
 template <int C>
 __global__ __launch_bounds__(1024) void k_gm_step(GmStep a) {
-    __shared__ double sh[2][16 * C];
-    const int t = threadIdx.x;
-    const int32_t n = (int32_t)a.n;
+    __shared__ double sh[2][16];
+    if (a.iters[1]) {  // the cycle stopped: this step was launched ahead
+        gm_report(a, *a.iters, 1);
+        return;
+    }
+    const int32_t n = (int32_t)a.n, e0 = (int32_t)threadIdx.x * C;
     double w[C], v[C], vn[C], p[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const int32_t e = t + 1024 * c;
-        w[c] = e < n ? a.w[e] : 0.0;
-        v[c] = e < n ? a.V[e] : 0.0;
+        w[c] = e0 + c < n ? a.w[e0 + c] : 0.0;
+        v[c] = e0 + c < n ? a.V[e0 + c] : 0.0;
         vn[c] = 0.0;
     }
     for (int32_t i = 0; i <= a.j; ++i) {
         const double* __restrict__ next = a.V + (int64_t)(i + 1) * n;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const int32_t e = t + 1024 * c;
-            if (i < a.j && e < n) vn[c] = next[e];
+            if (i < a.j && e0 + c < n) vn[c] = next[e0 + c];
             p[c] = 0.0 + w[c] * v[c];
         }
         const double h = gm_sum<C>(p, sh[i & 1]);
-        if (t == 0) a.H[(int64_t)i * a.m + a.j] = h;
+        if (threadIdx.x == 0) a.H[(int64_t)i * a.m + a.j] = h;
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            w[c] = t + 1024 * c < n ? w[c] - h * v[c] : 0.0;
+            w[c] = e0 + c < n ? w[c] - h * v[c] : 0.0;
             v[c] = vn[c];
         }
     }
@@ -311,7 +318,7 @@ __global__ __launch_bounds__(1024) void k_gm_step(GmStep a) {
         double* vnext = a.V + (int64_t)(a.j + 1) * n;
 #pragma unroll
         for (int c = 0; c < C; ++c)
-            if (t + 1024 * c < n) vnext[t + 1024 * c] = w[c] / hn;
+            if (e0 + c < n) vnext[e0 + c] = w[c] / hn;
     }
     gm_givens(a, hn);
 }
@@ -330,7 +337,7 @@ hipError_t launch_gm_step(const GmStep& a, double* partial, hipStream_t s) {
         // all blocks read one set of partials while they write the other
         double *pin = partial + (i & 1) * kDotBlocks, *pout = partial + ((i + 1) & 1) * kDotBlocks;
         const double* v = a.V + (int64_t)i * a.n;
-        hipLaunchKernelGGL(k_gm_axpy_dot, dim3(kDotBlocks), dim3(kDotThreads), 0, s, a.n, pin,
+        hipLaunchKernelGGL(k_gm_axpy_dot, dim3(kDotBlocks), dim3(kDotThreads), 0, s, a.n, a.iters, pin,
                            a.H + (int64_t)i * a.m + a.j, a.w, v, i < a.j ? v + a.n : nullptr, pout);
         e = hipGetLastError();
     }
@@ -342,23 +349,24 @@ hipError_t launch_gm_step(const GmStep& a, double* partial, hipStream_t s) {
 
 // cycle start: beta = ||r||, g_0 = beta, v_0 = r / beta
 __global__ __launch_bounds__(256) void k_gm_start(int64_t n, const double* __restrict__ partial,
-                                                  double* beta_slot, double* g0,
+                                                  double* beta_slot, double* g0, int32_t* stop,
                                                   const double* __restrict__ r,
                                                   double* __restrict__ v0) {
     const double beta = block_scalar(partial, 1);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *beta_slot = beta;
         *g0 = beta;
+        *stop = 0;
     }
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
          e += (int64_t)gridDim.x * blockDim.x)
         v0[e] = r[e] / beta;
 }
 
-hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, double* g0,
+hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, double* g0, int32_t* stop,
                            const double* r, double* v0, hipStream_t s) {
     int blocks = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 2048));
-    hipLaunchKernelGGL(k_gm_start, dim3(blocks), dim3(256), 0, s, n, partial, beta_slot, g0, r, v0);
+    hipLaunchKernelGGL(k_gm_start, dim3(blocks), dim3(256), 0, s, n, partial, beta_slot, g0, stop, r, v0);
     return hipGetLastError();
 }
 

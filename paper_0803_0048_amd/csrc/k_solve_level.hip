@@ -183,7 +183,8 @@ template <int KE>
 __global__ __launch_bounds__(1024) void k_solve_lds(int32_t n, LevelSched Lo, LevelSched Up,
                                                     const double* __restrict__ F, const int32_t* __restrict__ ci,
                                                     const double* __restrict__ b, double* x, double* y, int sweeps,
-                                                    int reset, Ctl* ctl, unsigned long long* trace) {
+                                                    int reset, Ctl* ctl, unsigned long long* trace, const int32_t* skip) {
+    if (skip && *skip) return;  // a GMRES cycle that has stopped
     extern __shared__ double xsh[];  // [n]: x, then y in its place; [n + 1]: 0.0
     __shared__ int32_t sh_done;
     LdsDouble* xs = (LdsDouble*)xsh;
@@ -209,12 +210,13 @@ __global__ __launch_bounds__(1024) void k_solve_lds(int32_t n, LevelSched Lo, Le
 
 hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& Up, int32_t max_half,
                             const double* f_val, const int32_t* ci, const double* b, double* x, double* y, int sweeps,
-                            bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s) {
+                            bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s, const int32_t* skip) {
     if (n <= 0) return hipSuccess;
     const size_t lds = ((size_t)n + 1) * sizeof(double);
     const int rs = reset ? 1 : 0;
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(1), dim3(1024), lds, s, n, Lo, Up, f_val, ci, b, x, y, sweeps, rs, ctl, trace);
+        hipLaunchKernelGGL(kern, dim3(1), dim3(1024), lds, s, n, Lo, Up, f_val, ci, b, x, y, sweeps, rs, ctl, trace,
+                           skip);
     };
     if (max_half <= 4) go(k_solve_lds<4>);
     else if (max_half <= 8) go(k_solve_lds<8>);

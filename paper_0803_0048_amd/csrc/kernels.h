@@ -150,6 +150,7 @@ struct PatDev {
     const int64_t* tptr;  // per F slot: start of the updates it receives; [nnz_f + 1]
     const int32_t* tsl;   // update: row-local slot of the pivot entry f_jh (ascending h per target)
     const int32_t* tq;    // update: slot of f_ht in row h
+    const int32_t* skip = nullptr;  // products with the inverses: nothing to do when it points at a nonzero
 };
 
 // fill `n` doubles with kPending; thread 0 also resets ctl->ticket (and, if
@@ -219,7 +220,8 @@ constexpr int32_t kLdsSolveHalf = 16;     // most entries of a row half there
 // sweeps: 1 forward (x nullable), 2 backward (reads x), 3 both in one launch (x nullable)
 hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& Up, int32_t max_half,
                             const double* f_val, const int32_t* ci, const double* b, double* x, double* y, int sweeps,
-                            bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s);
+                            bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s,
+                            const int32_t* skip = nullptr);
 // one sweep on one XCD with grid wavefronts there (out pre-filled with kPending)
 hipError_t launch_solve_chunks(const PatDev& P, const LevelSched& L, int32_t max_half, const double* f_val,
                                const double* in, double* out, bool backward, int32_t grid, Ctl* ctl,
@@ -264,7 +266,7 @@ hipError_t launch_dot_final(const double* partial, double* out, int sqrt_it, hip
 struct GmresDev;  // defined in the Krylov unit
 // One Arnoldi step j on w = A M^-1 v_j: h_ij and w by modified Gram-Schmidt,
 // v_{j+1}, the rotations and the stopping test; flags (host memory mapped for
-// the device) = iterations, stop, the control block's status.
+// the device) = iterations, stop, the control block's status, and then seq.
 struct GmStep {
     int64_t n;
     double* V;  // (m + 1) x n
@@ -272,16 +274,17 @@ struct GmStep {
     double *H, *cs, *sn, *g;
     int32_t m, j;
     double tol;
-    int32_t* iters;
+    int32_t* iters;  // [0] iterations, [1] the cycle has stopped: the step does nothing
     int32_t maxit;
     double* hist;
     volatile int32_t* flags;
+    int32_t seq;
     const Ctl* ctl;
 };
 constexpr int64_t kGmSmall = 8192;  // most rows whose step runs in one workgroup
 // partial: 2 x kDotBlocks
 hipError_t launch_gm_step(const GmStep& a, double* partial, hipStream_t s);
-hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, double* g0,
+hipError_t launch_gm_start(int64_t n, const double* partial, double* beta_slot, double* g0, int32_t* stop,
                            const double* r, double* v0, hipStream_t s);
 // rho, c, s of the rotation of every pair (a_i, b_i), with the same device
 // code as the GMRES step

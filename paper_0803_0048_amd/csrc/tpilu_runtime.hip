@@ -41,7 +41,9 @@ struct tpilu_ctx_s {
     // second stream (default priority) for work that overlaps the main one
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    int32_t* flags = nullptr;   // host memory the GMRES step reports to (a copy and its wait cost 10 us an iteration)
+    // mapped host memory the GMRES steps report to: [0] iterations, [1] stop,
+    // [2] status, [3] number of the last step that reported; [4] of the last launched
+    int32_t* flags = nullptr;
     double* scratch = nullptr;  // device address of the no-alloc scratch on this device
     hipError_t scratch_err = hipSuccess;
     std::string err;
@@ -644,14 +646,15 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
 // forward = false: x already holds L~^-1 b (the batched factorization with
 // the forward substitution fused in); only the backward sweep runs
 // keep_x: the caller wants x (the one-launch shape stores it only then).
+// skip: device flag, nonzero: nothing to do (the one-launch shape only).
 tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val, int32_t batch,
                            const double* b, double* y, double* x, bool reset, Ctl* ctl, bool timed = true,
-                           bool forward = true, bool keep_x = false) {
+                           bool forward = true, bool keep_x = false, const int32_t* skip = nullptr) {
     if (solve_in_lds(ctx, pat, batch)) {
         const int32_t half = std::max(pat->st.max_lrow, pat->st.max_upart);
         auto go = [&](double* xp, int sweeps, bool rs) {
             return launch_solve_lds((int32_t)pat->n, pat->lsL, pat->lsU, half, f_val, pat->ciF, b, xp, y, sweeps, rs,
-                                    ctl, ctx->trace, ctx->stream);
+                                    ctl, ctx->trace, ctx->stream, skip);
         };
         if (!ctx->timing || !timed) {
             HIPCHK(ctx, go(keep_x ? x : nullptr, 3, reset));
@@ -1705,12 +1708,28 @@ __global__ void k_fill_f64(double* p, int64_t n, double v) {
 namespace {
 // z = M^-1 v: the two substitutions with F, or the two products with G
 tpilu_status enqueue_precond(tpilu_ctx ctx, tpilu_pattern pat, const double* m_val, bool inverse,
-                             const double* v, double* z, double* t, bool reset) {
-    if (!inverse) return enqueue_apply(ctx, pat, m_val, 1, v, z, t, reset, pat->ctl);
+                             const double* v, double* z, double* t, bool reset, const int32_t* skip = nullptr) {
+    if (!inverse) return enqueue_apply(ctx, pat, m_val, 1, v, z, t, reset, pat->ctl, true, true, false, skip);
     if (reset) HIPCHK(ctx, launch_fill_pending(nullptr, 0, pat->ctl, true, ctx->stream));
-    HIPCHK(ctx, launch_apply_inverse(pdev(ctx, pat), m_val, v, t, z, inverse_product_shape(ctx, pat),
-                                     ctx->stream));
+    PatDev P = pdev(ctx, pat);
+    P.skip = skip;
+    HIPCHK(ctx, launch_apply_inverse(P, m_val, v, t, z, inverse_product_shape(ctx, pat), ctx->stream));
     return TPILU_OK;
+}
+
+// Wait until a GMRES step has reported: its number appears in mapped memory.
+// The stream is asked now and then, so that a failure ends the wait.
+tpilu_status await_step(tpilu_ctx ctx, int32_t seq) {
+    for (;;) {
+        for (int spin = 0; spin < 4096; ++spin)
+            if (__atomic_load_n(&ctx->flags[3], __ATOMIC_ACQUIRE) - seq >= 0) return TPILU_OK;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipErrorNotReady) continue;
+        HIPCHK(ctx, e);
+        // the stream is done, so the report is there
+        if (__atomic_load_n(&ctx->flags[3], __ATOMIC_ACQUIRE) - seq >= 0) return TPILU_OK;
+        return fail(ctx, TPILU_E_DEVICE, "a GMRES step did not report");
+    }
 }
 
 tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, const double* f_val, bool inverse,
@@ -1745,7 +1764,15 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     const size_t doubles = o_flags + 1;
     double* wsd = pat->grow(pat->ws_gm, sizeof(double) * doubles);
     if (!wsd) return fail(ctx, TPILU_E_NOMEM, "gmres workspace");
-    if (!ctx->flags) HIPCHK(ctx, hipHostMalloc((void**)&ctx->flags, 64, hipHostMallocMapped));
+    if (!ctx->flags) {
+        HIPCHK(ctx, hipHostMalloc((void**)&ctx->flags, 64, hipHostMallocMapped));
+        std::memset(ctx->flags, 0, 64);
+    }
+    // The next step is launched before this one has reported, so that the
+    // device does not wait for the host (about 25 us an iteration): a step
+    // after the last one finds the stop flag and leaves, which only the
+    // preconditioners that look at it themselves can do as well.
+    const bool ahead = !ctx->timing && (inverse || solve_in_lds(ctx, pat, 1));
     double* V = wsd;
     double* w = wsd + o_w;
     double* z = w + nn;
@@ -1785,17 +1812,26 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
         HIPCHK(ctx, hipMemcpyAsync(&beta, scal + 1, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));
         if (beta <= tol || it_host >= maxit) break;
-        HIPCHK(ctx, launch_gm_start(n, partial, scal + 1, g, w, V, s));
+        HIPCHK(ctx, launch_gm_start(n, partial, scal + 1, g, iflags + 1, w, V, s));
         int32_t jj = 0;
-        for (int32_t j = 0; j < m; ++j) {
-            double* vj = V + (size_t)j * nn;
-            st = enqueue_precond(ctx, pat, f_val, inverse, vj, z, t, reset);
+        const int32_t seq0 = ctx->flags[4];  // steps reported so far
+        auto enqueue_step = [&](int32_t j) -> tpilu_status {
+            tpilu_status se = enqueue_precond(ctx, pat, f_val, inverse, V + (size_t)j * nn, z, t, reset, iflags + 1);
             reset = false;
-            if (st) return st;
+            if (se) return se;
             HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
-            const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags, pat->ctl};
+            const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags,
+                              ++ctx->flags[4], pat->ctl};
             HIPCHK(ctx, launch_gm_step(step, partial, s));
-            HIPCHK(ctx, hipStreamSynchronize(s));
+            return TPILU_OK;
+        };
+        int32_t queued = 0;
+        for (int32_t j = 0; j < m; ++j) {
+            const int32_t upto = std::min(m, j + 1 + (ahead ? 1 : 0));
+            for (; queued < upto; ++queued)
+                if ((st = enqueue_step(queued))) return st;
+            st = await_step(ctx, seq0 + j + 1);
+            if (st) return st;
             it_host = ctx->flags[0];
             jj = j + 1;
             // a preconditioner wait that ran out leaves NaN iterates behind,
