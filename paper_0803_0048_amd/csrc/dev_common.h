@@ -353,6 +353,63 @@ __device__ __forceinline__ bool xcd_member(Ctl* ctl) {
     return __builtin_amdgcn_readfirstlane(l) == me;
 }
 
+// Row sums s_i = sum of v_q * in[ci_q] over the slots [a_i, b_i) of row i, from
+// +0.0 in ascending q, kRows consecutive rows per wavefront: the wavefront
+// stages the products of the next kTile entries of all its rows in LDS with
+// coalesced loads (an instruction covers kTile consecutive entries of 64 /
+// kTile rows), then lane r adds row r0 + r's in order, so the rows' chains run
+// side by side.  A round costs two memory latencies (columns and values, then
+// the gathers).  Fewer rows per wavefront waste fewer rounds on rows shorter
+// than the longest and leave more wavefronts to a CU; a longer tile wastes
+// lanes on short rows.  Entries past a row's end load a clamped, in-bounds slot
+// and are not stored.  (Rows sorted by length measured slower.)  tv: kRows *
+// (kTile + 1) doubles of LDS (odd stride: lanes reading their rows hit distinct
+// banks).
+template <int kTile, int kRows, class Range, class Finish>
+__device__ __forceinline__ void row_products(int32_t n, const int32_t* __restrict__ ci, const double* __restrict__ val,
+                                             const double* __restrict__ in, double* tv, Range range, Finish finish) {
+    constexpr int kLoads = kTile * kRows / kWave, kPer = kWave / kTile;  // loads per round, rows per load
+    static_assert(kLoads >= 1 && kLoads <= 32, "one bit per load");
+    const int lane = lane_id(), kk = lane % kTile;
+    for (int64_t r0 = (int64_t)blockIdx.x * kRows; r0 < n; r0 += (int64_t)gridDim.x * kRows) {
+        const bool has = lane < kRows && r0 + lane < n;
+        int32_t a = 0, b = 0;
+        if (has) range((int32_t)r0 + lane, a, b);
+        const int32_t len = b - a;
+        int32_t maxlen = len;
+        for (int off = 32; off > 0; off >>= 1) maxlen = max(maxlen, __shfl_xor(maxlen, off));
+        double s = 0.0;
+        for (int32_t k0 = 0; k0 < maxlen; k0 += kTile) {
+            int32_t cu[kLoads];
+            double gu[kLoads];
+            uint32_t on = 0u;
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                const int rr = u * kPer + lane / kTile;  // row of the tile
+                const int32_t ar = __shfl(a, rr), br = __shfl(b, rr);
+                const int32_t e = ar + k0 + kk;
+                if (e < br) on |= 1u << u;
+                const int32_t ec = e < br ? e : (br > ar ? br - 1 : 0);
+                cu[u] = ci[ec];
+                gu[u] = val[ec];
+            }
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) gu[u] = gu[u] * in[cu[u]];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u)
+                if (on & (1u << u)) tv[(u * kPer + lane / kTile) * (kTile + 1) + kk] = gu[u];
+            wave_sync();
+            const int32_t cnt = max(0, min(kTile, len - k0));
+            const int row = kRows < kWave ? lane & (kRows - 1) : lane;
+#pragma unroll
+            for (int k = 0; k < kTile; ++k)
+                if (k < cnt) s = s + tv[row * (kTile + 1) + k];
+            wave_sync();
+        }
+        if (has) finish((int32_t)r0 + lane, s);
+    }
+}
+
 // Running subtraction s <- s - f_k * v_k for k = 0 .. cnt-1 in that order,
 // where lane k holds f_k and the address of v_k (cnt <= 64).  The values are
 // produced by other rows; the chain advances over every prefix of entries

@@ -246,81 +246,26 @@ __global__ __launch_bounds__(64) void k_apply_inverse_wave(PatDev P, const doubl
     }
 }
 
-// 64 rows per wavefront, lane r owning row r0 + r and adding its products in
-// order.  The wavefront stages the next kTile entries of all 64 rows in LDS
-// with coalesced loads (each load instruction covers kTile consecutive
-// entries of 64 / kTile rows), then every lane walks its own row there: the
-// in-order sum of a row is one lane's chain, so the wavefront's 64 chains run
-// side by side instead of one at a time.
-// kTile entries per row per staging round (at most 32: one bit per staged
-// slice in `on`): 8 for short rows (a round of 16 mostly stages nothing;
-// 7-point 64^3 ILU(1), about 6 entries per half: 0.021 ms with 8, 0.042 with
-// 16, both products), else 32 (27-point 50^3 ILU(3), about 82 per half: 0.084
-// ms with 32, 0.101 with 16; random banded n=160,000 ILU(2): 0.220 / 0.237 ms).
-// Rows in their natural order, 64 consecutive ones to a wavefront: their
-// entries and the in_j they gather lie close together.  (Sorting the rows by
-// length so that a wavefront's lanes finish together measured slower on every
-// pattern tried, even and uneven alike.)
-template <bool kUpper, int kTile>
+// kRows rows per wavefront (row_products).  Both products, MI355X: random
+// banded n=160,000 ILU(2), 82 entries per half (longest 419): 0.185 ms with 16
+// rows and 32 entries a round, 0.194 with 32 rows, 0.214 with 64, 0.234 with 64
+// rows and 16 entries; 27-point 50^3 ILU(3), 82: 0.075 / 0.078 / 0.080 / 0.097;
+// 7-point 64^3 ILU(2), 11: 32 rows and 16 entries 0.032, 16 and 32 0.036, 64
+// and 8 0.045; ILU(1), 6: 0.024 / 0.034 / 0.021.  What bounds the first are the
+// gathers of in_j, two thirds of a line of L1 fill for 12 bytes of F.
+template <bool kUpper, int kTile, int kRows>
 __global__ __launch_bounds__(64) void k_apply_inverse_tile(PatDev P, const double* __restrict__ G,
                                                       const double* __restrict__ in, double* __restrict__ out) {
-    constexpr int kTileStride = kTile + 1;  // odd stride: lanes reading their rows hit distinct banks
-    __shared__ double tv[kWave * kTileStride];  // the staged products g_ij * in_j
+    __shared__ double tv[kRows * (kTile + 1)];
     if (P.skip && *P.skip) return;
-    const int lane = lane_id();
-    for (int64_t r0 = (int64_t)blockIdx.x * kWave; r0 < P.n; r0 += (int64_t)gridDim.x * kWave) {
-        const bool has = r0 + lane < P.n;
-        const int64_t i = has ? r0 + lane : 0;
-        int64_t a = 0, b = 0;
-        if (has) {
-            const int64_t dj = P.diagF[i];
-            a = kUpper ? dj : P.rpF[i];
-            b = kUpper ? P.rpF[i + 1] : dj;
-        }
-        int64_t len = b - a, maxlen = len;
-        for (int off = 32; off > 0; off >>= 1) maxlen = max(maxlen, (int64_t)__shfl_xor(maxlen, off));
-        double s = 0.0;
-        for (int64_t k0 = 0; k0 < maxlen; k0 += kTile) {
-            // stage the products of entries k0 .. k0+kTile-1 of every row:
-            // instruction u takes rows u*(64/kTile) .. +(64/kTile)-1, kTile
-            // consecutive entries each, so both the entries and the gathered
-            // in_j of one row (sorted columns, often close together) come in
-            // whole lines; each lane then adds its own row's products in order
-            // in three phases (column and value loads of every u, then the
-            // gathers, then the products), so a round costs two memory
-            // latencies; entries past a row's end load a clamped, in-bounds
-            // slot and are not stored
-            int32_t cu[kTile];
-            double gu[kTile];
-            uint32_t on = 0u;
-            const int kk = lane % kTile;  // entry of the row's slice
-#pragma unroll
-            for (int u = 0; u < kTile; ++u) {
-                const int rr = u * (kWave / kTile) + lane / kTile;  // row of the tile
-                const int64_t ar = __shfl(a, rr), br = __shfl(b, rr);
-                const int64_t e = ar + k0 + kk;
-                if (e < br) on |= 1u << u;
-                const int64_t ec = e < br ? e : (br > ar ? br - 1 : 0);
-                cu[u] = P.ciF[ec];
-                gu[u] = G[ec];
-            }
-#pragma unroll
-            for (int u = 0; u < kTile; ++u) gu[u] = gu[u] * in[cu[u]];
-#pragma unroll
-            for (int u = 0; u < kTile; ++u)
-                if (on & (1u << u)) tv[(u * (kWave / kTile) + lane / kTile) * kTileStride + kk] = gu[u];
-            wave_sync();
-            const int32_t cnt = (int32_t)max<int64_t>(0, min<int64_t>(kTile, len - k0));
-#pragma unroll
-            for (int kk = 0; kk < kTile; ++kk)
-                if (kk < cnt) s = s + tv[lane * kTileStride + kk];
-            wave_sync();
-        }
-        if (has) {
-            if (!kUpper) s = s + in[i];
-            out[i] = s;
-        }
-    }
+    row_products<kTile, kRows>(
+        P.n, P.ciF, G, in, tv,
+        [&](int32_t i, int32_t& a, int32_t& b) {
+            const int32_t dj = P.diagF[i];
+            a = kUpper ? dj : (int32_t)P.rpF[i];
+            b = kUpper ? (int32_t)P.rpF[i + 1] : dj;
+        },
+        [&](int32_t i, double s) { out[i] = kUpper ? s : s + in[i]; });
 }
 
 // one thread per row: the row's products and their sum in order, no
@@ -348,15 +293,15 @@ hipError_t launch_apply_inverse(const PatDev& P, const double* g_val, const doub
         const int grid = (P.n + 255) / 256;
         hipLaunchKernelGGL(k_apply_inverse_rows<false>, dim3(grid), dim3(256), 0, s, P, g_val, b, x);
         hipLaunchKernelGGL(k_apply_inverse_rows<true>, dim3(grid), dim3(256), 0, s, P, g_val, x, y);
-    } else if (shape == kProdTile || shape == kProdTileShort) {
-        const int grid = std::min((P.n + kWave - 1) / kWave, 65536);
-        if (shape == kProdTileShort) {
-            hipLaunchKernelGGL((k_apply_inverse_tile<false, 8>), dim3(grid), dim3(64), 0, s, P, g_val, b, x);
-            hipLaunchKernelGGL((k_apply_inverse_tile<true, 8>), dim3(grid), dim3(64), 0, s, P, g_val, x, y);
-        } else {
-            hipLaunchKernelGGL((k_apply_inverse_tile<false, 32>), dim3(grid), dim3(64), 0, s, P, g_val, b, x);
-            hipLaunchKernelGGL((k_apply_inverse_tile<true, 32>), dim3(grid), dim3(64), 0, s, P, g_val, x, y);
-        }
+    } else if (shape != kProdWaveRows) {
+        auto go = [&](auto lo, auto up, int rows) {
+            const int grid = std::min((P.n + rows - 1) / rows, 65536);
+            hipLaunchKernelGGL(lo, dim3(grid), dim3(64), 0, s, P, g_val, b, x);
+            hipLaunchKernelGGL(up, dim3(grid), dim3(64), 0, s, P, g_val, x, y);
+        };
+        if (shape == kProdTileShort) go(k_apply_inverse_tile<false, 8, 64>, k_apply_inverse_tile<true, 8, 64>, 64);
+        else if (shape == kProdTileMid) go(k_apply_inverse_tile<false, 16, 32>, k_apply_inverse_tile<true, 16, 32>, 32);
+        else go(k_apply_inverse_tile<false, 32, 16>, k_apply_inverse_tile<true, 32, 16>, 16);
     } else {
         const int grid = std::min(P.n, 65536);
         hipLaunchKernelGGL(k_apply_inverse_wave<false>, dim3(grid), dim3(64), 0, s, P, g_val, b, x);

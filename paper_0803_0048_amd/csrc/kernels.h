@@ -257,7 +257,7 @@ constexpr int kDotLanes = 16384;  // fixed shape of every inner product
 constexpr int kDotBlocks = 64;
 constexpr int kDotThreads = 256;
 
-hipError_t launch_spmv(int32_t n, const int64_t* rp, const int32_t* ci, const double* v,
+hipError_t launch_spmv(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const double* v,
                        const double* x, const double* b_minus, double* y, hipStream_t s);
 hipError_t launch_dot_partial(int64_t n, const double* x, const double* y, double* partial,
                               hipStream_t s);
@@ -365,8 +365,8 @@ hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_va
                           Ctl* ctl, uint64_t spin_limit, int32_t grid, hipStream_t s);
 // x = L~~^-1 b, y = U~~^-1 x; thread_rows: one thread per row, else a wavefront
 // shapes of the two products of the incomplete inverses
-// (kProdTile stages 32 entries per row and round, kProdTileShort 8)
-enum { kProdWaveRows = 0, kProdThreadRows = 1, kProdTile = 2, kProdTileShort = 3 };
+// (entries per row and round: kProdTile 32, kProdTileMid 16, kProdTileShort 8)
+enum { kProdWaveRows = 0, kProdThreadRows = 1, kProdTile = 2, kProdTileMid = 3, kProdTileShort = 4 };
 hipError_t launch_apply_inverse(const PatDev& P, const double* g_val, const double* b, double* x, double* y,
                                 int shape, hipStream_t s);
 

@@ -844,23 +844,22 @@ tpilu_status compute_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
 }
 
 // Shape of the two products (kProd*): as the solver mode asks (1 a wavefront
-// per row, 3 a thread per row) or automatically: 64 rows per wavefront
-// staged through LDS (each lane one row's in-order sum) when the rows are of
-// even length (longest row at most 1.5 x the average) and not very long,
-// else a wavefront per row.  Measured on MI355X (both products): 7-point
-// 64^3 ILU(1), 13 entries per row: 0.042 ms tiled, 0.061 by thread, 0.165
-// by wavefront; 27-point 50^3 ILU(3), 165 per row (longest 183): 0.147 vs
-// 0.225 ms by wavefront; random banded n=160,000 ILU(2), 164 per row (longest
-// 419): 0.29 ms by wavefront, 0.35 tiled; paper-scale ILU(1), 1,276 per row:
-// 1.9 ms by wavefront, 2.8 tiled.
+// per row, 3 a thread per row) or automatically: tiles of 64, 32 or 16 rows a
+// wavefront staged through LDS (each lane one row's in-order sum) when the rows
+// are not very long, else a wavefront per row.  Measured on MI355X (both
+// products): 7-point 64^3 ILU(1), 13 entries per row: 0.021 ms tiled, 0.061 by
+// thread, 0.165 by wavefront; 27-point 50^3 ILU(3), 165 per row: 0.073 vs 0.225
+// ms by wavefront; random banded n=160,000 ILU(2), 164 per row (longest 419):
+// 0.185 vs 0.29; paper-scale ILU(1), 1,276 per row: 1.9 ms by wavefront, 2.8
+// tiled.
 constexpr int64_t kInvTileMaxAvg = 512;
-constexpr int64_t kInvShortAvg = 24;  // entries per row of F at or below: 8-entry tiles
+constexpr int64_t kInvShortAvg = 14, kInvMidAvg = 30;  // entries per row of F at or below: 8- and 16-entry tiles
 int inverse_product_shape(tpilu_ctx ctx, tpilu_pattern pat) {
     if (ctx->solver == 1) return kProdWaveRows;
     if (ctx->solver == 3) return kProdThreadRows;
     const int64_t n = std::max<int64_t>(pat->n, 1);
     if (pat->nnz_f > kInvTileMaxAvg * n) return kProdWaveRows;
-    return pat->nnz_f <= kInvShortAvg * n ? kProdTileShort : kProdTile;
+    return pat->nnz_f <= kInvShortAvg * n ? kProdTileShort : pat->nnz_f <= kInvMidAvg * n ? kProdTileMid : kProdTile;
 }
 
 tpilu_status build_inverse_sched(tpilu_ctx ctx, tpilu_pattern pat) {
@@ -1605,7 +1604,7 @@ extern "C" TPILU_API tpilu_status tpilu_spmv(tpilu_ctx ctx, tpilu_pattern pat, c
     tpilu_status st = check_common(ctx, pat, 1);
     if (st) return st;
     DeviceGuard dg(ctx->device);
-    HIPCHK(ctx, launch_spmv((int32_t)pat->n, pat->rpA, pat->ciA, a_val, x, nullptr, y, ctx->stream));
+    HIPCHK(ctx, launch_spmv((int32_t)pat->n, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, nullptr, y, ctx->stream));
     return TPILU_OK;
 }
 
@@ -1805,7 +1804,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     int32_t it_host = 0;
     bool reset = true;
     for (;;) {
-        HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, x, b, w, s));
+        HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, w, s));
         HIPCHK(ctx, launch_dot_partial(n, w, w, partial, s));
         HIPCHK(ctx, launch_dot_final(partial, scal + 1, 1, s));
         double beta = 0.0;
@@ -1819,7 +1818,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
             tpilu_status se = enqueue_precond(ctx, pat, f_val, inverse, V + (size_t)j * nn, z, t, reset, iflags + 1);
             reset = false;
             if (se) return se;
-            HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
             const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags,
                               ++ctx->flags[4], pat->ctl};
             HIPCHK(ctx, launch_gm_step(step, partial, s));
@@ -1849,7 +1848,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
         if (st) return st;
         HIPCHK(ctx, launch_axpy1(n, x, z, s));
     }
-    HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, x, b, w, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, w, s));
     HIPCHK(ctx, launch_dot_partial(n, w, w, partial, s));
     HIPCHK(ctx, launch_dot_final(partial, scal + 2, 1, s));
     double rn = 0.0;
@@ -1924,7 +1923,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
     }
     const double tol = rtol * bnorm;
     // r = b - A x, rs = r, p = v = 0, rho = alpha = omega = 1
-    HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, x, b, r, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, r, s));
     HIPCHK(ctx, launch_copy(rs, r, n, s));
     {
         const double init[8] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 0.0, 0.0};
@@ -1952,7 +1951,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
             st = enqueue_precond(ctx, pat, m_val, inv, p, ph, tmp, reset);
             reset = false;
             if (st) return st;
-            HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, ph, nullptr, v, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, ph, nullptr, v, s));
             HIPCHK(ctx, launch_dot_partial(n, rs, v, pa, s));
             HIPCHK(ctx, launch_bi(kBiOpAlpha, n, 0, pa, nullptr, sc, nullptr, nullptr, nullptr, nullptr, nullptr,
                                   nullptr, s));
@@ -1979,7 +1978,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
             }
             st = enqueue_precond(ctx, pat, m_val, inv, sv, sh, tmp, false);
             if (st) return st;
-            HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, sh, nullptr, t, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, sh, nullptr, t, s));
             HIPCHK(ctx, launch_dot_partial(n, t, sv, pa, s));
             HIPCHK(ctx, launch_dot_partial(n, t, t, pb, s));
             HIPCHK(ctx, launch_bi(kBiOpOmega, n, 0, pa, pb, sc, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -2010,7 +2009,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
         }
     }
     // true residual
-    HIPCHK(ctx, launch_spmv(ni, pat->rpA, pat->ciA, a_val, x, b, tmp, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, tmp, s));
     double rn = 0.0;
     st = nrm(tmp, &rn);
     if (st) return st;
