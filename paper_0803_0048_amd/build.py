@@ -27,7 +27,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtpilu.so")
 JITTER_LIB = os.path.join(HERE, "libtpilu_jitter.so")
-SOURCES = ["k_symbolic.hip", "k_numeric.hip", "k_solve.hip", "k_solve_cu.hip", "k_solve_level.hip", "k_solve_block.hip", "k_krylov.hip", "k_adjoint.hip",
+SOURCES = ["k_symbolic.hip", "k_numeric.hip", "k_numeric_level.hip", "k_solve.hip", "k_solve_cu.hip", "k_solve_level.hip", "k_solve_block.hip", "k_krylov.hip", "k_adjoint.hip",
            "k_inverse.hip", "k_probe.hip", "tpilu_runtime.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

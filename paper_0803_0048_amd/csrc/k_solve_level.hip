@@ -37,8 +37,8 @@ namespace tpilu {
 // (first position, end, first chunk of its level, 0); depth comes from device
 // memory, the chunk count goes there.
 __global__ __launch_bounds__(1024) void k_level_chunks(const int64_t* __restrict__ off,
-                                                       const int32_t* __restrict__ depth, int4* __restrict__ head,
-                                                       int32_t* __restrict__ nchunk) {
+                                                       const int32_t* __restrict__ depth, int32_t size,
+                                                       int4* __restrict__ head, int32_t* __restrict__ nchunk) {
     __shared__ int32_t sh[1024];
     const int tid = threadIdx.x;
     const int32_t levels = *depth;
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(1024) void k_level_chunks(const int64_t* __restrict
     for (int32_t l0 = 0; l0 < levels; l0 += 1024) {
         const int32_t l = l0 + tid;
         const int32_t a = l < levels ? (int32_t)off[l] : 0, b = l < levels ? (int32_t)off[l + 1] : 0;
-        const int32_t c = (b - a + kWave - 1) / kWave;
+        const int32_t c = (b - a + size - 1) / size;
         sh[tid] = c;
         __syncthreads();
         for (int w = 1; w < 1024; w <<= 1) {
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(1024) void k_level_chunks(const int64_t* __restrict
         }
         const int32_t first = base + sh[tid] - c;
         for (int32_t k = 0; k < c; ++k)
-            head[first + k] = make_int4(a + k * kWave, min(a + (k + 1) * kWave, b), first, 0);
+            head[first + k] = make_int4(a + k * size, min(a + (k + 1) * size, b), first, 0);
         base += sh[1023];
         __syncthreads();
     }
@@ -83,11 +83,17 @@ __global__ void k_level_recs(int32_t n, const int64_t* __restrict__ off, const i
     rec[p] = make_int4(i, q, kBackward ? q - d : d - q, l >= kHintLevels ? perm[off[l - kHintLevels + 1] - 1] : -1);
 }
 
+hipError_t launch_level_chunks(const int64_t* off, const int32_t* max_depth, int32_t size, int4* head, int32_t* nchunk,
+                               hipStream_t s) {
+    hipLaunchKernelGGL(k_level_chunks, dim3(1), dim3(1024), 0, s, off, max_depth, size, head, nchunk);
+    return hipGetLastError();
+}
+
 hipError_t launch_level_sched(int32_t n, const int64_t* off, const int32_t* depth, const int32_t* max_depth,
                               const int32_t* perm, const int64_t* rpF, const int32_t* diagF, bool backward, int4* rec,
                               int4* head, int32_t* nchunk, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_level_chunks, dim3(1), dim3(1024), 0, s, off, max_depth, head, nchunk);
+    hipLaunchKernelGGL(k_level_chunks, dim3(1), dim3(1024), 0, s, off, max_depth, kWave, head, nchunk);
     const dim3 g((n + 255) / 256);
     if (backward)
         hipLaunchKernelGGL(k_level_recs<true>, g, dim3(256), 0, s, n, off, depth, perm, rpF, diagF, rec);
@@ -98,16 +104,6 @@ hipError_t launch_level_sched(int32_t n, const int64_t* off, const int32_t* dept
 
 typedef __attribute__((address_space(3))) volatile double LdsDouble;
 typedef __attribute__((address_space(3))) volatile int32_t LdsInt;
-
-// head of chunk c, and the record of the calling lane's position in it (z =
-// -1: no position)
-__device__ __forceinline__ int4 chunk_head(const LevelSched& L, int32_t c) {
-    return c < L.nchunk ? L.head[c] : make_int4(0, 0, 0, 0);
-}
-__device__ __forceinline__ int4 chunk_rec(const LevelSched& L, const int4& h) {
-    const int32_t p = h.x + lane_id();
-    return p < h.y ? L.rec[p] : make_int4(0, 0, -1, -1);
-}
 
 // ----------------------------------------------------------------------------------
 // one compute unit, x in LDS

@@ -298,6 +298,7 @@ struct tpilu_pattern_s {
     int32_t* permU = nullptr;   // rows sorted by depthU: the ticket order of backward
     uint8_t *wcntL = nullptr, *wcntU = nullptr;  // entries of every row inside its window (k_solve_block.hip)
     BlockStats bst{};
+    NumericPlan nplan;          // Phase II by level chunks (k_numeric_level.hip)
     LevelSched lsL, lsU;        // the two level orders cut into chunks (k_solve_level.hip)
     Ctl* ctl = nullptr;
     // adjoint transposes (built on first use)
@@ -496,6 +497,14 @@ size_t numeric_wrow_bytes(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch) {
            sizeof(double);
 }
 
+// Phase II by the plan: the library's choice when nothing is asked for and
+// Phase I laid one down.  (In the LDS of one compute unit no row waits for a
+// published value, so the host-forced failure needs the other kernel.)
+bool numeric_by_plan(tpilu_ctx ctx, tpilu_pattern pat) {
+    return pat->nplan.plan && ctx->numeric == 0 && ctx->placement == 0 && !ctx->grid_override &&
+           !(pat->nplan.ucum && ctx->skip_row >= 0);
+}
+
 // wrow: numeric_wrow_bytes(ctx, pat, batch) bytes of device memory, or null
 // when that is 0.  b, x (batches only, both or neither): the forward
 // substitution x = L~^-1 b fused into the factorization.
@@ -532,9 +541,16 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
         // the timed region holds the pending-marker fill of F too: the
         // elimination cannot run without it
         TimedLaunch tl(ctx, TPILU_KERNEL_NUMERIC);
-        HIPCHK(ctx, launch_fill_pending_upper(f_val, (int32_t)pat->n, pat->rpF, pat->diagF, batch, ctl, true,
-                                              ctx->stream));
+        const bool by_plan = batch == 1 && numeric_by_plan(ctx, pat);
+        if (!(by_plan && pat->nplan.ucum))
+            HIPCHK(ctx, launch_fill_pending_upper(f_val, (int32_t)pat->n, pat->rpF, pat->diagF, batch, ctl, true,
+                                                  ctx->stream));
         if (x) HIPCHK(ctx, launch_fill_pending(x, pat->n * batch, ctl, false, ctx->stream));
+        if (by_plan) {
+            HIPCHK(ctx, launch_numeric_level(pdev(ctx, pat, RowKernel::Numeric, true), pat->lsL, pat->nplan, a_val, f_val,
+                                             ctx->fused, ctl, ctx->spin_limit, ctx->skip_row, ctx->stream));
+            return TPILU_OK;
+        }
         HIPCHK(ctx, launch_numeric(pdev(ctx, pat, RowKernel::Numeric, true), a_val, batch, f_val, ctl,
                                    ctx->spin_limit, ctx->skip_row, grid, pat->st.max_row, pat->st.max_lrow, flow,
                                    one_xcd, batch_global_row(ctx, pat, batch) ? wrow : nullptr, b, x,
@@ -762,6 +778,10 @@ struct LevelSpec {
     int4* head = nullptr;
     int32_t* nchunk = nullptr;  // host, set by finish_levels
     const uint8_t* wcnt = nullptr;  // window entries, when the levels go by blocks
+    // the same in parts of part_rows positions (null: not wanted), with room for n
+    int4* part = nullptr;
+    int32_t part_rows = 0;
+    int32_t* nparts = nullptr;  // host, set by finish_levels
 };
 
 // Enqueue the level computation on stream s without waiting for it: the
@@ -818,6 +838,8 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
         if (js[q].rec)
             HIPCHK(ctx, launch_level_sched(n, off, js[q].depth, dmax + 16 * q, js[q].perm, pat->rpF, pat->diagF, js[q].desc != 0,
                                            js[q].rec, js[q].head, dmax + 16 * q + 1, s));
+        if (js[q].part)
+            HIPCHK(ctx, launch_level_chunks(off, dmax + 16 * q, js[q].part_rows, js[q].part, dmax + 16 * q + 2, s));
     }
     return TPILU_OK;
 }
@@ -830,6 +852,7 @@ tpilu_status finish_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js
     for (int q = 0; q < njobs; ++q) {
         *js[q].max_depth = dm[16 * q];
         if (js[q].nchunk) *js[q].nchunk = dm[16 * q + 1];
+        if (js[q].nparts) *js[q].nparts = dm[16 * q + 2];
     }
     return read_ctl(ctx, pat, nullptr, false);
 }
@@ -894,6 +917,45 @@ tpilu_status build_inverse_sched(tpilu_ctx ctx, tpilu_pattern pat) {
     pat->n_inv_updates = total;
     pat->have_inv = true;
     return TPILU_OK;
+}
+
+// The plan of Phase II with several rows per wavefront.  Not laid down for
+// longer rows of few updates (general sparse matrices: random banded n=160,000
+// ILU(0), rows of up to 11, 0.07 updates per pivot, 1.14 ms by the plan against
+// 1.06); where there is no memory for it the other kernels do without.
+//
+// Where it runs, measured (us, one XCD with 128 / 256 wavefronts / the device
+// with 2,048), by parts per level: 17 (2-D 400^2 ILU(1)) 984 / 1031 / 1514; 25
+// (7-point 24^3 ILU(1)) 215 / 241 / 266; 42 (2-D 1000^2 ILU(1)) 3295 / 2970 /
+// 3860; 172 (7-point 64^3 ILU(0)) 778 / 554 / 366; 196 (27-point 50^3 ILU(1)) 8551
+// / 4775 / 2253.
+constexpr int64_t kPlanXcdNarrow = 32, kPlanXcdParts = 64;
+tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat, TmpBufs& T) {
+    NumericPlan& N = pat->nplan;
+    if (N.config < 0) return TPILU_OK;
+    hipStream_t s = ctx->stream;
+    const int32_t n = (int32_t)pat->n;
+    N.nnz_u = pat->nnz_f - (int64_t)pat->st.nnz_l;
+    const int64_t width = N.nparts / std::max<int64_t>(pat->depth_l, 1);
+    N.one_xcd = width <= kPlanXcdParts;
+    N.waves = !N.one_xcd ? 2048 : width <= kPlanXcdNarrow ? 128 : 256;
+    N.rec = (int4*)pat->take(sizeof(int4) * (size_t)n);
+    uint8_t* plan = N.rec ? (uint8_t*)pat->take(numeric_plan_bytes(N.config) * (size_t)n) : nullptr;
+    if (!plan) {
+        (void)hipGetLastError();
+        return TPILU_OK;
+    }
+    if (N.config <= 1 && N.nnz_u <= kLdsNumericU) {
+        int32_t* cnt = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);
+        int64_t* stmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(n));
+        N.ucum = (int64_t*)pat->take(sizeof(int64_t) * (size_t)(n + 1));
+        if (!cnt || !stmp || !N.ucum) return fail(ctx, TPILU_E_NOMEM, "numeric plan");
+        HIPCHK(ctx, launch_lower_count(n, pat->rpF, pat->diagF, cnt, s));
+        HIPCHK(ctx, launch_scan(cnt, n, N.ucum, stmp, s));
+    }
+    N.plan = plan;
+    HIPCHK(ctx, launch_numeric_plan(pat->dev(), pat->lsL, N, s));
+    return TPILU_OK;  // (the caller waits for the stream before it releases T)
 }
 
 // waits for the second stream when it goes out of scope (before the
@@ -1299,6 +1361,15 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         L.rec = ljobs[q].rec;
         L.head = ljobs[q].head;
     }
+    P->nplan.config = numeric_plan_config(P->st.max_row, P->st.max_lrow);
+    if (P->nplan.config >= 0) {
+        ljobs[0].part = P->nplan.part = (int4*)P->take(sizeof(int4) * (size_t)n);
+        if (!P->nplan.part) P->nplan.config = -1;
+    }
+    if (P->nplan.config >= 0) {
+        ljobs[0].part_rows = numeric_plan_rows(P->nplan.config);
+        ljobs[0].nparts = &P->nplan.nparts;
+    }
     if (levels_by_blocks(ctx, P)) {
         ljobs[0].wcnt = P->wcntL;
         ljobs[1].wcnt = P->wcntU;
@@ -1420,6 +1491,8 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         P->lsL.depth = P->depth_l;
         P->lsU.depth = P->depth_u;
     }
+    if (P->nplan.config >= 2 && nupd < nl_) P->nplan.config = -1;
+    if (tpilu_status ps = build_numeric_plan(ctx, P, T); ps != TPILU_OK) return bail(ps);
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);
     *out = P;
