@@ -73,7 +73,7 @@ __device__ __forceinline__ void unrolled(Fn&& f) {
 // (null: slots in F): entries of L~ before row i, a diagonal's place among the
 // entries of U~ being its slot minus those up to its row.
 template <int G, int KP>
-__global__ __launch_bounds__(64) void k_numeric_plan(PatDev P, LevelSched L, const int64_t* __restrict__ ucum,
+__global__ __launch_bounds__(64) void k_numeric_plan(PatDev P, LevelSched L, const int32_t* __restrict__ ucum,
                                                      uint8_t* __restrict__ plan, int4* __restrict__ rec) {
     constexpr int R = kWave / G;
     __shared__ uint8_t tab[R * KP * G];
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(64) void k_numeric_plan(PatDev P, LevelSched L, con
             int32_t place = 0;
             if (t < r.z) {
                 const int32_t dh = P.lsd[rs + t];
-                place = ucum ? dh - (int32_t)ucum[P.ciF[rs + t] + 1] : dh;
+                place = ucum ? dh - ucum[P.ciF[rs + t] + 1] : dh;
                 tab[(g * KP + t) * G + t] = 0;
                 for (int64_t e = P.sptr[rs + t]; e < P.sptr[rs + t + 1]; ++e)
                     tab[(g * KP + t) * G + (P.sp[e] - rs)] = (uint8_t)(P.sq[e] - dh);
@@ -281,11 +281,11 @@ __global__ __launch_bounds__(kLdsWaves * 64) void k_numeric_lds(PatDev P, Numeri
     int4 h = part(c), h1 = part(c + kLdsWaves), h2 = part(c + 2 * kLdsWaves);
     GroupRow<G, KP> x = group_load<G, KP>(N, h), x1 = group_load<G, KP>(N, h1);
     double a = group_a<G, KP>(x, a_val);
-    int32_t at = x.rs - (int32_t)N.ucum[x.j] - x.nl;  // place of the row's first entry of U~, minus its pivots
+    int32_t at = x.rs - N.ucum[x.j] - x.nl;  // place of the row's first entry of U~, minus its pivots
     while (c < N.nparts) {
         const GroupRow<G, KP> x2 = group_load<G, KP>(N, h2);
         const double a1 = group_a<G, KP>(x1, a_val);
-        const int32_t at1 = x1.rs - (int32_t)N.ucum[x1.j] - x1.nl;
+        const int32_t at1 = x1.rs - N.ucum[x1.j] - x1.nl;
         const int4 h3 = part(c + 3 * kLdsWaves);
         const bool mine = t < x.len;
         trace_mark_lane(P.trace, x.j, mine && t == 0);
@@ -338,15 +338,32 @@ int numeric_plan_config(int32_t max_row, int32_t max_lrow) {
 int numeric_plan_rows(int config) { return kWave / kConfigs[config].g; }
 size_t numeric_plan_bytes(int config) { return plan_bytes(kConfigs[config].g, kConfigs[config].kp); }
 
-__global__ void k_lower_count(int32_t n, const int64_t* __restrict__ rpF, const int32_t* __restrict__ diagF,
-                              int32_t* __restrict__ cnt) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) cnt[i] = diagF[i] - (int32_t)rpF[i];
+__global__ __launch_bounds__(1024) void k_lower_before(int32_t n, const int64_t* __restrict__ rpF,
+                                                       const int32_t* __restrict__ diagF,
+                                                       int32_t* __restrict__ before) {
+    __shared__ int32_t sh[1024];
+    const int tid = threadIdx.x;
+    int32_t base = 0;
+    for (int32_t i0 = 0; i0 < n; i0 += 1024) {
+        const int32_t i = i0 + tid, own = i < n ? diagF[i] - (int32_t)rpF[i] : 0;
+        sh[tid] = own;
+        __syncthreads();
+        for (int w = 1; w < 1024; w <<= 1) {
+            const int32_t v = tid >= w ? sh[tid - w] : 0;
+            __syncthreads();
+            sh[tid] += v;
+            __syncthreads();
+        }
+        if (i < n) before[i] = base + sh[tid] - own;
+        base += sh[1023];
+        __syncthreads();
+    }
+    if (tid == 0) before[n] = base;
 }
 
-hipError_t launch_lower_count(int32_t n, const int64_t* rpF, const int32_t* diagF, int32_t* cnt, hipStream_t s) {
+hipError_t launch_lower_before(int32_t n, const int64_t* rpF, const int32_t* diagF, int32_t* before, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lower_count, dim3((n + 255) / 256), dim3(256), 0, s, n, rpF, diagF, cnt);
+    hipLaunchKernelGGL(k_lower_before, dim3(1), dim3(1024), 0, s, n, rpF, diagF, before);
     return hipGetLastError();
 }
 

@@ -36,9 +36,14 @@ namespace tpilu {
 // off[l] .. off[l + 1]: positions of level l (0-based).  head[c] of chunk c =
 // (first position, end, first chunk of its level, 0); depth comes from device
 // memory, the chunk count goes there.
+// The second block does the same in parts of `rows` positions, when wanted.
 __global__ __launch_bounds__(1024) void k_level_chunks(const int64_t* __restrict__ off,
-                                                       const int32_t* __restrict__ depth, int32_t size,
-                                                       int4* __restrict__ head, int32_t* __restrict__ nchunk) {
+                                                       const int32_t* __restrict__ depth, int4* __restrict__ heads,
+                                                       int32_t* __restrict__ nheads, int32_t rows,
+                                                       int4* __restrict__ part, int32_t* __restrict__ nparts) {
+    const int32_t size = blockIdx.x ? rows : kWave;
+    int4* __restrict__ head = blockIdx.x ? part : heads;
+    int32_t* __restrict__ nchunk = blockIdx.x ? nparts : nheads;
     __shared__ int32_t sh[1024];
     const int tid = threadIdx.x;
     const int32_t levels = *depth;
@@ -83,17 +88,13 @@ __global__ void k_level_recs(int32_t n, const int64_t* __restrict__ off, const i
     rec[p] = make_int4(i, q, kBackward ? q - d : d - q, l >= kHintLevels ? perm[off[l - kHintLevels + 1] - 1] : -1);
 }
 
-hipError_t launch_level_chunks(const int64_t* off, const int32_t* max_depth, int32_t size, int4* head, int32_t* nchunk,
-                               hipStream_t s) {
-    hipLaunchKernelGGL(k_level_chunks, dim3(1), dim3(1024), 0, s, off, max_depth, size, head, nchunk);
-    return hipGetLastError();
-}
-
 hipError_t launch_level_sched(int32_t n, const int64_t* off, const int32_t* depth, const int32_t* max_depth,
                               const int32_t* perm, const int64_t* rpF, const int32_t* diagF, bool backward, int4* rec,
-                              int4* head, int32_t* nchunk, hipStream_t s) {
+                              int4* head, int32_t* nchunk, int32_t part_rows, int4* part, int32_t* nparts,
+                              hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_level_chunks, dim3(1), dim3(1024), 0, s, off, max_depth, kWave, head, nchunk);
+    hipLaunchKernelGGL(k_level_chunks, dim3(part ? 2 : 1), dim3(1024), 0, s, off, max_depth, head, nchunk, part_rows, part,
+                       nparts);
     const dim3 g((n + 255) / 256);
     if (backward)
         hipLaunchKernelGGL(k_level_recs<true>, g, dim3(256), 0, s, n, off, depth, perm, rpF, diagF, rec);

@@ -1217,9 +1217,10 @@ __global__ __launch_bounds__(64) void k_depth(int32_t n, LevelJob j0, LevelJob j
 
 // Lane per node: a ticket hands a wavefront 64 consecutive nodes (in the
 // sweep's order), so the whole graph can be in flight at once and wide
-// graphs are not throttled by the ticket.  A lane polls its first dependency
-// not known yet, and when that is there takes the next ones with kLaneBatch
-// loads in flight; dependencies on the wavefront's own nodes (the chains of a
+// graphs are not throttled by the ticket.  A lane looks at its first
+// kLaneBatch dependencies not known yet at a time, in whatever order they
+// become known (a maximum), so that little is left when the last one comes;
+// dependencies on the wavefront's own nodes (the chains of a
 // stencil's grid lines) go through LDS.  The wavefront keeps looping until
 // every lane published, so lanes that depend on other lanes of the same
 // wavefront cannot deadlock.  Bound by one hand-off per level and the polls
@@ -1248,6 +1249,11 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
         const int32_t first = J.desc ? n - 1 - (int32_t)t * kWave : (int32_t)t * kWave;  // lane 0's node
         int64_t q = 0, b = 0;
         if (valid) dep_range(J.G, i, q, b);
+        // the dependencies not known yet, 64 at a time
+        auto window = [&](int64_t from) {
+            return from >= b ? 0ull : b - from >= kWave ? ~0ull : (1ull << (b - from)) - 1ull;
+        };
+        uint64_t open = window(q);
         int32_t best = 0;
         bool done = !valid;
         lv[lane] = -1;
@@ -1263,29 +1269,35 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
         };
         for (;;) {
             bool prog = false;
-            int32_t v0 = -1;
-            if (!done) v0 = q < b ? level_of(ciF[q]) : 0;
-            if (v0 >= 0) {
-                prog = true;
-                best = max(best, v0);
-                if (q < b) ++q;
-                int32_t c[kLaneBatch], v[kLaneBatch];
-#pragma unroll
-                for (int u = 0; u < kLaneBatch; ++u) c[u] = q + u < b ? ciF[q + u] : first;
-#pragma unroll
-                for (int u = 0; u < kLaneBatch; ++u) v[u] = q + u < b ? level_of(c[u]) : -1;
-                bool go = true;
+            if (!done) {
+                // the first kLaneBatch dependencies not known yet, all loads in flight together
+                int32_t id[kLaneBatch], c[kLaneBatch], v[kLaneBatch];
+                uint64_t m = open;
 #pragma unroll
                 for (int u = 0; u < kLaneBatch; ++u) {
-                    go = go && v[u] >= 0;
-                    best = max(best, go ? v[u] : 0);
-                    q += go ? 1 : 0;
+                    id[u] = m ? __builtin_ctzll(m) : -1;
+                    m &= m - 1ull;
+                    c[u] = id[u] >= 0 ? ciF[q + id[u]] : first;
                 }
-                if (q >= b) {
-                    jitter((uint32_t)i);
-                    lv[lane] = best + 1;
-                    __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    done = true;
+#pragma unroll
+                for (int u = 0; u < kLaneBatch; ++u) v[u] = id[u] >= 0 ? level_of(c[u]) : -1;
+#pragma unroll
+                for (int u = 0; u < kLaneBatch; ++u)
+                    if (v[u] >= 0) {
+                        best = max(best, v[u]);
+                        open &= ~(1ull << id[u]);
+                        prog = true;
+                    }
+                if (open == 0ull) {
+                    q += kWave;
+                    open = window(q);
+                    prog = true;
+                    if (open == 0ull) {
+                        jitter((uint32_t)i);
+                        lv[lane] = best + 1;
+                        __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        done = true;
+                    }
                 }
             }
             const uint64_t left = __ballot(!done);
@@ -1298,8 +1310,9 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
             // nothing new: watch the first waiting lane's dependency alone for a
             // while, longer each time
             const int f = __builtin_ctzll(left);
-            const int32_t c = ciF[((int64_t)__builtin_amdgcn_readlane((int32_t)(q >> 32), f) << 32) |
-                                  (uint32_t)__builtin_amdgcn_readlane((int32_t)q, f)];
+            const int64_t qw = q + (open ? __builtin_ctzll(open) : 0);
+            const int32_t c = ciF[((int64_t)__builtin_amdgcn_readlane((int32_t)(qw >> 32), f) << 32) |
+                                  (uint32_t)__builtin_amdgcn_readlane((int32_t)qw, f)];
             if ((uint32_t)(J.desc ? first - c : c - first) >= (uint32_t)kWave) {
                 for (int w = min(4 << idle, kLaneWatch); w > 0 && uniform(ld_level(J.depth + c)) < 0; --w) {}
                 idle = min(idle + 1, 3);
@@ -1480,9 +1493,12 @@ __global__ __launch_bounds__(128) void k_depth_blocks(int32_t n, LevelJob j0, Le
 // scatter.  The order inside a level is whatever the atomics give; any
 // order that lists every level before the next is a valid schedule, and the
 // results never depend on it.
-__global__ void k_level_hist(int32_t n, const int32_t* __restrict__ depth, int32_t* hist) {
+__global__ void k_level_hist(int32_t n, const int32_t* __restrict__ depth, int32_t* hist, int32_t* most) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(&hist[depth[i] - 1], 1);
+    int32_t d = i < n ? depth[i] : 0;
+    if (i < n) atomicAdd(&hist[d - 1], 1);
+    for (int off = 32; off > 0; off >>= 1) d = max(d, __shfl_xor(d, off));
+    if (lane_id() == 0 && d > *(volatile int32_t*)most) atomicMax(most, d);
 }
 
 __global__ void k_level_scatter(int32_t n, const int32_t* __restrict__ depth,
@@ -1493,12 +1509,12 @@ __global__ void k_level_scatter(int32_t n, const int32_t* __restrict__ depth,
     perm[off[d] + atomicAdd(&cursor[d], 1)] = i;
 }
 
-hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth, int32_t* hist,
+hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth, int32_t* hist, int32_t* most,
                               int64_t* off, int64_t* scan_tmp, int32_t* perm, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipError_t e = launch_fill_i32(hist, 2 * (int64_t)max_depth, 0, s);
+    hipLaunchKernelGGL(k_level_hist, dim3((n + 255) / 256), dim3(256), 0, s, n, depth, hist, most);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_level_hist, dim3((n + 255) / 256), dim3(256), 0, s, n, depth, hist);
     e = launch_scan(hist, max_depth, off, scan_tmp, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_level_scatter, dim3((n + 255) / 256), dim3(256), 0, s, n, depth, off,
@@ -1537,22 +1553,6 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     int blocks = (int)std::min<int64_t>((n + 255) / 256, 16384);
     hipLaunchKernelGGL(k_fill_i32, dim3(blocks), dim3(256), 0, s, p, n, v);
-    return hipGetLastError();
-}
-
-__global__ void k_max_i32(const int32_t* __restrict__ p, int64_t n, int32_t* out) {
-    int32_t m = 0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        m = max(m, p[i]);
-    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
-    if (lane_id() == 0) atomicMax(out, m);
-}
-
-hipError_t launch_max_i32(const int32_t* p, int64_t n, int32_t* out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    int blocks = (int)std::min<int64_t>((n + 255) / 256, 64);  // an atomic per wavefront, on one address
-    hipLaunchKernelGGL(k_max_i32, dim3(blocks), dim3(256), 0, s, p, n, out);
     return hipGetLastError();
 }
 

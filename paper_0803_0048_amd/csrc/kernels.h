@@ -122,11 +122,10 @@ hipError_t launch_depth(int32_t n, const LevelJob& j0, const LevelJob* j1, Ctl* 
 hipError_t launch_depth_blocks(int32_t n, const LevelJob& j0, const LevelJob& j1, Ctl* ctl, uint64_t spin_limit,
                                int32_t grid, hipStream_t s);
 // perm = nodes sorted by level (counting sort); levels are 1 .. max_depth
-// (depth[i] >= 1); hist needs 2 * max_depth ints
-hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth, int32_t* hist,
+// (depth[i] >= 1); hist: 2 * max_depth zeros, most: a zero, the deepest level
+hipError_t launch_level_order(int32_t n, const int32_t* depth, int32_t max_depth, int32_t* hist, int32_t* most,
                               int64_t* off, int64_t* scan_tmp, int32_t* perm, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_max_i32(const int32_t* p, int64_t n, int32_t* out, hipStream_t s);
 
 // ---- numeric phase -------------------------------------------------------------
 struct PatDev {
@@ -221,10 +220,12 @@ __device__ __forceinline__ int4 chunk_rec(const LevelSched& L, const int4& h) {
     const int32_t p = h.x + lane_id();
     return p < h.y ? L.rec[p] : make_int4(0, 0, -1, -1);
 }
-// off: first position of every level (scan of the level sizes); *max_depth, *nchunk on the device
+// off: first position of every level (scan of the level sizes); *max_depth, *nchunk on the device;
+// part (nullable): the level order also in parts of part_rows positions
 hipError_t launch_level_sched(int32_t n, const int64_t* off, const int32_t* depth, const int32_t* max_depth,
                               const int32_t* perm, const int64_t* rpF, const int32_t* diagF, bool backward, int4* rec,
-                              int4* head, int32_t* nchunk, hipStream_t s);
+                              int4* head, int32_t* nchunk, int32_t part_rows, int4* part, int32_t* nparts,
+                              hipStream_t s);
 // ---- Phase II, several rows per wavefront, rows of up to 64 entries (k_numeric_level.hip)
 struct NumericPlan {
     int config = -1;
@@ -232,7 +233,7 @@ struct NumericPlan {
     int4* rec = nullptr;        // per position: row, first slot, pivots and length << 16, first entry of A
     int4* part = nullptr;       // the level order in parts of numeric_plan_rows(config) (as LevelSched::head)
     int32_t nparts = 0;
-    int64_t* ucum = nullptr;    // entries of L~ before row i, [n + 1]: U~ in the LDS of one compute unit
+    int32_t* ucum = nullptr;    // entries of L~ before row i, [n + 1]: U~ in the LDS of one compute unit
     int64_t nnz_u = 0;
     bool one_xcd = true;
     int32_t waves = 0;          // wavefronts (of the XCD)
@@ -241,14 +242,12 @@ constexpr int64_t kLdsNumericU = 19456;  // most entries of U~ in LDS (152 KB)
 int numeric_plan_config(int32_t max_row, int32_t max_lrow);  // -1: rows too long
 int numeric_plan_rows(int config);
 size_t numeric_plan_bytes(int config);
-hipError_t launch_lower_count(int32_t n, const int64_t* rpF, const int32_t* diagF, int32_t* cnt, hipStream_t s);
+// before[i] = entries of L~ in rows 0 .. i - 1, [n + 1] (one workgroup: small systems)
+hipError_t launch_lower_before(int32_t n, const int64_t* rpF, const int32_t* diagF, int32_t* before, hipStream_t s);
 hipError_t launch_numeric_plan(const PatDev& P, const LevelSched& L, const NumericPlan& N, hipStream_t s);
 hipError_t launch_numeric_level(const PatDev& P, const LevelSched& L, const NumericPlan& N, const double* a_val,
                                 double* f_val, bool fused, Ctl* ctl, uint64_t spin_limit, int64_t skip_row,
                                 hipStream_t s);
-// only the chunks, of `size` positions
-hipError_t launch_level_chunks(const int64_t* off, const int32_t* max_depth, int32_t size, int4* head, int32_t* nchunk,
-                               hipStream_t s);
 constexpr int32_t kLdsSolveRows = 16384;  // most rows of k_solve_lds (128 KB of LDS)
 constexpr int32_t kLdsSolveHalf = 16;     // most entries of a row half there
 // sweeps: 1 forward (x nullable), 2 backward (reads x), 3 both in one launch (x nullable)

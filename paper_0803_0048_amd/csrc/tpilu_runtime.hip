@@ -143,7 +143,9 @@ constexpr int64_t kNarrowWidth = 32;   // n / depth below this: narrow
 constexpr int64_t kXcdMaxAvg = 128;
 // wavefronts per CU that the LDS of a tier of the symbolic construction allows
 constexpr int32_t kSymWaves[] = {32, 12, 6, 2};
-constexpr int64_t kLevelLaneMax = 40;  // level computation: lane per node below this many dependencies
+// level computation: lane per node below this many dependencies (of a small
+// system, 27-point 20^3 ILU(1), Phase I 2.1 ms so and 1.9 by wavefronts, only below the fewer)
+constexpr int64_t kLevelLaneMax = 40, kLevelLaneShort = 14, kLevelLaneRows = 16384;
 constexpr int64_t kLevelWideMax = 60;  // wavefront per node: the wide window below this, else the narrow one
 constexpr int32_t kLevelWavesWide = 768;
 constexpr int32_t kLevelWavesNarrow = 192;
@@ -791,7 +793,9 @@ struct LevelSpec {
 tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js, int njobs, hipStream_t s,
                             TmpBufs& T, int32_t** dmax_out) {
     const int32_t n = (int32_t)pat->n;
-    int32_t* dmax = (int32_t*)T.get(sizeof(int32_t) * 32);
+    // the maxima and the histograms, zeroed together
+    const size_t zeros = 32 + (size_t)njobs * 2 * (size_t)std::max(n, 1);
+    int32_t* dmax = (int32_t*)T.get(sizeof(int32_t) * zeros);
     Ctl* ctl2 = (Ctl*)T.get(sizeof(Ctl));
     if (!dmax || !ctl2) return fail(ctx, TPILU_E_NOMEM, "levels");
     *dmax_out = dmax;
@@ -808,11 +812,13 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     // wavefronts, 32 at 768.
     const int64_t avg = deps / std::max<int64_t>(n, 1);
     const int32_t lane_waves = (int32_t)std::min<int64_t>(((int64_t)n + 63) / 64, 4096);
-    const int32_t grid = avg < kLevelLaneMax ? -lane_waves : (avg < kLevelWideMax ? kLevelWavesWide
+    const bool lanes = avg < kLevelLaneMax && (avg < kLevelLaneShort || n >= kLevelLaneRows);
+    const int32_t grid = lanes ? -lane_waves : (avg < kLevelWideMax ? kLevelWavesWide
                                                                                     : kLevelWavesNarrow);
     LevelJob jb[2];
+    const bool joined = njobs > 1 && js[1].depth == js[0].depth + n;
     for (int q = 0; q < njobs; ++q) {
-        HIPCHK(ctx, launch_fill_i32(js[q].depth, n, -1, s));
+        if (q == 0 || !joined) HIPCHK(ctx, launch_fill_i32(js[q].depth, joined ? 2 * (int64_t)n : n, -1, s));
         jb[q] = LevelJob{js[q].G, js[q].desc, js[q].depth, q == 0 ? pat->ctl : ctl2, js[q].wcnt};
     }
     HIPCHK(ctx, launch_fill_pending(nullptr, 0, pat->ctl, true, s));
@@ -827,25 +833,23 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
         HIPCHK(ctx, launch_depth_blocks(n, jb[0], jb[1], pat->ctl, ctx->spin_limit, kLevelBlockGroups, s));
     else
         HIPCHK(ctx, launch_depth(n, jb[0], njobs > 1 ? &jb[1] : nullptr, pat->ctl, ctx->spin_limit, grid, lv_xcd, s));
-    HIPCHK(ctx, launch_fill_i32(dmax, 32, 0, s));
+    HIPCHK(ctx, launch_fill_i32(dmax, (int64_t)zeros, 0, s));
     for (int q = 0; q < njobs; ++q) {
-        HIPCHK(ctx, launch_max_i32(js[q].depth, n, dmax + 16 * q, s));
-        int32_t* hist = (int32_t*)T.get(sizeof(int32_t) * 2 * (size_t)std::max(n, 1));
+        int32_t* hist = dmax + 32 + (size_t)q * 2 * (size_t)std::max(n, 1);
         int64_t* off = (int64_t*)T.get(sizeof(int64_t) * ((size_t)n + 1));
         int64_t* stmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(std::max(n, 1)));
-        if (!hist || !off || !stmp) return fail(ctx, TPILU_E_NOMEM, "level order");
-        HIPCHK(ctx, launch_level_order(n, js[q].depth, std::max(n, 1), hist, off, stmp, js[q].perm, s));
+        if (!off || !stmp) return fail(ctx, TPILU_E_NOMEM, "level order");
+        HIPCHK(ctx, launch_level_order(n, js[q].depth, std::max(n, 1), hist, dmax + 16 * q, off, stmp, js[q].perm, s));
         if (js[q].rec)
             HIPCHK(ctx, launch_level_sched(n, off, js[q].depth, dmax + 16 * q, js[q].perm, pat->rpF, pat->diagF, js[q].desc != 0,
-                                           js[q].rec, js[q].head, dmax + 16 * q + 1, s));
-        if (js[q].part)
-            HIPCHK(ctx, launch_level_chunks(off, dmax + 16 * q, js[q].part_rows, js[q].part, dmax + 16 * q + 2, s));
+                                           js[q].rec, js[q].head, dmax + 16 * q + 1, js[q].part_rows, js[q].part, dmax + 16 * q + 2,
+                                           s));
     }
     return TPILU_OK;
 }
 
-// After the level work has completed: the maxima to the host, and the
-// watchdog / abort status of the level kernels.
+// After the level work has completed: the maxima to the host.  (The caller
+// reads the watchdog's status.)
 tpilu_status finish_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js, int njobs, const int32_t* dmax) {
     int32_t dm[32] = {0};
     HIPCHK(ctx, hipMemcpy(dm, dmax, sizeof(dm), hipMemcpyDeviceToHost));
@@ -854,7 +858,7 @@ tpilu_status finish_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js
         if (js[q].nchunk) *js[q].nchunk = dm[16 * q + 1];
         if (js[q].nparts) *js[q].nparts = dm[16 * q + 2];
     }
-    return read_ctl(ctx, pat, nullptr, false);
+    return TPILU_OK;
 }
 
 tpilu_status compute_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js, int njobs) {
@@ -863,7 +867,8 @@ tpilu_status compute_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     tpilu_status st = enqueue_levels(ctx, pat, js, njobs, ctx->stream, T, &dmax);
     if (st != TPILU_OK) return st;
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    return finish_levels(ctx, pat, js, njobs, dmax);
+    st = finish_levels(ctx, pat, js, njobs, dmax);
+    return st != TPILU_OK ? st : read_ctl(ctx, pat, nullptr, false);
 }
 
 // Shape of the two products (kProd*): as the solver mode asks (1 a wavefront
@@ -930,7 +935,7 @@ tpilu_status build_inverse_sched(tpilu_ctx ctx, tpilu_pattern pat) {
 // 3860; 172 (7-point 64^3 ILU(0)) 778 / 554 / 366; 196 (27-point 50^3 ILU(1)) 8551
 // / 4775 / 2253.
 constexpr int64_t kPlanXcdNarrow = 32, kPlanXcdParts = 64;
-tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat, TmpBufs& T) {
+tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     NumericPlan& N = pat->nplan;
     if (N.config < 0) return TPILU_OK;
     hipStream_t s = ctx->stream;
@@ -946,16 +951,13 @@ tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat, TmpBufs& T) {
         return TPILU_OK;
     }
     if (N.config <= 1 && N.nnz_u <= kLdsNumericU) {
-        int32_t* cnt = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);
-        int64_t* stmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(n));
-        N.ucum = (int64_t*)pat->take(sizeof(int64_t) * (size_t)(n + 1));
-        if (!cnt || !stmp || !N.ucum) return fail(ctx, TPILU_E_NOMEM, "numeric plan");
-        HIPCHK(ctx, launch_lower_count(n, pat->rpF, pat->diagF, cnt, s));
-        HIPCHK(ctx, launch_scan(cnt, n, N.ucum, stmp, s));
+        N.ucum = (int32_t*)pat->take(sizeof(int32_t) * (size_t)(n + 1));
+        if (!N.ucum) return fail(ctx, TPILU_E_NOMEM, "numeric plan");
+        HIPCHK(ctx, launch_lower_before(n, pat->rpF, pat->diagF, N.ucum, s));
     }
     N.plan = plan;
     HIPCHK(ctx, launch_numeric_plan(pat->dev(), pat->lsL, N, s));
-    return TPILU_OK;  // (the caller waits for the stream before it releases T)
+    return TPILU_OK;
 }
 
 // waits for the second stream when it goes out of scope (before the
@@ -1320,35 +1322,35 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
                                     gcap, grid, s));
     }
     // A -> F map
-    HIPCHK(ctx, launch_fill_i32((int32_t*)vstat, 16, 0, s));
-    HIPCHK(ctx, launch_a2f(ni, P->rpA, P->ciA, P->rpF, P->ciF, P->a2f, vstat, s));
-    // statistics
-    PatStats* dst = (PatStats*)T.get(sizeof(PatStats));
-    if (!dst) return bail(fail(ctx, TPILU_E_NOMEM, "stats"));
-    {
-        PatStats z{};
-        HIPCHK(ctx, hipMemcpyAsync(dst, &z, sizeof(z), hipMemcpyHostToDevice, s));
-    }
-    HIPCHK(ctx, launch_stats(ni, P->rpF, P->diagF, dst, s));
+    // statistics and the block windows, read back in one copy
+    struct Facts {
+        PatStats st;
+        BlockStats bst;
+        uint32_t missing, pad;
+    };
+    Facts* facts = (Facts*)T.get(sizeof(Facts));
     P->wcntL = (uint8_t*)P->take((size_t)n * 2);
-    BlockStats* bdst = (BlockStats*)T.get(sizeof(BlockStats));
-    if (!P->wcntL || !bdst) return bail(fail(ctx, TPILU_E_NOMEM, "block windows"));
+    if (!facts || !P->wcntL) return bail(fail(ctx, TPILU_E_NOMEM, "stats"));
     P->wcntU = P->wcntL + n;
-    HIPCHK(ctx, launch_fill_i32((int32_t*)bdst, sizeof(BlockStats) / 4, 0, s));
-    HIPCHK(ctx, launch_block_stats(ni, P->rpF, P->ciF, P->diagF, P->wcntL, P->wcntU, bdst, s));
-    HIPCHK(ctx, hipMemcpyAsync(&P->bst, bdst, sizeof(BlockStats), hipMemcpyDeviceToHost, s));
-    HIPCHK(ctx, hipMemcpyAsync(&P->st, dst, sizeof(PatStats), hipMemcpyDeviceToHost, s));
-    HIPCHK(ctx, hipMemcpyAsync(&vs, vstat, sizeof(vs), hipMemcpyDeviceToHost, s));
+    HIPCHK(ctx, launch_fill_i32((int32_t*)facts, sizeof(Facts) / 4, 0, s));
+    HIPCHK(ctx, launch_a2f(ni, P->rpA, P->ciA, P->rpF, P->ciF, P->a2f, &facts->missing, s));
+    HIPCHK(ctx, launch_stats(ni, P->rpF, P->diagF, &facts->st, s));
+    HIPCHK(ctx, launch_block_stats(ni, P->rpF, P->ciF, P->diagF, P->wcntL, P->wcntU, &facts->bst, s));
+    Facts hf{};
+    HIPCHK(ctx, hipMemcpyAsync(&hf, facts, sizeof(Facts), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
+    P->st = hf.st;
+    P->bst = hf.bst;
+    vs = hf.missing;
     if (vs) return bail(fail(ctx, TPILU_E_INVAL, "internal: an entry of A is missing from F"));
     // ---- dependency levels and the level-ordered schedules, on the second
     // stream: a latency-bound chain on a few wavefronts, overlapped with the
     // throughput-bound update schedules below
-    P->depthL = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
-    P->depthU = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
+    P->depthL = (int32_t*)P->take(sizeof(int32_t) * (size_t)n * 2);
+    P->depthU = P->depthL + n;
     P->permL = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
     P->permU = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
-    if (!P->depthL || !P->depthU || !P->permL || !P->permU) return bail(fail(ctx, TPILU_E_NOMEM, "levels"));
+    if (!P->depthL || !P->permL || !P->permU) return bail(fail(ctx, TPILU_E_NOMEM, "levels"));
     const int64_t nl_ = (int64_t)P->st.nnz_l, nu_ = nnzf - nl_ - n;
     LevelSpec ljobs[2] = {{DepGraph{P->rpF, P->ciF, P->diagF, 0}, 0, nl_, P->depthL, P->permL, &P->depth_l},
                           {DepGraph{P->rpF, P->ciF, P->diagF, 1}, 1, nu_, P->depthU, P->permU, &P->depth_u}};
@@ -1492,7 +1494,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         P->lsU.depth = P->depth_u;
     }
     if (P->nplan.config >= 2 && nupd < nl_) P->nplan.config = -1;
-    if (tpilu_status ps = build_numeric_plan(ctx, P, T); ps != TPILU_OK) return bail(ps);
+    if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return bail(ps);
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);
     *out = P;
