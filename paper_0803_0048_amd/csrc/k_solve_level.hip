@@ -21,7 +21,7 @@
 //                   its L2 (see Scope::Xcd), for rows of at most 16 entries:
 //                   0.45 us a level for up to 4 entries, 0.6 for 8, 0.97 for
 //                   16 (2-D 400 x 400 ILU(1), both sweeps: 5.00 -> 1.16 ms;
-//                   7-point 64^3 ILU(1): 1.78 -> 0.77 ms, ILU(2): 5.05 -> 1.65
+//                   7-point 64^3 ILU(1): 1.78 -> 0.70 ms, ILU(2): 5.05 -> 1.65
 //                   ms).  The former kernel for this shape polled across XCDs and
 //                   kept every lane at an entry of its own.
 // The order of every row's subtractions is that of k_solve.hip: forward
@@ -224,10 +224,11 @@ hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& U
 // ----------------------------------------------------------------------------------
 // one XCD, values handed over through its L2
 // ----------------------------------------------------------------------------------
-// Chunks are drawn in order from one counter, one chunk ahead of the one in
-// work (its records are loaded meanwhile).  Deadlock-free: a wavefront works
-// on the earlier of the two chunks it holds, so the smallest unfinished chunk
-// is always in work, and it only waits on smaller ones.
+// Chunks are drawn in order from one counter, the next when the last is done: a
+// chunk drawn ahead waits behind its wavefront's own and starts late (7-point
+// 64^3 ILU(1), both sweeps, 0.84 ms so, 0.70 here; with 63 chunks a level, 110^3
+// ILU(0), 1.18 and 1.28).  Deadlock-free: the smallest unfinished chunk is
+// always in work, and it only waits on smaller ones.
 // KE: entries of a row whose loads are in flight together.  The smallest that
 // holds a whole row half is the fastest (7-point 64^3 ILU(1), 6 entries: 0.77
 // ms with 8, 1.06 with 4, 0.96 with 16).
@@ -238,22 +239,12 @@ __global__ __launch_bounds__(64) void k_solve_chunks(LevelSched L, const double*
                                                      unsigned long long* trace, int64_t tr0, int32_t n) {
     if (!xcd_member(ctl)) return;
     const int lane = lane_id();
-    auto draw = [&]() {
-        uint32_t t = 0, z;
-        asm volatile("v_mov_b32 %0, 0" : "=v"(z));  // a per-lane address: the atomic's result is not waited for here
-        __builtin_amdgcn_wave_barrier();
-        if (lane == 0) t = atomicAdd(&ctl->part[0] + z, 1u);
-        __builtin_amdgcn_wave_barrier();
-        return t;
-    };
-    auto chunk = [&](uint32_t t) { return (int32_t)min((uint32_t)__builtin_amdgcn_readfirstlane(t), (uint32_t)L.nchunk); };
-    int32_t c = chunk(draw());
-    int4 r = chunk_rec(L, chunk_head(L, c));
-    uint32_t ahead = draw();
-    while (c < L.nchunk) {
-        const int32_t c2 = chunk(ahead);
-        const int4 r2 = chunk_rec(L, chunk_head(L, c2));
-        ahead = draw();
+    for (;;) {
+        int32_t c = 0;
+        if (lane == 0) c = (int32_t)atomicAdd(&ctl->part[0], 1u);
+        c = uniform(c);
+        if (c >= L.nchunk) break;
+        const int4 r = chunk_rec(L, chunk_head(L, c));
         const bool act = r.z >= 0;
         trace_mark_lane(trace, tr0 + r.x, act);
         double s = 0.0, fii = 1.0;
@@ -303,8 +294,6 @@ __global__ __launch_bounds__(64) void k_solve_chunks(LevelSched L, const double*
         } while (__any(k0 < r.z));
         if (act) st_final<Scope::Xcd>(out + r.x, stop ? as_f64(kQNaN) : kBackward ? s / fii : s);
         trace_mark_lane(trace, tr0 + n + r.x, act);
-        c = c2;
-        r = r2;
     }
 }
 

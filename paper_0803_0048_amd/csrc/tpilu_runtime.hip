@@ -647,9 +647,10 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
                                      : std::max(blocks * kBlockNs + rounds2 * kBlockRoundNs / 2,
                                                 (int64_t)((double)half * kBlockEntryNs));
         if (t_blocks < t_row && t_blocks <= t_chunks) return {kBlockGroups, true, SolveKind::Blocks};
-        // chunks in work at a time: the ones of about eight levels (7-point 64^3
-        // ILU(1), 11 chunks a level: 24 / 48 / 96 wavefronts 0.91 / 0.84 / 0.77 ms;
-        // ILU(2), 6 a level: 1.65 / 1.69 / 1.73 ms)
+        // chunks in work at a time: the ones of about eight levels (both sweeps,
+        // 24 / 48 / 96 / 192 wavefronts: 7-point 64^3 ILU(0), 21 chunks a level, 0.64 /
+        // 0.43 / 0.36 / 0.44 ms; ILU(1), 11: 0.85 / 0.70 / 0.70 / 0.84; 2-D 400^2
+        // ILU(1), 2: 1.12 / 1.15 / 1.17 / 1.33)
         if (t_chunks < t_row)
             return {(int32_t)std::min<int64_t>(96, std::max<int64_t>(24, 8 * (width / 64))), true, SolveKind::Chunks};
     }
