@@ -241,15 +241,16 @@ __device__ __forceinline__ uint32_t wave_ticket(Ctl* ctl) {
 struct PosRun {
     uint32_t next = 0, end = 0;
 };
+// (of `waves` wavefronts, this one `who`; counters from `base` on)
 __device__ __forceinline__ bool next_pos(Ctl* ctl, uint32_t n, uint32_t group, uint32_t parts, PosRun& r,
-                                         uint32_t& pos) {
+                                         uint32_t& pos, uint32_t who, uint32_t waves, uint32_t base) {
     if (r.next == r.end) {
         __shared__ uint32_t s_ticket;
-        if (parts > gridDim.x) parts = gridDim.x;
+        if (parts > waves) parts = waves;
         if (parts == 0) parts = 1;
-        const uint32_t x = blockIdx.x % parts;
+        const uint32_t x = who % parts;
         __syncthreads();
-        if (lane_id() == 0) s_ticket = atomicAdd(&ctl->part[x * kTicketStride], 1u);
+        if (lane_id() == 0) s_ticket = atomicAdd(&ctl->part[(base + x) * kTicketStride], 1u);
         __syncthreads();
         const uint64_t v = __builtin_amdgcn_readfirstlane(s_ticket);
         const uint64_t first = (v * parts + x) * group;
@@ -259,6 +260,11 @@ __device__ __forceinline__ bool next_pos(Ctl* ctl, uint32_t n, uint32_t group, u
     }
     pos = r.next++;
     return true;
+}
+
+__device__ __forceinline__ bool next_pos(Ctl* ctl, uint32_t n, uint32_t group, uint32_t parts, PosRun& r,
+                                         uint32_t& pos) {
+    return next_pos(ctl, n, group, parts, r, pos, blockIdx.x, gridDim.x, 0u);
 }
 
 __device__ __forceinline__ int64_t bcast_i64(int64_t v, int src) {

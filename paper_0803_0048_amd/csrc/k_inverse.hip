@@ -110,15 +110,19 @@ hipError_t launch_isched(int32_t n, const int64_t* rpF, const int32_t* ciF, cons
 constexpr int kInvChunk = 2;
 
 template <bool kUpper>
-__global__ __launch_bounds__(64) void k_inverse(PatDev P, InvSched S, const double* __restrict__ F, double* G,
-                                                Ctl* ctl, uint64_t spin_limit) {
+__device__ __forceinline__ void inverse_rows(const PatDev& P, const InvSched& S, const double* __restrict__ F,
+                                             double* G, Ctl* ctl, uint64_t spin_limit) {
     const int lane = lane_id();
     const int32_t n = P.n;
     const int32_t* perm = kUpper ? P.permU : P.permL;
     PosRun run;
     for (;;) {
         uint32_t tk;
-        if (!next_pos(ctl, (uint32_t)n, (uint32_t)(kUpper ? P.groupU : P.groupL), (uint32_t)P.parts, run, tk)) break;
+        // half the counters each
+        const uint32_t half = (uint32_t)(P.parts > 1 ? P.parts / 2 : 1);
+        if (!next_pos(ctl, (uint32_t)n, (uint32_t)(kUpper ? P.groupU : P.groupL), half, run, tk, blockIdx.x / 2,
+                      gridDim.x / 2, kUpper ? (uint32_t)kTicketParts / 2 : 0u))
+            break;
         const int32_t i = perm ? perm[tk] : (kUpper ? n - 1 - (int32_t)tk : (int32_t)tk);
         const int64_t rs = P.rpF[i], dj = P.diagF[i];
         const int64_t p0 = kUpper ? dj : rs, p1 = kUpper ? P.rpF[i + 1] : dj;
@@ -211,13 +215,20 @@ __global__ __launch_bounds__(64) void k_inverse(PatDev P, InvSched S, const doub
     }
 }
 
-hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_val, double* g_val, bool upper,
-                          Ctl* ctl, uint64_t spin_limit, int32_t grid, hipStream_t s) {
+// Both inverses in one launch, alternate wavefronts taking rows of either: the
+// two chains of dependencies are independent and each leaves the device mostly
+// waiting (random banded n=160,000 ILU(2): 3.8 and 2.3 ms one after the other,
+// 4.15 here).
+__global__ __launch_bounds__(64) void k_inverse(PatDev P, InvSched S, const double* __restrict__ F, double* G,
+                                                Ctl* ctl, uint64_t spin_limit) {
+    if (blockIdx.x & 1) inverse_rows<true>(P, S, F, G, ctl, spin_limit);
+    else inverse_rows<false>(P, S, F, G, ctl, spin_limit);
+}
+
+hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_val, double* g_val, Ctl* ctl,
+                          uint64_t spin_limit, int32_t grid, hipStream_t s) {
     if (P.n <= 0) return hipSuccess;
-    if (upper)
-        hipLaunchKernelGGL(k_inverse<true>, dim3(grid), dim3(64), 0, s, P, S, f_val, g_val, ctl, spin_limit);
-    else
-        hipLaunchKernelGGL(k_inverse<false>, dim3(grid), dim3(64), 0, s, P, S, f_val, g_val, ctl, spin_limit);
+    hipLaunchKernelGGL(k_inverse, dim3(2 * grid), dim3(64), 0, s, P, S, f_val, g_val, ctl, spin_limit);
     return hipGetLastError();
 }
 

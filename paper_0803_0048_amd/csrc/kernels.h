@@ -394,8 +394,8 @@ hipError_t launch_isched(int32_t n, const int64_t* rpF, const int32_t* ciF, cons
                          int32_t max_row, hipStream_t s);
 size_t isched_lds_bytes(int32_t max_row);
 // one half of G from F (G pre-filled with kPending; ctl ticket reset)
-hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_val, double* g_val, bool upper,
-                          Ctl* ctl, uint64_t spin_limit, int32_t grid, hipStream_t s);
+hipError_t launch_inverse(const PatDev& P, const InvSched& S, const double* f_val, double* g_val, Ctl* ctl,
+                          uint64_t spin_limit, int32_t grid, hipStream_t s);  // grid wavefronts per inverse
 // x = L~~^-1 b, y = U~~^-1 x; thread_rows: one thread per row, else a wavefront
 // shapes of the two products of the incomplete inverses
 // (entries per row and round: kProdTile 32, kProdTileMid 16, kProdTileShort 8)

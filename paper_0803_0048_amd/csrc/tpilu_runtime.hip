@@ -130,7 +130,13 @@ constexpr int64_t kFlowMaxChain = 12;
 constexpr int64_t kFlowMaxWidth = 64;
 constexpr int32_t kAdjointWaves = 512;
 constexpr int32_t kAdjointBatchWaves = 1024;  // batched reverse elimination (3-D 7-point 32^3 x16: 1.9 ms, 2.2 at 512)
-constexpr int32_t kInverseWaves = 1024;  // incomplete inverses (n=160,000 ILU(2): 7.0 ms, 8.3 at 512)
+// wavefronts per incomplete inverse, more for shorter rows, whose polls are
+// fewer (512 / 1024 / 2048 / 4096, ms: random banded n=160,000 ILU(2), 164 entries
+// a row, 4.10 / 4.15 / 4.61 / 34; 27-point 50^3 ILU(1), 59: 4.13 / 2.64 / 1.81 /
+// 1.84; 2-D 400^2 ILU(1), 7: 1.26 / 0.87 / 0.67 / 0.64; 7-point 64^3 ILU(1), 13: 2.67
+// / 2.10 / 2.18 / 13)
+constexpr int32_t kInverseWaves = 1024, kInverseWavesWide = 2048;
+constexpr int64_t kInverseWideAvg = 80;
 constexpr int64_t kNarrowWidth = 32;   // n / depth below this: narrow
 // Wavefront-per-row solves run on one XCD, where the hand-offs stay in that
 // XCD's L2, when the device-wide shape would take at most 256 wavefronts (a
@@ -1647,12 +1653,12 @@ extern "C" TPILU_API tpilu_status tpilu_inverse(tpilu_ctx ctx, tpilu_pattern pat
     if (st) return st;
     hipStream_t s = ctx->stream;
     const InvSched S{pat->iptr, pat->is_s, pat->is_q};
-    const int grid = ctx->grid_override ? ctx->grid_override : kInverseWaves;
+    const int grid = ctx->grid_override                           ? ctx->grid_override
+                     : pat->nnz_f <= kInverseWideAvg * pat->n ? kInverseWavesWide
+                                                              : kInverseWaves;
     const PatDev P = pdev(ctx, pat, RowKernel::Inverse);
     HIPCHK(ctx, launch_fill_pending(g_val, pat->nnz_f, pat->ctl, true, s));
-    HIPCHK(ctx, launch_inverse(P, S, f_val, g_val, false, pat->ctl, ctx->spin_limit, grid, s));
-    HIPCHK(ctx, launch_fill_pending(nullptr, 0, pat->ctl, false, s));
-    HIPCHK(ctx, launch_inverse(P, S, f_val, g_val, true, pat->ctl, ctx->spin_limit, grid, s));
+    HIPCHK(ctx, launch_inverse(P, S, f_val, g_val, pat->ctl, ctx->spin_limit, grid, s));
     return read_ctl(ctx, pat, nullptr, false);
 }
 
