@@ -252,6 +252,172 @@ __global__ __launch_bounds__(64) void k_numeric_group(PatDev P, LevelSched L, Nu
     }
 }
 
+// Batches of patterns of short rows: lanes are instances (as in
+// k_numeric_batch), a wavefront's row in registers, KW entries and KP pivots at
+// most, and everything about the row scalar: its plan (laid out for G lanes and
+// GK pivots), so that an absent update costs a scalar test.  Waits go pivot by
+// pivot.  The fused forward substitution (bvec, xout) is k_numeric_batch's.
+// Bound by the hand-off across the device and the scalar tests and pivots after
+// the last value to arrive.  Factorization alone, k_numeric_batch -> here (ms):
+// 2-D 128^2 ILU(2) x 256 1.23 -> 0.96, x 1024 2.20 -> 1.73, ILU(0) x 256 0.69 ->
+// 0.48, ILU(1) x 64 0.81 -> 0.57, 7-point 32^3 ILU(1) x 16 0.76 -> 0.72.  (One XCD
+// per team of instance groups gained nothing: the same 0.98 at x 256.)
+template <int KP, int KW, int G, int GK, bool kFused>
+__global__ __launch_bounds__(64) void k_numeric_batch_plan(PatDev P, NumericPlan N, const double* __restrict__ a_val,
+                                                           int32_t B, double* F, Ctl* ctl, uint64_t limit,
+                                                           int64_t skip_row, const double* __restrict__ bvec,
+                                                           double* xout) {
+    const int lane = lane_id();
+    const int32_t groups = (B + kWave - 1) / kWave;
+    const uint32_t ntask = (uint32_t)P.n * (uint32_t)groups;
+    PosRun run;
+    uint32_t task;
+    while (next_pos(ctl, ntask, 1u, (uint32_t)P.parts, run, task)) {
+        const int32_t pos = (int32_t)(task / (uint32_t)groups), g = (int32_t)(task % (uint32_t)groups);
+        const bool act = g * kWave + lane < B;
+        // this instance's byte in a line of B values (in bounds for inactive lanes too)
+        const uint32_t own = (uint32_t)(act ? g * kWave + lane : B - 1) << 3;
+        auto line = [&](const double* base, int32_t slot) {  // scalar base, 32-bit lane offset
+            return reinterpret_cast<const double*>(reinterpret_cast<const char*>(base + (int64_t)slot * B) + own);
+        };
+        const int4 r = N.rec[pos];
+        const int32_t j = uniform(r.x), rs = uniform(r.y), nl = uniform(r.z) & 0xffff, len = uniform(r.z) >> 16,
+                      a0 = uniform(r.w);
+        const uint32_t* pl = reinterpret_cast<const uint32_t*>(N.plan + (int64_t)pos * plan_bytes(G, GK));
+        uint32_t rel[KP / 4 * KW], at[KW / 4];
+        int32_t dh[KP];
+        unrolled<KP / 4 * KW>([&](auto xc) {
+            constexpr int x = decltype(xc)::value;
+            rel[x] = (uint32_t)uniform((int32_t)pl[x / KW * G + x % KW]);
+        });
+        unrolled<KW / 4>([&](auto xc) {
+            constexpr int x = decltype(xc)::value;
+            at[x] = (uint32_t)uniform((int32_t)pl[G * (GK + 4) / 4 + x]);
+        });
+        unrolled<KP>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            dh[k] = k < nl ? uniform(P.lsd[rs + k]) : 0;
+        });
+        auto byte = [&](auto kc, auto tc) {
+            constexpr int k = decltype(kc)::value, t = decltype(tc)::value;
+            return (rel[k / 4 * KW + t] >> (8 * (k & 3))) & 255u;
+        };
+        uint32_t has[KP];  // entries that pivot k updates
+        unrolled<KP>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            has[k] = 0u;
+            unrolled<KW>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if constexpr (t > k) has[k] |= byte(kc, tc) != kNone ? 1u << t : 0u;
+            });
+        });
+        double w[KW];
+        unrolled<KW>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            const uint32_t x = (at[t / 4] >> (8 * (t & 3))) & 255u;
+            w[t] = 0.0;
+            if (x != kNone) w[t] = *line(a_val, a0 + (int32_t)x);
+        });
+        uint64_t u[KP], v[KP * KW];  // (place k * KW + t; those of t <= k are never used)
+        auto fetch = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            u[k] = ld_coherent(line(F, dh[k]));
+            unrolled<KW>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if constexpr (t > k)
+                    if (has[k] >> t & 1u) v[k * KW + t] = ld_coherent(line(F, dh[k] + (int32_t)byte(kc, tc)));
+            });
+        };
+        unrolled<KP>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            unrolled<KW>([&](auto tc) { v[k * KW + decltype(tc)::value] = 0ull; });
+            if (k < nl) fetch(kc);
+        });
+        unrolled<KW>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            w[t] = sanitize_input(w[t], ctl);
+        });
+        bool stop = false;
+        unrolled<KP>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if (k >= nl) return;
+            uint32_t polls = 0;
+            uint64_t t0 = 0;
+            for (;;) {
+                bool pend = u[k] == kPending;
+                unrolled<KW>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    if constexpr (t > k) pend |= v[k * KW + t] == kPending;
+                });
+                if (!__any(pend)) break;
+                if (stop || wait_expired(polls, t0, ctl, limit)) {
+                    stop = true;
+                    if (u[k] == kPending) u[k] = kQNaN;
+                    unrolled<KW>([&](auto tc) {
+                        constexpr int t = decltype(tc)::value;
+                        if (v[k * KW + t] == kPending) v[k * KW + t] = kQNaN;
+                    });
+                    break;
+                }
+                fetch(kc);
+                if constexpr (k + 1 < KP)
+                    if (k + 1 < nl) fetch(std::integral_constant<int, k + 1>{});
+            }
+            const double l = w[k] / as_f64(u[k]);
+            unrolled<KW>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if constexpr (t > k)
+                    if (has[k] >> t & 1u) w[t] = ikj_update<kFused>(w[t], l, as_f64(v[k * KW + t]));
+            });
+            w[k] = l;
+        });
+        if (act && (int64_t)j != skip_row) {
+            // the U part first: other rows wait on it
+            unrolled<KW>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t >= nl && t < len) st_publish(const_cast<double*>(line(F, rs + t)), w[t]);
+            });
+            unrolled<KP>([&](auto tc) {
+                constexpr int t = decltype(tc)::value;
+                if (t < nl) *const_cast<double*>(line(F, rs + t)) = w[t];
+            });
+        }
+        bool zero = false;
+        unrolled<KP + 1>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            zero |= (t == nl) & (w[t] == 0.0);
+        });
+        if (act && zero) atomicMin(&ctl->bad_row, (unsigned long long)j);
+        if (xout) {
+            double sx = sanitize_input(*line(bvec, j), ctl);
+            uint64_t xv[KP];
+            int32_t h[KP];
+            unrolled<KP>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                if (k >= nl) return;
+                h[k] = uniform(P.ciF[rs + k]);
+                xv[k] = ld_coherent(line(xout, h[k]));
+            });
+            unrolled<KP>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                if (k >= nl) return;
+                uint32_t polls = 0;
+                uint64_t t0 = 0;
+                while (__any(xv[k] == kPending)) {
+                    if (stop || wait_expired(polls, t0, ctl, limit)) {
+                        stop = true;
+                        if (xv[k] == kPending) xv[k] = kQNaN;
+                        break;
+                    }
+                    xv[k] = ld_coherent(line(xout, h[k]));
+                }
+                sx = sx - w[k] * as_f64(xv[k]);
+            });
+            if (act && (int64_t)j != skip_row) st_publish(const_cast<double*>(line(xout, j)), sx);
+        }
+    }
+}
+
 typedef __attribute__((address_space(3))) volatile double LdsDouble;
 typedef __attribute__((address_space(3))) volatile int32_t LdsInt;
 constexpr int kLdsWaves = 16;
@@ -378,6 +544,25 @@ hipError_t launch_numeric_plan(const PatDev& P, const LevelSched& L, const Numer
     else if (N.config == 1) go(k_numeric_plan<16, 8>);
     else if (N.config == 2) go(k_numeric_plan<32, 16>);
     else go(k_numeric_plan<64, 32>);
+    return hipGetLastError();
+}
+
+int numeric_batch_plan_shape(const NumericPlan& N, int32_t max_row, int32_t max_lrow) {
+    if (!N.plan || N.config > 1) return -1;
+    return N.config == 0 ? 0 : max_row <= 12 && max_lrow <= 4 ? 1 : 2;
+}
+
+hipError_t launch_numeric_batch_plan(const PatDev& P, const NumericPlan& N, int shape, const double* a_val,
+                                     int32_t batch, double* f_val, bool fused, Ctl* ctl, uint64_t spin_limit,
+                                     int64_t skip_row, int32_t grid, const double* bvec, double* xout, hipStream_t s) {
+    if (P.n <= 0) return hipSuccess;
+    auto go = [&](auto plain, auto fma) {
+        hipLaunchKernelGGL(fused ? fma : plain, dim3(grid), dim3(kWave), 0, s, P, N, a_val, batch, f_val, ctl, spin_limit,
+                           skip_row, bvec, xout);
+    };
+    if (shape == 0) go(k_numeric_batch_plan<4, 8, 8, 4, false>, k_numeric_batch_plan<4, 8, 8, 4, true>);
+    else if (shape == 1) go(k_numeric_batch_plan<4, 12, 16, 8, false>, k_numeric_batch_plan<4, 12, 16, 8, true>);
+    else go(k_numeric_batch_plan<8, 16, 16, 8, false>, k_numeric_batch_plan<8, 16, 16, 8, true>);
     return hipGetLastError();
 }
 

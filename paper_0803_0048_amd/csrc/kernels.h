@@ -245,6 +245,11 @@ size_t numeric_plan_bytes(int config);
 // before[i] = entries of L~ in rows 0 .. i - 1, [n + 1] (one workgroup: small systems)
 hipError_t launch_lower_before(int32_t n, const int64_t* rpF, const int32_t* diagF, int32_t* before, hipStream_t s);
 hipError_t launch_numeric_plan(const PatDev& P, const LevelSched& L, const NumericPlan& N, hipStream_t s);
+// batches by the plan: the shape for the pattern (-1: none)
+int numeric_batch_plan_shape(const NumericPlan& N, int32_t max_row, int32_t max_lrow);
+hipError_t launch_numeric_batch_plan(const PatDev& P, const NumericPlan& N, int shape, const double* a_val,
+                                     int32_t batch, double* f_val, bool fused, Ctl* ctl, uint64_t spin_limit,
+                                     int64_t skip_row, int32_t grid, const double* bvec, double* xout, hipStream_t s);
 hipError_t launch_numeric_level(const PatDev& P, const LevelSched& L, const NumericPlan& N, const double* a_val,
                                 double* f_val, bool fused, Ctl* ctl, uint64_t spin_limit, int64_t skip_row,
                                 hipStream_t s);

@@ -559,6 +559,17 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
                                              ctx->fused, ctl, ctx->spin_limit, ctx->skip_row, ctx->stream));
             return TPILU_OK;
         }
+        const int shape = numeric_batch_plan_shape(pat->nplan, pat->st.max_row, pat->st.max_lrow);
+        if (batch > 1 && shape >= 0 && ctx->placement == 0) {
+            // tasks of a level; 1024 / 2048 wavefronts (ms): 2-D 128^2 ILU(2) x 256,
+            // 128 tasks, 0.96 / 0.98; ILU(1) x 64, 43, 0.57 / 0.61; ILU(2) x 1024, 512,
+            // 2.17 / 1.73
+            const int64_t wide = pat->n * ((batch + kWave - 1) / kWave) / std::max<int64_t>(pat->depth_l, 1);
+            const int32_t waves = ctx->grid_override ? ctx->grid_override : wide <= 256 ? 1024 : 2048;
+            HIPCHK(ctx, launch_numeric_batch_plan(pdev(ctx, pat), pat->nplan, shape, a_val, batch, f_val, ctx->fused,
+                                                  ctl, ctx->spin_limit, ctx->skip_row, waves, b, x, ctx->stream));
+            return TPILU_OK;
+        }
         HIPCHK(ctx, launch_numeric(pdev(ctx, pat, RowKernel::Numeric, true), a_val, batch, f_val, ctl,
                                    ctx->spin_limit, ctx->skip_row, grid, pat->st.max_row, pat->st.max_lrow, flow,
                                    one_xcd, batch_global_row(ctx, pat, batch) ? wrow : nullptr, b, x,

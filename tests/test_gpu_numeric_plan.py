@@ -109,3 +109,33 @@ def test_zero_pivot_is_reported(m, row):
     with pytest.raises(T.TpiluError) as e:
         T.numeric(pat, torch.from_numpy(val).to(dev))
     assert e.value.bad_row == row
+
+
+@pytest.mark.parametrize("n,lower,upper,B", [
+    (1, 0, 0, 2), (3, 1, 1, 65), (150, 4, 3, 2), (150, 4, 4, 63), (150, 3, 8, 64), (150, 4, 7, 65), (150, 4, 8, 66),
+    (120, 5, 6, 7), (120, 8, 7, 130), (90, 8, 8, 3), (60, 9, 2, 5)])
+def test_batches(n, lower, upper, B):
+    """Instances as lanes: rows that just fill 8, 12 and 16 entries and one more, part and
+    whole groups of instances, the forward substitution fused into the factorization or not."""
+    A = _band(n, lower, upper, n + lower)
+    rng = np.random.default_rng(B)
+    val = A.val[:, None] * rng.uniform(0.5, 1.5, (1, B))
+    b = rng.standard_normal((n, B))
+    dev = torch.device("cuda")
+    pat = T.symbolic(torch.from_numpy(A.rowptr).to(dev), torch.from_numpy(A.col).to(dev), 0)
+    a, bt = torch.from_numpy(val).to(dev), torch.from_numpy(b).to(dev)
+    rp, ci, _ = oracle.symbolic(n, A.rowptr, A.col, 0)
+    graph = T.BatchedGraph(pat, a, bt)
+    graph.launch()
+    torch.cuda.synchronize()
+    for fused in (False, True):
+        ref = np.stack([oracle.numeric(n, A.rowptr, A.col, val[:, q], rp, ci, fused=fused)[0] for q in range(B)], 1)
+        T.context().set_fused(fused)
+        try:
+            assert_bits_equal(T.numeric(pat, a), ref, f"fused {fused}")
+        finally:
+            T.context().set_fused(False)
+        if not fused:
+            y = np.stack([oracle.apply(n, rp, ci, ref[:, q], b[:, q])[1] for q in range(B)], 1)
+            assert_bits_equal(graph.f_val, ref, "graph factor")
+            assert_bits_equal(graph.y, y, "graph y")
