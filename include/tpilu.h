@@ -124,11 +124,13 @@ TPILU_API tpilu_status tpilu_ctx_set_grid(tpilu_ctx ctx, int32_t waves);
 enum { TPILU_SOLVER_AUTO = 0, TPILU_SOLVER_DEVICE = 1, TPILU_SOLVER_WORKGROUP = 2, TPILU_SOLVER_LANES = 3 };
 TPILU_API tpilu_status tpilu_ctx_set_solver(tpilu_ctx ctx, int mode);
 
-/* Kernel of the single-instance numeric factorization: 0 = automatic (the
- * dataflow kernel when the pattern's rows fit its LDS staging, the strict
- * lower part holds at least 4n entries, an entry receives fewer than 12
- * updates on average and a dependency level holds fewer than 64 rows on
- * average, else the pivot-serial one),
+/* Kernel of the single-instance numeric factorization: 0 = automatic (while
+ * placement and grid are automatic too, several rows per wavefront with their
+ * entries in registers for rows of at most 64 entries, of more than 16 only if
+ * the pattern has an update per pivot; else the dataflow kernel when the
+ * pattern's rows fit its LDS staging, the strict lower part holds at least 4n
+ * entries, an entry receives fewer than 12 updates on average and a dependency
+ * level holds fewer than 64 rows on average; else the pivot-serial one),
  * 1 = dataflow (lanes own the entries of a row and take
  * their updates in ascending pivot order; a later tpilu_numeric fails with
  * TPILU_E_INVAL if the pattern's rows do not fit), 2 = pivot-serial (the
@@ -151,9 +153,11 @@ TPILU_API tpilu_status tpilu_ctx_set_fused(tpilu_ctx ctx, int on);
 /* Placement of the single-instance numeric kernels, of the
  * wavefront-per-row solves and of the single-instance transposed solves of
  * tpilu_apply_adjoint: 0 = automatic (the numeric kernels on the whole
- * device; a solve on one XCD when its device-wide shape would take at most
- * 256 wavefronts, i.e. a dependency level holds fewer than 32 rows, or fewer
- * than 64 short ones, and a row half at most 128 entries on average),
+ * device, but on one XCD or one CU where rows are short and levels narrow; a
+ * solve on one XCD when its device-wide shape would take at most 256
+ * wavefronts, i.e. a dependency level holds fewer than 32 rows, or fewer than
+ * 64 short ones, and a row half at most 128 entries on average, and the solves
+ * of short halves by their level chunks: one CU, one XCD or the device),
  * 1 = the whole device, 2 = one XCD (then also the batched factorization
  * and solves, and the dependency-level computation of tpilu_symbolic, one XCD
  * per dependency graph, when its nodes have long dependency lists; by blocks

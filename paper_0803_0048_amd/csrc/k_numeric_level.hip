@@ -18,7 +18,7 @@
 //   k_numeric_lds    small systems of short rows on one compute unit, U~ in its
 //                    LDS: 0.33 us for the pivots of a 2-D ILU(1) level and 0.17
 //                    to store
-// Measured (us, a wavefront per row -> here): 2-D 64 x 64 ILU(1) 431 -> 125, 400
+// Measured (us, a wavefront per row -> here): 2-D 64 x 64 ILU(1) 429 -> 121, 400
 // x 400 ILU(1) 2788 -> 984 and ILU(3) 4725 -> 2081, 7-point 64^3 ILU(0) 805 ->
 // 366, ILU(1) 1264 -> 756, ILU(2) 2258 -> 1756, 110^3 ILU(0) 3470 -> 798; 27-point
 // 50^3 ILU(0) 1147 -> 922, ILU(1) 2711 -> 2253.  (A lane per row with 64 rows a

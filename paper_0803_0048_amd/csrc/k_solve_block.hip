@@ -24,7 +24,7 @@
 // reads, two dependent subtractions, the choice of the next two entries), and
 // one hand-off through the L2 of the XCD that all wavefronts run on
 // (Scope::Xcd), about 0.23 us.  Random banded n=160,000 ILU(2) (9 rounds a
-// block, 12,281 levels), both sweeps: 16.6 ms by a wavefront per row, 6.4 ms
+// block, 12,281 levels), both sweeps: 16.6 ms by a wavefront per row, 6.7 ms
 // here; ILU(1) 4.9 -> 3.0 ms; n=10,000 ILU(2) 1.39 -> 0.56 ms.  Rows that
 // depend on their direct predecessor (stencils) walk 64 rounds a block and
 // stay with the other kernels.

@@ -1332,7 +1332,7 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
 // levels as they come.  The maximum does not depend on order, so a lane walks
 // four strided parts of its window at a time.  Bound by one hand-off and the walk of
 // each block.  Random banded n=160,000 ILU(2), both DAGs, beside the update
-// schedule: 16.2 ms by a wavefront per node, 6.6 ms here (the whole of Phase I
+// schedule: 16.2 ms by a wavefront per node, 5.8 ms here (the whole of Phase I
 // 27.6 -> 22.6 ms; ILU(1) 11.2 -> 9.3, ILU(0) 6.9 -> 4.0 ms).
 // The two DAGs of a launch take alternate workgroups, which the dispatcher
 // deals to the XCDs in turn: each elects an XCD of its own.
