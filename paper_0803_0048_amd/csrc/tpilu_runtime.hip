@@ -970,8 +970,8 @@ tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     }
     if (N.config <= 1 && N.nnz_u <= kLdsNumericU) {
         N.ucum = (int32_t*)pat->take(sizeof(int32_t) * (size_t)(n + 1));
-        if (!N.ucum) return fail(ctx, TPILU_E_NOMEM, "numeric plan");
-        HIPCHK(ctx, launch_lower_before(n, pat->rpF, pat->diagF, N.ucum, s));
+        if (N.ucum) HIPCHK(ctx, launch_lower_before(n, pat->rpF, pat->diagF, N.ucum, s));
+        else (void)hipGetLastError();
     }
     N.plan = plan;
     HIPCHK(ctx, launch_numeric_plan(pat->dev(), pat->lsL, N, s));
@@ -1857,7 +1857,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     double* wsd = pat->grow(pat->ws_gm, sizeof(double) * doubles);
     if (!wsd) return fail(ctx, TPILU_E_NOMEM, "gmres workspace");
     if (!ctx->flags) {
-        HIPCHK(ctx, hipHostMalloc((void**)&ctx->flags, 64, hipHostMallocMapped));
+        HIPCHK(ctx, hipHostMalloc((void**)&ctx->flags, 64, hipHostMallocMapped | hipHostMallocCoherent));
         std::memset(ctx->flags, 0, 64);
     }
     // The next step is launched before this one has reported, so that the
