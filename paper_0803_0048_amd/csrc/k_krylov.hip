@@ -146,13 +146,14 @@ __device__ __forceinline__ Rotation givens_rotation(double a, double b) {
     return r;
 }
 
-// The step's outcome to the host, which polls flags[3] for the step's number.
+// The step's outcome to the host, which polls the slot for the step's number.
 __device__ __forceinline__ void gm_report(const GmStep& a, int32_t iters, int32_t stop) {
     if (threadIdx.x != 0) return;
-    a.flags[0] = iters;
-    a.flags[1] = stop;
-    a.flags[2] = (int32_t)ld_u32_coherent(&a.ctl->status);
-    __hip_atomic_store(const_cast<int32_t*>(a.flags) + 3, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    volatile int32_t* slot = gm_report_slot(a.flags, a.seq);
+    slot[0] = iters;
+    slot[1] = stop;
+    slot[2] = (int32_t)ld_u32_coherent(&a.ctl->status);
+    __hip_atomic_store(const_cast<int32_t*>(slot) + 3, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Givens, by one workgroup: apply rotations 0..j-1 to column j of H, form

@@ -303,8 +303,16 @@ hipError_t launch_dot_final(const double* partial, double* out, int sqrt_it, hip
 
 struct GmresDev;  // defined in the Krylov unit
 // One Arnoldi step j on w = A M^-1 v_j: h_ij and w by modified Gram-Schmidt,
-// v_{j+1}, the rotations and the stopping test; flags (host memory mapped for
-// the device) = iterations, stop, the control block's status, and then seq.
+// v_{j+1}, the rotations and the stopping test; the slot of seq in flags (host
+// memory mapped for the device) = iterations, stop, the control block's status,
+// and then seq.
+// Consecutive steps report to different slots: the host launches one step
+// before it has read the report of the last.
+constexpr int32_t kGmReports = 2;
+template <class Int>
+__host__ __device__ __forceinline__ Int* gm_report_slot(Int* flags, int32_t seq) {
+    return flags + 4 * (int32_t)((uint32_t)seq % (uint32_t)kGmReports);
+}
 struct GmStep {
     int64_t n;
     double* V;  // (m + 1) x n

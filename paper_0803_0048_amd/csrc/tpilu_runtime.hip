@@ -41,9 +41,10 @@ struct tpilu_ctx_s {
     // second stream (default priority) for work that overlaps the main one
     hipStream_t aux = nullptr;
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-    // mapped host memory the GMRES steps report to: [0] iterations, [1] stop,
-    // [2] status, [3] number of the last step that reported; [4] of the last launched
+    // mapped host memory the GMRES steps report to, kGmReports slots of
+    // iterations, stop, status, number of the step (k_krylov.hip)
     int32_t* flags = nullptr;
+    int32_t gm_launched = 0;  // number of the last step launched
     double* scratch = nullptr;  // device address of the no-alloc scratch on this device
     hipError_t scratch_err = hipSuccess;
     std::string err;
@@ -1809,19 +1810,29 @@ tpilu_status enqueue_precond(tpilu_ctx ctx, tpilu_pattern pat, const double* m_v
     return TPILU_OK;
 }
 
-// Wait until a GMRES step has reported: its number appears in mapped memory.
-// The stream is asked now and then, so that a failure ends the wait.
-tpilu_status await_step(tpilu_ctx ctx, int32_t seq) {
-    for (;;) {
-        for (int spin = 0; spin < 4096; ++spin)
-            if (__atomic_load_n(&ctx->flags[3], __ATOMIC_ACQUIRE) - seq >= 0) return TPILU_OK;
+// Wait until GMRES step seq has reported: its number appears in its slot of the
+// mapped memory (report: iterations, stop, status).  At most one later step is
+// in flight meanwhile, and that one reports to another slot, so the report
+// stays what this step wrote however late the host reads it.  The stream is
+// asked now and then, so that a failure ends the wait.
+tpilu_status await_step(tpilu_ctx ctx, int32_t seq, int32_t (&report)[3]) {
+    const int32_t* slot = gm_report_slot(ctx->flags, seq);
+#ifdef TPILU_JITTER
+    // the latest a host can look: every step in flight has reported
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+#endif
+    for (int spin = 0; __atomic_load_n(&slot[3], __ATOMIC_ACQUIRE) != seq; ++spin) {
+        if (spin < 4096) continue;
+        spin = 0;
         const hipError_t e = hipStreamQuery(ctx->stream);
         if (e == hipErrorNotReady) continue;
         HIPCHK(ctx, e);
         // the stream is done, so the report is there
-        if (__atomic_load_n(&ctx->flags[3], __ATOMIC_ACQUIRE) - seq >= 0) return TPILU_OK;
-        return fail(ctx, TPILU_E_DEVICE, "a GMRES step did not report");
+        if (__atomic_load_n(&slot[3], __ATOMIC_ACQUIRE) != seq)
+            return fail(ctx, TPILU_E_DEVICE, "a GMRES step did not report");
     }
+    for (int i = 0; i < 3; ++i) report[i] = slot[i];
+    return TPILU_OK;
 }
 
 tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, const double* f_val, bool inverse,
@@ -1906,14 +1917,14 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
         if (beta <= tol || it_host >= maxit) break;
         HIPCHK(ctx, launch_gm_start(n, partial, scal + 1, g, iflags + 1, w, V, s));
         int32_t jj = 0;
-        const int32_t seq0 = ctx->flags[4];  // steps reported so far
+        const int32_t seq0 = ctx->gm_launched;  // all of them have reported, or will before the next ones
         auto enqueue_step = [&](int32_t j) -> tpilu_status {
             tpilu_status se = enqueue_precond(ctx, pat, f_val, inverse, V + (size_t)j * nn, z, t, reset, iflags + 1);
             reset = false;
             if (se) return se;
             HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
             const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags,
-                              ++ctx->flags[4], pat->ctl};
+                              ++ctx->gm_launched, pat->ctl};
             HIPCHK(ctx, launch_gm_step(step, partial, s));
             return TPILU_OK;
         };
@@ -1922,18 +1933,19 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
             const int32_t upto = std::min(m, j + 1 + (ahead ? 1 : 0));
             for (; queued < upto; ++queued)
                 if ((st = enqueue_step(queued))) return st;
-            st = await_step(ctx, seq0 + j + 1);
+            int32_t report[3];
+            st = await_step(ctx, seq0 + j + 1, report);
             if (st) return st;
-            it_host = ctx->flags[0];
+            it_host = report[0];
             jj = j + 1;
             // a preconditioner wait that ran out leaves NaN iterates behind,
             // which no stopping test catches: end the solve at once
-            if ((uint32_t)ctx->flags[2] & kStTimeout) {
+            if ((uint32_t)report[2] & kStTimeout) {
                 *iters = it_host;
                 *relres = NAN;
                 return read_ctl(ctx, pat, nullptr, false);
             }
-            if (ctx->flags[1]) break;
+            if (report[1]) break;
         }
         HIPCHK(ctx, launch_gm_backsub(H, g, yv, m, jj, s));
         HIPCHK(ctx, launch_gm_combine(n, V, yv, jj, u, s));
