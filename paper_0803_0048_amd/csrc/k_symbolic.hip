@@ -1317,7 +1317,13 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
                 for (int w = min(4 << idle, kLaneWatch); w > 0 && uniform(ld_level(J.depth + c)) < 0; --w) {}
                 idle = min(idle + 1, 3);
             }
-            if (wait_expired(polls, t0, ctl, spin_limit)) break;
+            if (wait_expired(polls, t0, ctl, spin_limit)) {
+                // the status tells; a level all the same, so that the order sorted
+                // by level next still holds every node once
+                if (!done)
+                    __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
         }
     }
 }
@@ -1490,7 +1496,8 @@ __global__ __launch_bounds__(128) void k_depth_blocks(int32_t n, LevelJob j0, Le
 }
 
 // Rows sorted by level (counting sort): hist, scan (shared scan kernel),
-// scatter.  The order inside a level is whatever the atomics give; any
+// scatter.  Every depth is in 1 .. n, also after a wait that ran out: each
+// level kernel then stores 1 + the largest level that it saw.  The order inside a level is whatever the atomics give; any
 // order that lists every level before the next is a valid schedule, and the
 // results never depend on it.
 __global__ void k_level_hist(int32_t n, const int32_t* __restrict__ depth, int32_t* hist, int32_t* most) {

@@ -853,6 +853,7 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     else
         HIPCHK(ctx, launch_depth(n, jb[0], njobs > 1 ? &jb[1] : nullptr, pat->ctl, ctx->spin_limit, grid, lv_xcd, s));
     HIPCHK(ctx, launch_fill_i32(dmax, (int64_t)zeros, 0, s));
+    HIPCHK(ctx, hipMemcpyAsync(dmax + 3, &pat->ctl->status, sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
     for (int q = 0; q < njobs; ++q) {
         int32_t* hist = dmax + 32 + (size_t)q * 2 * (size_t)std::max(n, 1);
         int64_t* off = (int64_t*)T.get(sizeof(int64_t) * ((size_t)n + 1));
@@ -867,11 +868,12 @@ tpilu_status enqueue_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     return TPILU_OK;
 }
 
-// After the level work has completed: the maxima to the host.  (The caller
-// reads the watchdog's status.)
+// After the level work has completed: the maxima to the host, and whether a
+// wait ran out (then the levels are not to be used).
 tpilu_status finish_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* js, int njobs, const int32_t* dmax) {
     int32_t dm[32] = {0};
     HIPCHK(ctx, hipMemcpy(dm, dmax, sizeof(dm), hipMemcpyDeviceToHost));
+    if ((uint32_t)dm[3] & kStTimeout) return read_ctl(ctx, pat, nullptr, false);
     for (int q = 0; q < njobs; ++q) {
         *js[q].max_depth = dm[16 * q];
         if (js[q].nchunk) *js[q].nchunk = dm[16 * q + 1];
@@ -886,8 +888,7 @@ tpilu_status compute_levels(tpilu_ctx ctx, tpilu_pattern pat, const LevelSpec* j
     tpilu_status st = enqueue_levels(ctx, pat, js, njobs, ctx->stream, T, &dmax);
     if (st != TPILU_OK) return st;
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    st = finish_levels(ctx, pat, js, njobs, dmax);
-    return st != TPILU_OK ? st : read_ctl(ctx, pat, nullptr, false);
+    return finish_levels(ctx, pat, js, njobs, dmax);
 }
 
 // Shape of the two products (kProd*): as the solver mode asks (1 a wavefront
