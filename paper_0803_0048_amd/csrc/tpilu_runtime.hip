@@ -177,9 +177,11 @@ struct Alloc {
     void* user = nullptr;
     void* get(size_t bytes) const {
         if (bytes == 0) bytes = 8;
-        if (alloc) return alloc(bytes, user);
         void* p = nullptr;
-        if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+        if (alloc) p = alloc(bytes, user);
+        else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
+        // who asks may do with less: the launch that follows must not report this
+        if (!p) (void)hipGetLastError();
         return p;
     }
     void put(void* p) const {
@@ -966,14 +968,10 @@ tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     N.waves = !N.one_xcd ? 2048 : width <= kPlanXcdNarrow ? 128 : 256;
     N.rec = (int4*)pat->take(sizeof(int4) * (size_t)n);
     uint8_t* plan = N.rec ? (uint8_t*)pat->take(numeric_plan_bytes(N.config) * (size_t)n) : nullptr;
-    if (!plan) {
-        (void)hipGetLastError();
-        return TPILU_OK;
-    }
+    if (!plan) return TPILU_OK;
     if (N.config <= 1 && N.nnz_u <= kLdsNumericU) {
         N.ucum = (int32_t*)pat->take(sizeof(int32_t) * (size_t)(n + 1));
         if (N.ucum) HIPCHK(ctx, launch_lower_before(n, pat->rpF, pat->diagF, N.ucum, s));
-        else (void)hipGetLastError();
     }
     N.plan = plan;
     HIPCHK(ctx, launch_numeric_plan(pat->dev(), pat->lsL, N, s));
