@@ -91,10 +91,11 @@ TPILU_API void tpilu_ctx_destroy(tpilu_ctx ctx);
 TPILU_API const char *tpilu_status_string(tpilu_status st);
 TPILU_API const char *tpilu_last_error(tpilu_ctx ctx);
 
-/* Watchdog for the dependency waits inside the persistent kernels: a wait
- * gives up after `timeout_us` microseconds of wall-clock time (0 = library
- * default, 10 s), every other wait of the call then gives up at once, and the
- * call reports TPILU_E_TIMEOUT.  `skip_publish_row` >= 0 makes the numeric
+/* Watchdog for the waits of a wavefront on values that other workgroups
+ * publish: a wait gives up after `timeout_us` microseconds of wall-clock time (0
+ * = library default, 10 s), every other wait of the call then gives up at once,
+ * and the call reports TPILU_E_TIMEOUT.  (The kernels that run in one workgroup
+ * wait only for its own wavefronts, which always end.)  `skip_publish_row` >= 0 makes the numeric
  * kernel never publish that row (a host-forced failure for testing the
  * watchdog); -1 turns that off. */
 TPILU_API tpilu_status tpilu_ctx_set_watchdog(tpilu_ctx ctx, uint32_t timeout_us,

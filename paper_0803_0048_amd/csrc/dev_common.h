@@ -22,7 +22,16 @@
 // Every wait is bounded: after a wall-clock budget it sets the control
 // block's abort word and the TIMEOUT bit and returns a quiet NaN; every other
 // wait notices the abort word within a few polls and gives up too, so all
-// waves always drain.
+// waves always drain.  Waits of a workgroup for its own wavefronts: the walk
+// inside a block of rows is watched over (watch_walk); the one-compute-unit
+// kernels poll a count of finished parts in LDS without a limit.  Part c there
+// waits until `first` parts are done, first <= c the number of parts before its
+// level, and every wavefront takes its parts in ascending order, counting each
+// once: the smallest unfinished part finds all before it done, so its wait
+// ends, whatever values the arrays hold.  (Measured, 2-D 64 x 64 ILU(1), both
+// sweeps, 76 us: with a look at the clock every 64 polls 93, with a counted bound
+// 81 to 142 by the form of the loop, with a wavefront that watches the count 78;
+// the factorization 92, with a watching wavefront 98.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -301,6 +310,29 @@ __device__ __forceinline__ bool wait_expired(uint32_t& polls, uint64_t& t0, Ctl*
         give_up = true;
     }
     return give_up;
+}
+
+typedef __attribute__((address_space(3))) volatile int32_t LdsWord32;
+// The walk inside a block of rows (k_solve_block.hip, the levels by blocks) ends
+// when its window has all values, so the wavefront that brings them watches
+// over it: `walk` holds 2 t + 1 while block t's walk is under way and 2 t + 2 after
+// it; when that takes too long, `release` puts a value in every place that has
+// none.  (A count of rounds in the walk itself cost 4 % of the solve, a look at the
+// clock 21 %.)
+template <class Release>
+__device__ __forceinline__ void watch_walk(LdsWord32* walk, int32_t t, Ctl* ctl, uint64_t limit, Release&& release) {
+    uint32_t polls = 0;
+    uint64_t t0 = 0;
+    for (;;) {
+        const int32_t w = uniform(*walk);
+        if (w == 2 * t + 2) return;
+        if (w != 2 * t + 1) polls = 0;
+        __builtin_amdgcn_s_sleep(2);
+        if (wait_expired(polls, t0, ctl, limit)) {
+            release();
+            return;
+        }
+    }
 }
 
 // Communication scope of the hand-off protocol: across the whole device

@@ -131,7 +131,10 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
     __shared__ int32_t cw[(kWinEntries + 4) * kWave];
     __shared__ uint64_t xsh[(kWinBlocks + 1) * kWave];
     __shared__ uint32_t sh_ticket;
+    __shared__ int32_t sh_walk;
     LdsWord* xw = (LdsWord*)xsh;
+    LdsWord32* walk = (LdsWord32*)&sh_walk;
+    if (threadIdx.x == 0) *walk = 0;
     if (!xcd_member(ctl)) return;
     const int lane = lane_id();
     const bool solver = uniform((int32_t)(threadIdx.x / kWave)) == 0;
@@ -176,6 +179,10 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
                     }
                 }
             }
+            watch_walk(walk, (int32_t)t, ctl, limit, [&]() {
+                for (int u = 0; u <= kWinBlocks; ++u)
+                    if (xw[u * kWave + lane] == kPending) xw[u * kWave + lane] = kQNaN;
+            });
             continue;
         }
         trace_mark_lane(trace, tr0 + i, has);
@@ -276,6 +283,7 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
         uint64_t left = __ballot(has);  // rows not finished
         double f0 = fw[lane], f1 = fw[kWave + lane];
         int32_t c0 = cw[lane], c1 = cw[kWave + lane];
+        if (lane == 0) *walk = 2 * (int32_t)t + 1;
         if (!stop) do {
             // the two entries after this round's, then the values of this round's
             const double* fp = fw + (e + 2) * kWave + lane;
@@ -306,6 +314,7 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
             }
             left &= ~m;
         } while (left);
+        if (lane == 0) *walk = 2 * (int32_t)t + 2;
         if (stop && !done) st_final<Scope::Xcd>(out + i, as_f64(kQNaN));
     }
 }

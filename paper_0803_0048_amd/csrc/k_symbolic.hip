@@ -1347,7 +1347,8 @@ constexpr int kDepthOuter = 8;
 
 template <bool kBackward>
 __device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const uint8_t* __restrict__ wcnt, Ctl* ctl,
-                                             uint64_t limit, int32_t* cw, LdsLevel* lw, uint32_t* sh_ticket) {
+                                             uint64_t limit, int32_t* cw, LdsLevel* lw, uint32_t* sh_ticket,
+                                             LdsWord32* walk) {
     const int32_t* __restrict__ ci = J.G.idx;
     const int lane = lane_id();
     const bool walker = uniform((int32_t)(threadIdx.x / kWave)) == 0;
@@ -1390,6 +1391,10 @@ __device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const
                     }
                 }
             }
+            watch_walk(walk, (int32_t)t, ctl, limit, [&]() {
+                for (int u = 0; u <= kWinBlocks; ++u)
+                    if (lw[u * kWave + lane] < 0) lw[u * kWave + lane] = 0;
+            });
             continue;
         }
         int32_t q = 0, z = 0, w = 0;
@@ -1452,6 +1457,7 @@ __device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const
         }
         bool done = !has;
         uint64_t left = __ballot(has);
+        if (lane == 0) *walk = 2 * (int32_t)t + 1;
         if (!stop) do {
             int32_t cn[kDepthSlots], v[kDepthSlots];
 #pragma unroll
@@ -1478,6 +1484,7 @@ __device__ __forceinline__ void depth_blocks(int32_t n, const LevelJob& J, const
             done = done || fin;
             left &= ~m;
         } while (left);
+        if (lane == 0) *walk = 2 * (int32_t)t + 2;
         if (stop && !done) __hip_atomic_store(J.depth + i, best + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
@@ -1490,9 +1497,12 @@ __global__ __launch_bounds__(128) void k_depth_blocks(int32_t n, LevelJob j0, Le
     __shared__ uint32_t sh_ticket;
     const LevelJob J = (blockIdx.x & 1) ? j1 : j0;
     if (!xcd_member(J.tctl)) return;
+    __shared__ int32_t sh_walk;
     LdsLevel* lw = (LdsLevel*)lwsh;
-    if (J.desc) depth_blocks<true>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket);
-    else depth_blocks<false>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket);
+    LdsWord32* walk = (LdsWord32*)&sh_walk;
+    if (threadIdx.x == 0) *walk = 0;
+    if (J.desc) depth_blocks<true>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket, walk);
+    else depth_blocks<false>(n, J, J.wcnt, ctl, spin_limit, cw, lw, &sh_ticket, walk);
 }
 
 // Rows sorted by level (counting sort): hist, scan (shared scan kernel),
