@@ -475,6 +475,7 @@ __global__ __launch_bounds__(kLdsWaves * 64) void k_numeric_lds(PatDev P, Numeri
             if (k < most) w = group_step<G, KP, kFused, k>(w, x.rel, v[k]);
         });
         trace_mark_lane(P.trace, 3 * (int64_t)P.n + x.j, mine && t == 0);
+        jitter((uint32_t)c);
         if (mine && t >= x.nl) U[at + t] = w;
         // the wavefront's LDS operations complete in order: the count rises after the values are there
         if (lane_id() == 0) __hip_atomic_fetch_add((int32_t*)done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
