@@ -650,29 +650,31 @@ __global__ __launch_bounds__(256) void k_a2f(int32_t n, const int64_t* __restric
                                              const int32_t* __restrict__ ciA, const int64_t* __restrict__ rpF,
                                              const int32_t* __restrict__ ciF, int32_t* __restrict__ a2f,
                                              uint32_t* status) {
-    const int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kA2fLanes;
-    if (i >= n) return;
-    const int64_t qb = rpF[i], qe = rpF[i + 1], pe = rpA[i + 1];
-    for (int64_t p = rpA[i] + threadIdx.x % kA2fLanes; p < pe; p += kA2fLanes) {
-        const int32_t c = ciA[p];
-        int64_t lo = qb, hi = qe;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (ciF[mid] < c) lo = mid + 1;
-            else hi = mid;
-        }
-        if (lo < qe && ciF[lo] == c) {
-            a2f[p] = static_cast<int32_t>(lo);
-        } else {
-            a2f[p] = -1;
-            atomicOr(status, kValBadCol);
+    const int64_t stride = gridDim.x * (int64_t)(blockDim.x / kA2fLanes);
+    for (int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kA2fLanes; i < n; i += stride) {
+        const int64_t qb = rpF[i], qe = rpF[i + 1], pe = rpA[i + 1];
+        for (int64_t p = rpA[i] + threadIdx.x % kA2fLanes; p < pe; p += kA2fLanes) {
+            const int32_t c = ciA[p];
+            int64_t lo = qb, hi = qe;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (ciF[mid] < c) lo = mid + 1;
+                else hi = mid;
+            }
+            if (lo < qe && ciF[lo] == c) {
+                a2f[p] = static_cast<int32_t>(lo);
+            } else {
+                a2f[p] = -1;
+                atomicOr(status, kValBadCol);
+            }
         }
     }
 }
 
 hipError_t launch_a2f(int32_t n, const int64_t* rpA, const int32_t* ciA, const int64_t* rpF,
                       const int32_t* ciF, int32_t* a2f, uint32_t* status, hipStream_t s) {
-    const int64_t blocks = ((int64_t)n * kA2fLanes + 255) / 256;
+    // (a launch holds fewer than 2^32 threads)
+    const int64_t blocks = std::min<int64_t>(((int64_t)n * kA2fLanes + 255) / 256, 1 << 22);
     hipLaunchKernelGGL(k_a2f, dim3((unsigned)blocks), dim3(256), 0, s, n, rpA, ciA, rpF, ciF, a2f, status);
     return hipGetLastError();
 }
