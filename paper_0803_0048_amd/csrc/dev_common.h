@@ -424,10 +424,10 @@ __device__ __forceinline__ void row_products(int32_t n, const int32_t* __restric
 #pragma unroll
             for (int u = 0; u < kLoads; ++u) {
                 const int rr = u * kPer + lane / kTile;  // row of the tile
-                const int32_t ar = __shfl(a, rr), br = __shfl(b, rr);
-                const int32_t e = ar + k0 + kk;
-                if (e < br) on |= 1u << u;
-                const int32_t ec = e < br ? e : (br > ar ? br - 1 : 0);
+                const int32_t ar = __shfl(a, rr), lr = __shfl(len, rr);
+                const int32_t x = k0 + kk;  // (not ar + x < br: that sum can pass 2^31)
+                if (x < lr) on |= 1u << u;
+                const int32_t ec = lr > 0 ? ar + min(x, lr - 1) : 0;
                 cu[u] = ci[ec];
                 gu[u] = val[ec];
             }

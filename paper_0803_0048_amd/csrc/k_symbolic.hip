@@ -889,8 +889,8 @@ __global__ __launch_bounds__(64) void k_sched(int32_t n, const int64_t* __restri
                     for (int u = 0; u < kSchedAhead; ++u) {
                         tp[u] = p0 + (u << (6 - shift)) + (lane >> shift);
                         const int32_t a = __shfl(pd, tp[u] & (kWave - 1)), e = __shfl(pe, tp[u] & (kWave - 1));
-                        tq[u] = a + (lane & ((1 << shift) - 1));
-                        on[u] = tp[u] < np && tq[u] < e;
+                        tq[u] = (int32_t)((uint32_t)a + (uint32_t)(lane & ((1 << shift) - 1)));
+                        on[u] = tp[u] < np && (uint32_t)tq[u] < (uint32_t)e;  // (lanes past the end can pass 2^31)
                         tv[u] = on[u] ? ciF[tq[u]] : 0;
                     }
 #pragma unroll
@@ -907,8 +907,8 @@ __global__ __launch_bounds__(64) void k_sched(int32_t n, const int64_t* __restri
                             he = __builtin_amdgcn_readlane(pe, p & (kWave - 1));
                         }
                         tp[u] = p;
-                        tq[u] = q0 + lane;
-                        on[u] = p < np && tq[u] < he;
+                        tq[u] = (int32_t)((uint32_t)q0 + (uint32_t)lane);
+                        on[u] = p < np && (uint32_t)tq[u] < (uint32_t)he;
                         tv[u] = on[u] ? ciF[tq[u]] : 0;
                         q0 += kWave;
                     }
