@@ -897,7 +897,8 @@ __global__ __launch_bounds__(64) void k_sched(int32_t n, const int64_t* __restri
                     for (int u = 0; u < kSchedAhead; ++u) test(on[u], tv[u], tq[u], tp[u]);
                 }
             } else {
-                int32_t p = 0, q0 = __builtin_amdgcn_readlane(pd, 0), he = __builtin_amdgcn_readlane(pe, 0);
+                int32_t p = 0;
+                uint32_t q0 = __builtin_amdgcn_readlane(pd, 0), he = __builtin_amdgcn_readlane(pe, 0);
                 while (p < np) {
 #pragma unroll
                     for (int u = 0; u < kSchedAhead; ++u) {
@@ -907,8 +908,8 @@ __global__ __launch_bounds__(64) void k_sched(int32_t n, const int64_t* __restri
                             he = __builtin_amdgcn_readlane(pe, p & (kWave - 1));
                         }
                         tp[u] = p;
-                        tq[u] = (int32_t)((uint32_t)q0 + (uint32_t)lane);
-                        on[u] = p < np && (uint32_t)tq[u] < (uint32_t)he;
+                        tq[u] = (int32_t)(q0 + (uint32_t)lane);
+                        on[u] = p < np && (uint32_t)tq[u] < he;
                         tv[u] = on[u] ? ciF[tq[u]] : 0;
                         q0 += kWave;
                     }
