@@ -229,6 +229,7 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
                 }
         }
         if constexpr (!kBackward) s = sanitize_input(s, ctl);
+        const double s0 = s;
 
         // outer entries, the next chunk's loaded before this one's values are waited for
         bool stop = false;
@@ -276,6 +277,8 @@ __global__ __launch_bounds__(128) void k_solve_blocks(int32_t n, const int64_t* 
 #pragma unroll
             for (int k = 0; k < kOuterChunk; ++k) s = s - f[k] * as_f64(v[k]);  // before the row's start +0.0 * +0.0
         }
+
+        if (!kBackward && z == 0) s = s0;  // nothing to subtract: every bit stays
 
         // window: every lane walks its row, two entries a round
         int32_t e = 0;

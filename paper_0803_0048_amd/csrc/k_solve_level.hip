@@ -118,7 +118,7 @@ typedef __attribute__((address_space(3))) volatile int32_t LdsInt;
 // latency never sits between two levels.  Entries past a row's end multiply
 // +0.0 by the +0.0 kept in xs[n], which leaves every running difference as it
 // is, its sign of zero included.
-template <bool kBackward, int KE>
+template <bool kBackward, int KE, bool kKeepX>
 __device__ __forceinline__ void lds_sweep(const LevelSched& L, const double* __restrict__ F,
                                           const int32_t* __restrict__ ci, const double* __restrict__ in, double* out,
                                           LdsDouble* xs, LdsInt* done, Ctl* ctl, unsigned long long* trace,
@@ -174,9 +174,20 @@ __device__ __forceinline__ void lds_sweep(const LevelSched& L, const double* __r
         r1 = chunk_rec(L, h1);
         h2 = chunk_head(L, c + 2 * waves);
     }
+    // Rows of the first level have no entries, and their x is b to the bit; the
+    // +0.0 subtracted above makes a signalling NaN quiet.  Done again for callers
+    // that see x, in instances of their own: the loop above is a few percent slower
+    // beside any code for it (2-D 64^2 ILU(1) 76 -> 78 us).
+    if constexpr (kKeepX && !kBackward)
+        for (c = uniform((int32_t)(threadIdx.x / kWave)); c < L.nchunk; c += waves) {
+            h = chunk_head(L, c);
+            if (uniform(h.z) != 0) break;
+            r = chunk_rec(L, h);
+            if (r.z >= 0) out[r.x] = sanitize_input(in[r.x], ctl);
+        }
 }
 
-template <int KE>
+template <int KE, bool kKeepX>
 __global__ __launch_bounds__(1024) void k_solve_lds(int32_t n, LevelSched Lo, LevelSched Up,
                                                     const double* __restrict__ F, const int32_t* __restrict__ ci,
                                                     const double* __restrict__ b, double* x, double* y, int sweeps,
@@ -196,13 +207,13 @@ __global__ __launch_bounds__(1024) void k_solve_lds(int32_t n, LevelSched Lo, Le
         *done = 0;
     }
     __syncthreads();
-    if (sweeps & 1) lds_sweep<false, KE>(Lo, F, ci, b, x, xs, done, ctl, trace, 0, n, false);
+    if (sweeps & 1) lds_sweep<false, KE, kKeepX>(Lo, F, ci, b, x, xs, done, ctl, trace, 0, n, false);
     if (sweeps == 3) {
         __syncthreads();
         if (threadIdx.x == 0) *done = 0;
         __syncthreads();
     }
-    if (sweeps & 2) lds_sweep<true, KE>(Up, F, ci, x, y, xs, done, ctl, trace, 2 * (int64_t)n, n, (sweeps & 1) != 0);
+    if (sweeps & 2) lds_sweep<true, KE, kKeepX>(Up, F, ci, x, y, xs, done, ctl, trace, 2 * (int64_t)n, n, (sweeps & 1) != 0);
 }
 
 hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& Up, int32_t max_half,
@@ -215,9 +226,14 @@ hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& U
         hipLaunchKernelGGL(kern, dim3(1), dim3(1024), lds, s, n, Lo, Up, f_val, ci, b, x, y, sweeps, rs, ctl, trace,
                            skip);
     };
-    if (max_half <= 4) go(k_solve_lds<4>);
-    else if (max_half <= 8) go(k_solve_lds<8>);
-    else go(k_solve_lds<16>);
+    auto pick = [&](auto keep) {
+        constexpr bool K = decltype(keep)::value;
+        if (max_half <= 4) go(k_solve_lds<4, K>);
+        else if (max_half <= 8) go(k_solve_lds<8, K>);
+        else go(k_solve_lds<16, K>);
+    };
+    if (x && (sweeps & 1)) pick(std::true_type{});
+    else pick(std::false_type{});
     return hipGetLastError();
 }
 
@@ -232,7 +248,8 @@ hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& U
 // KE: entries of a row whose loads are in flight together.  The smallest that
 // holds a whole row half is the fastest (7-point 64^3 ILU(1), 6 entries: 0.77
 // ms with 8, 1.06 with 4, 0.96 with 16).
-template <bool kBackward, int KE>
+// kKeepX: the caller sees x (see lds_sweep); never backward.
+template <bool kBackward, int KE, bool kKeepX = false>
 __global__ __launch_bounds__(64) void k_solve_chunks(LevelSched L, const double* __restrict__ F,
                                                      const int32_t* __restrict__ ci, const double* __restrict__ in,
                                                      double* out, Ctl* ctl, uint64_t limit,
@@ -244,9 +261,16 @@ __global__ __launch_bounds__(64) void k_solve_chunks(LevelSched L, const double*
         if (lane == 0) c = (int32_t)atomicAdd(&ctl->part[0], 1u);
         c = uniform(c);
         if (c >= L.nchunk) break;
-        const int4 r = chunk_rec(L, chunk_head(L, c));
+        const int4 h = chunk_head(L, c), r = chunk_rec(L, h);
         const bool act = r.z >= 0;
         trace_mark_lane(trace, tr0 + r.x, act);
+        if constexpr (kKeepX) {
+            if (uniform(h.z) == 0) {  // the first level: no entries, x is b to the bit
+                if (act) st_final<Scope::Xcd>(out + r.x, sanitize_input(in[r.x], ctl));
+                trace_mark_lane(trace, tr0 + n + r.x, act);
+                continue;
+            }
+        }
         double s = 0.0, fii = 1.0;
         if (act) {
             s = in[r.x];
@@ -298,17 +322,17 @@ __global__ __launch_bounds__(64) void k_solve_chunks(LevelSched L, const double*
 }
 
 hipError_t launch_solve_chunks(const PatDev& P, const LevelSched& L, int32_t max_half, const double* f_val,
-                               const double* in, double* out, bool backward, int32_t grid, Ctl* ctl,
+                               const double* in, double* out, bool backward, bool keep_x, int32_t grid, Ctl* ctl,
                                uint64_t spin_limit, hipStream_t s) {
     if (P.n <= 0) return hipSuccess;
     const int64_t tr0 = backward ? 2 * (int64_t)P.n : 0;
-    auto go = [&](auto fwd, auto bwd) {
-        hipLaunchKernelGGL(backward ? bwd : fwd, dim3(grid * kXcds), dim3(64), 0, s, L, f_val, P.ciF, in, out, ctl,
+    auto go = [&](auto fwd, auto keep, auto bwd) {
+        hipLaunchKernelGGL(backward ? bwd : keep_x ? keep : fwd, dim3(grid * kXcds), dim3(64), 0, s, L, f_val, P.ciF, in, out, ctl,
                            spin_limit, P.trace, tr0, P.n);
     };
-    if (max_half <= 4) go(k_solve_chunks<false, 4>, k_solve_chunks<true, 4>);
-    else if (max_half <= 8) go(k_solve_chunks<false, 8>, k_solve_chunks<true, 8>);
-    else go(k_solve_chunks<false, 16>, k_solve_chunks<true, 16>);
+    if (max_half <= 4) go(k_solve_chunks<false, 4>, k_solve_chunks<false, 4, true>, k_solve_chunks<true, 4>);
+    else if (max_half <= 8) go(k_solve_chunks<false, 8>, k_solve_chunks<false, 8, true>, k_solve_chunks<true, 8>);
+    else go(k_solve_chunks<false, 16>, k_solve_chunks<false, 16, true>, k_solve_chunks<true, 16>);
     return hipGetLastError();
 }
 

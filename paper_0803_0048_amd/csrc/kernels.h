@@ -260,9 +260,10 @@ hipError_t launch_solve_lds(int32_t n, const LevelSched& Lo, const LevelSched& U
                             const double* f_val, const int32_t* ci, const double* b, double* x, double* y, int sweeps,
                             bool reset, Ctl* ctl, unsigned long long* trace, hipStream_t s,
                             const int32_t* skip = nullptr);
-// one sweep on one XCD with grid wavefronts there (out pre-filled with kPending)
+// one sweep on one XCD with grid wavefronts there (out pre-filled with kPending);
+// keep_x (forward): the caller sees out
 hipError_t launch_solve_chunks(const PatDev& P, const LevelSched& L, int32_t max_half, const double* f_val,
-                               const double* in, double* out, bool backward, int32_t grid, Ctl* ctl,
+                               const double* in, double* out, bool backward, bool keep_x, int32_t grid, Ctl* ctl,
                                uint64_t spin_limit, hipStream_t s);
 
 // ---- the solves by blocks of consecutive rows (k_solve_block.hip) -----------------

@@ -727,7 +727,7 @@ tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val
             HIPCHK(ctx, launch_solve_blocks(P, pat->wcntL, f_val, b, x, false, gf.grid, ctl, ctx->spin_limit,
                                             ctx->stream));
         else if (gf.kind == SolveKind::Chunks)
-            HIPCHK(ctx, launch_solve_chunks(P, pat->lsL, pat->st.max_lrow, f_val, b, x, false, gf.grid, ctl,
+            HIPCHK(ctx, launch_solve_chunks(P, pat->lsL, pat->st.max_lrow, f_val, b, x, false, keep_x, gf.grid, ctl,
                                             ctx->spin_limit, ctx->stream));
         else
             HIPCHK(ctx, launch_forward(P, f_val, batch, b, x, ctl, ctx->spin_limit, gf.grid, gf.one_xcd,
@@ -742,7 +742,7 @@ tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val
             HIPCHK(ctx, launch_solve_blocks(P, pat->wcntU, f_val, x, y, true, gb.grid, ctl, ctx->spin_limit,
                                             ctx->stream));
         else if (gb.kind == SolveKind::Chunks)
-            HIPCHK(ctx, launch_solve_chunks(P, pat->lsU, pat->st.max_upart, f_val, x, y, true, gb.grid, ctl,
+            HIPCHK(ctx, launch_solve_chunks(P, pat->lsU, pat->st.max_upart, f_val, x, y, true, false, gb.grid, ctl,
                                             ctx->spin_limit, ctx->stream));
         else
             HIPCHK(ctx, launch_backward(P, f_val, batch, x, y, ctl, ctx->spin_limit, gb.grid, gb.one_xcd,
