@@ -149,26 +149,27 @@ __device__ __forceinline__ double wait_final(const double* p, Ctl* ctl, uint64_t
     return wait_final(p, ld_cached(p), ctl, limit);
 }
 
-// Make every staged value of a chunk final: the pending ones are re-read
-// together, one round trip per round, until none is left; after a timeout or
-// an abort they become quiet NaNs.  Unused entries must hold a final value
-// and a valid index.
+// Make every staged value of a chunk final (from..to: those that have to be): the
+// pending ones from `from` on are re-read together, one round trip per round,
+// until none is left of those; after a timeout or an abort they become quiet
+// NaNs.  Unused entries must hold a final value and a valid index.
 template <int K>
 __device__ __forceinline__ void settle(const double* v, const int32_t (&idx)[K], uint64_t (&val)[K], int32_t B,
-                                       int32_t col, Ctl* ctl, uint64_t limit) {
+                                       int32_t col, Ctl* ctl, uint64_t limit, int from = 0, int to = K) {
     uint32_t n = 0;
     uint64_t t0 = 0;
     for (;;) {
         bool pend = false;
 #pragma unroll
-        for (int u = 0; u < K; ++u) pend = pend || val[u] == kPending;
+        for (int u = 0; u < K; ++u) pend = pend || (u >= from && u < to && val[u] == kPending);
         if (!pend) return;
         uint64_t nv[K];
 #pragma unroll
-        for (int u = 0; u < K; ++u) nv[u] = ld_coherent(v + (int64_t)idx[u] * B + col);
+        for (int u = 0; u < K; ++u)
+            if (u >= from) nv[u] = ld_coherent(v + (int64_t)idx[u] * B + col);
 #pragma unroll
         for (int u = 0; u < K; ++u)
-            if (val[u] == kPending) val[u] = nv[u];
+            if (u >= from && val[u] == kPending) val[u] = nv[u];
         if ((n & 31u) == 31u) {
             bool stop = (n & 255u) == 255u && ld_u32_coherent(&ctl->abort) != 0u;
             const uint64_t now = wall_clock64();

@@ -512,7 +512,11 @@ __global__ __launch_bounds__(64) void k_adj_numeric_batch(PatDev P, AdjPat T, co
             // Staged: the values of all their pairs kAdjPoll at a time, whichever
             // rows they are of (each slot still takes them in that order), then
             // the lbar, which only reach the diagonal: one wait instead of two
-            // per row (7-point 32^3 ILU(1), 16 instances: 1.81 ms, 1.17 here).
+            // per row (7-point 32^3 ILU(1), 16 instances: 1.81 ms, 1.15 here).  The
+            // lbar are taken one after the other while the later ones are on their
+            // way: the last to come is the last in order, and eight divisions after
+            // it are too many (band 300 n=20,000 ILU(0), 8 instances: 1.16 ms with
+            // all eight waited for first, 0.95 so).
             if (st_rows) {
                 for (int32_t c = 0; c < npair; c += kAdjPoll) {
                     uint64_t gv[kAdjPoll];
@@ -547,10 +551,10 @@ __global__ __launch_bounds__(64) void k_adj_numeric_batch(PatDev P, AdjPat T, co
 #pragma unroll
                     for (int u = 0; u < kAdjChunk; ++u)
                         if (c + u >= nrow) lb[u] = 0ull;
-                    settle(lbar_out, pp, lb, B, col, ctl, spin_limit);
 #pragma unroll
                     for (int u = 0; u < kAdjChunk; ++u) {
                         if (c + u < nrow) {
+                            settle(lbar_out, pp, lb, B, col, ctl, spin_limit, u, u + 1);
                             double tmp = as_f64(lb[u]) * La[(c + u) * kWave + lane];
                             tmp = tmp / ujj;
                             d = d - tmp;
