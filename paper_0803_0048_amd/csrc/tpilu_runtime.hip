@@ -129,6 +129,17 @@ constexpr int32_t kSolveWavesWide = 1024;
 constexpr int64_t kFlowMinL = 4;
 constexpr int64_t kFlowMaxChain = 12;
 constexpr int64_t kFlowMaxWidth = 64;
+// The plan of Phase II (k_numeric_level.hip): least updates per pivot for which it
+// is laid down, by the lanes of a row (32: uniform random n=40,000 ILU(1), 1.0
+// updates a pivot, 82 us by the plan, 116 pivot-serial; 64: uniform random
+// n=20,000 ILU(1), 1.1, 97 / 79, but band 15 n=50,000 ILU(1), 3.5, 43.2 / 52.1 ms
+// dataflow), and below which the dataflow kernel, where it would be the choice
+// otherwise, is ahead (plan / dataflow: band 300 n=160,000 ILU(0) 4.59 / 0.46
+// ms, ILU(1), 1.0 updates a pivot, 5.06 / 0.53; band 30 n=50,000 ILU(2), 2.2, 18.4
+// / 13.8; 2-D 200^2 ILU(3), 4.6, 0.99 / 2.38; 7-point 16^3 ILU(1), 3.5, 0.12 /
+// 0.26).
+int64_t plan_updates(int config) { return config < 2 ? 0 : config == 2 ? 1 : 3; }
+constexpr int64_t kPlanFlowUpdates = 2;
 constexpr int32_t kAdjointWaves = 512;
 constexpr int32_t kAdjointBatchWaves = 1024;  // batched reverse elimination (3-D 7-point 32^3 x16: 1.9 ms, 2.2 at 512)
 // wavefronts per incomplete inverse, more for shorter rows, whose polls are
@@ -508,12 +519,25 @@ size_t numeric_wrow_bytes(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch) {
            sizeof(double);
 }
 
+// The dataflow kernel rather than the pivot-serial one: rows with very short L
+// parts (a few pivots each) gain nothing from spreading a row over lanes and pay
+// for the extra staging; long update chains per entry (a lane walks its entry's
+// chain alone) are faster pivot by pivot with the lanes over that pivot's
+// updates.  Measured: random banded n=160,000 ILU(2) (1.7 updates per entry) 6.0
+// ms dataflow vs 22.9 ms pivot-serial; 27-point 50^3 ILU(2) and ILU(3) (16.5 and
+// 26 per entry) 20.8 and 38.7 ms dataflow vs 4.7 and 8.6 ms.
+bool auto_flow(tpilu_pattern pat) {
+    return (int64_t)pat->st.nnz_l >= kFlowMinL * pat->n && pat->n_updates < kFlowMaxChain * pat->nnz_f &&
+           pat->n < kFlowMaxWidth * std::max<int64_t>(pat->depth_l, 1);
+}
+
 // Phase II by the plan: the library's choice when nothing is asked for and
 // Phase I laid one down.  (In the LDS of one compute unit no row waits for a
 // published value, so the host-forced failure needs the other kernel.)
 bool numeric_by_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     return pat->nplan.plan && ctx->numeric == 0 && ctx->placement == 0 && !ctx->grid_override &&
-           !(pat->nplan.ucum && ctx->skip_row >= 0);
+           !(pat->nplan.ucum && ctx->skip_row >= 0) &&
+           !(pat->flow && auto_flow(pat) && pat->n_updates < kPlanFlowUpdates * (int64_t)pat->st.nnz_l);
 }
 
 // wrow: numeric_wrow_bytes(ctx, pat, batch) bytes of device memory, or null
@@ -527,17 +551,7 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
         return fail(ctx, TPILU_E_INVAL, "numeric factorization supports rows of at most 6600 entries");
     if (batch == 1 && ctx->numeric == 1 && !pat->flow)
         return fail(ctx, TPILU_E_INVAL, "the rows of this pattern do not fit the dataflow numeric kernel");
-    // automatic choice: rows with very short L parts (a few pivots each) gain
-    // nothing from spreading a row over lanes and pay for the extra staging;
-    // long update chains per entry (a lane walks its entry's chain alone) are
-    // faster pivot by pivot with the lanes over that pivot's updates.
-    // Measured: random banded n=160,000 ILU(2) (1.7 updates per entry)
-    // 6.0 ms dataflow vs 22.9 ms pivot-serial; 27-point 50^3 ILU(2) and ILU(3)
-    // (16.5 and 26 per entry) 20.8 and 38.7 ms dataflow vs 4.7 and 8.6 ms.
-    const bool auto_flow = (int64_t)pat->st.nnz_l >= kFlowMinL * pat->n &&
-                           pat->n_updates < kFlowMaxChain * pat->nnz_f &&
-                           pat->n < kFlowMaxWidth * std::max<int64_t>(pat->depth_l, 1);
-    const bool flow = batch == 1 && pat->flow && (ctx->numeric == 1 || (ctx->numeric == 0 && auto_flow));
+    const bool flow = batch == 1 && pat->flow && (ctx->numeric == 1 || (ctx->numeric == 0 && auto_flow(pat)));
     // one XCD only when asked for: the factorization keeps many rows in flight
     // and needs the whole device (random banded n=160,000 ILU(2) ran 3x
     // slower on one XCD); there the grid is that XCD's resident maximum
@@ -947,16 +961,20 @@ tpilu_status build_inverse_sched(tpilu_ctx ctx, tpilu_pattern pat) {
 }
 
 // The plan of Phase II with several rows per wavefront.  Not laid down for
-// longer rows of few updates (general sparse matrices: random banded n=160,000
-// ILU(0), rows of up to 11, 0.07 updates per pivot, 1.14 ms by the plan against
-// 1.06); where there is no memory for it the other kernels do without.
+// longer rows of few updates (plan_updates); where there is no memory for it the
+// other kernels do without.
 //
 // Where it runs, measured (us, one XCD with 128 / 256 wavefronts / the device
 // with 2,048), by parts per level: 17 (2-D 400^2 ILU(1)) 984 / 1031 / 1514; 25
 // (7-point 24^3 ILU(1)) 215 / 241 / 266; 42 (2-D 1000^2 ILU(1)) 3295 / 2970 /
 // 3860; 172 (7-point 64^3 ILU(0)) 778 / 554 / 366; 196 (27-point 50^3 ILU(1)) 8551
-// / 4775 / 2253.
-constexpr int64_t kPlanXcdNarrow = 32, kPlanXcdParts = 64;
+// / 4775 / 2253.  One XCD from 16 levels on only: its launch outweighs fewer
+// (uniform random n=5,000 ILU(0), 11 levels, 39 us, on the device 30; n=3,000 ILU(1),
+// 12, 58 and 33).  The LDS of one compute unit for up to 10 parts a level, or 128 in
+// all (LDS / as above: 2-D 64^2 ILU(0), 4 parts, 75 / 93; 7-point 16^3 ILU(0), 11,
+// 66 / 60; uniform random n=3,000 ILU(1), 62, 85 / 33; diagonal n=16,000 142 / 21).
+constexpr int64_t kPlanXcdNarrow = 32, kPlanXcdParts = 64, kPlanXcdDepth = 16;
+constexpr int64_t kPlanLdsParts = 10, kPlanLdsSmall = 128;
 tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     NumericPlan& N = pat->nplan;
     if (N.config < 0) return TPILU_OK;
@@ -964,12 +982,13 @@ tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     const int32_t n = (int32_t)pat->n;
     N.nnz_u = pat->nnz_f - (int64_t)pat->st.nnz_l;
     const int64_t width = N.nparts / std::max<int64_t>(pat->depth_l, 1);
-    N.one_xcd = width <= kPlanXcdParts;
+    N.one_xcd = width <= kPlanXcdParts && pat->depth_l >= kPlanXcdDepth;
     N.waves = !N.one_xcd ? 2048 : width <= kPlanXcdNarrow ? 128 : 256;
     N.rec = (int4*)pat->take(sizeof(int4) * (size_t)n);
     uint8_t* plan = N.rec ? (uint8_t*)pat->take(numeric_plan_bytes(N.config) * (size_t)n) : nullptr;
     if (!plan) return TPILU_OK;
-    if (N.config <= 1 && N.nnz_u <= kLdsNumericU) {
+    if (N.config <= 1 && N.nnz_u <= kLdsNumericU &&
+        N.nparts <= std::max<int64_t>(kPlanLdsParts * pat->depth_l, kPlanLdsSmall)) {
         N.ucum = (int32_t*)pat->take(sizeof(int32_t) * (size_t)(n + 1));
         if (N.ucum) HIPCHK(ctx, launch_lower_before(n, pat->rpF, pat->diagF, N.ucum, s));
     }
@@ -1511,7 +1530,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         P->lsL.depth = P->depth_l;
         P->lsU.depth = P->depth_u;
     }
-    if (P->nplan.config >= 2 && nupd < nl_) P->nplan.config = -1;
+    if (nupd < plan_updates(P->nplan.config) * nl_) P->nplan.config = -1;
     if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return bail(ps);
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);
