@@ -140,6 +140,7 @@ constexpr int64_t kFlowMaxWidth = 64;
 // 0.26).
 int64_t plan_updates(int config) { return config < 2 ? 0 : config == 2 ? 1 : 3; }
 constexpr int64_t kPlanFlowUpdates = 2;
+constexpr int64_t kBatchPlanTasks = 200;
 constexpr int32_t kAdjointWaves = 512;
 constexpr int32_t kAdjointBatchWaves = 1024;  // batched reverse elimination (3-D 7-point 32^3 x16: 1.9 ms, 2.2 at 512)
 // wavefronts per incomplete inverse, more for shorter rows, whose polls are
@@ -577,11 +578,19 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
             return TPILU_OK;
         }
         const int shape = numeric_batch_plan_shape(pat->nplan, pat->st.max_row, pat->st.max_lrow);
-        if (batch > 1 && shape >= 0 && ctx->placement == 0) {
-            // tasks of a level; 1024 / 2048 wavefronts (ms): 2-D 128^2 ILU(2) x 256,
-            // 128 tasks, 0.96 / 0.98; ILU(1) x 64, 43, 0.57 / 0.61; ILU(2) x 1024, 512,
-            // 2.17 / 1.73
-            const int64_t wide = pat->n * ((batch + kWave - 1) / kWave) / std::max<int64_t>(pat->depth_l, 1);
+        // tasks of a level
+        const int64_t wide = pat->n * ((batch + kWave - 1) / kWave) / std::max<int64_t>(pat->depth_l, 1);
+        // Rows of 13 to 16 entries or more than 4 pivots: their registers leave two
+        // wavefronts to a SIMD, so where no level waits, or there is little to
+        // update, k_numeric_batch is the faster one (us, here / there: 7-point ILU(1)
+        // 32^3 x 16, 175 tasks, 695 / 735, 48^3 x 16, 390, 1705 / 1424, 32^3 x 256,
+        // 700, 1845 / 1431; blocks of 8 x 40, 250, 43 / 40, 2,500, 232 / 154; uniform
+        // random ILU(0), no updates, 2,000 rows x 30, 100, 53 / 49, 20,000 x 70 435 /
+        // 225)
+        const bool many = shape == 2 && (wide > kBatchPlanTasks || pat->n_updates < (int64_t)pat->st.nnz_l);
+        if (batch > 1 && shape >= 0 && !many && ctx->placement == 0) {
+            // 1024 / 2048 wavefronts (ms): 2-D 128^2 ILU(2) x 256, 128 tasks, 0.96 /
+            // 0.98; ILU(1) x 64, 43, 0.57 / 0.61; ILU(2) x 1024, 512, 2.17 / 1.73
             const int32_t waves = ctx->grid_override ? ctx->grid_override : wide <= 256 ? 1024 : 2048;
             HIPCHK(ctx, launch_numeric_batch_plan(pdev(ctx, pat), pat->nplan, shape, a_val, batch, f_val, ctx->fused,
                                                   ctl, ctx->spin_limit, ctx->skip_row, waves, b, x, ctx->stream));

@@ -110,3 +110,21 @@ def test_factorization(name, make, k):
     asked.append(_least(run))
     assert_bits_equal(f, vF, "F as asked for")
     _compare(auto, asked, name)
+
+
+@pytest.mark.parametrize("name,make,k,batch", [
+    ("uniform", lambda: _uniform(20000, 8), 0, 70), ("blocks of 8", lambda: _blocks(2500, 8), 0, 40),
+    ("7-point", lambda: inputs.conv_diff_3d(16, 1.0, np.ones(3)), 1, 70)])
+def test_batch(name, make, k, batch):
+    A = make()
+    rp, ci, _ = oracle.symbolic(A.n, A.rowptr, A.col, k)
+    vals = A.val[:, None] * np.random.default_rng(4).uniform(0.5, 1.0, (1, batch))
+    pat, a, ctx = T.symbolic(g(A.rowptr), g(A.col), k), g(np.ascontiguousarray(vals)), T.context(0)
+    f = T.numeric(pat, a)
+    for i in (0, batch - 1):
+        vF, _ = oracle.numeric(A.n, A.rowptr, A.col, np.ascontiguousarray(vals[:, i]), rp, ci)
+        assert_bits_equal(f[:, i].contiguous(), vF, f"F instance {i}")
+    run = lambda: T.numeric(pat, a, out=f, check=False)  # noqa: E731
+    auto = _least(run)
+    ctx.set_placement(ctx.PLACE_DEVICE)
+    _compare(auto, [_least(run)], name)
