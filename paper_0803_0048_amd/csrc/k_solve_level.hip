@@ -118,6 +118,10 @@ typedef __attribute__((address_space(3))) volatile int32_t LdsInt;
 // latency never sits between two levels.  Entries past a row's end multiply
 // +0.0 by the +0.0 kept in xs[n], which leaves every running difference as it
 // is, its sign of zero included.
+// kKeepX: the caller sees x.  Rows of the first level have no entries, and their
+// x is b to the bit, where the +0.0 subtracted makes a signalling NaN quiet.  (In
+// instances of its own: beside any code for it the loop is a few percent slower,
+// 2-D 64^2 ILU(1) 76 -> 78 us.)
 template <bool kBackward, int KE, bool kKeepX>
 __device__ __forceinline__ void lds_sweep(const LevelSched& L, const double* __restrict__ F,
                                           const int32_t* __restrict__ ci, const double* __restrict__ in, double* out,
@@ -164,6 +168,8 @@ __device__ __forceinline__ void lds_sweep(const LevelSched& L, const double* __r
         if (act) xs[r.x] = a;
         // the wavefront's LDS operations complete in order: the count rises after the values are there
         if (lane == 0) __hip_atomic_fetch_add((int32_t*)done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (kKeepX && !kBackward)
+            if (uniform(h.z) == 0) a = s;  // the first level
         if (act && out) out[r.x] = a;
         trace_mark_lane(trace, tr0 + n + r.x, act);
         c += waves;
@@ -174,17 +180,6 @@ __device__ __forceinline__ void lds_sweep(const LevelSched& L, const double* __r
         r1 = chunk_rec(L, h1);
         h2 = chunk_head(L, c + 2 * waves);
     }
-    // Rows of the first level have no entries, and their x is b to the bit; the
-    // +0.0 subtracted above makes a signalling NaN quiet.  Done again for callers
-    // that see x, in instances of their own: the loop above is a few percent slower
-    // beside any code for it (2-D 64^2 ILU(1) 76 -> 78 us).
-    if constexpr (kKeepX && !kBackward)
-        for (c = uniform((int32_t)(threadIdx.x / kWave)); c < L.nchunk; c += waves) {
-            h = chunk_head(L, c);
-            if (uniform(h.z) != 0) break;
-            r = chunk_rec(L, h);
-            if (r.z >= 0) out[r.x] = sanitize_input(in[r.x], ctl);
-        }
 }
 
 template <int KE, bool kKeepX>
