@@ -273,13 +273,17 @@ struct DeviceGuard {
 // it but runs the group's rows back to back, which costs a whole row time per
 // level where a row waits on earlier levels: random banded n=160,000 ILU(2)
 // factorization 8.5 -> 147 ms at 2 rows, 27-point 50^3 ILU(1) solves (196 rows
-// per level) 1.61 -> 4.27 ms at 2.  Only the inverses gain, on wide levels
-// (7-point 64^3 ILU(1), 692 rows per level: 6.6 -> 4.0 ms at 2 rows).
+// per level) 1.61 -> 4.27 ms at 2.  The inverses gain on wide levels (7-point 64^3
+// ILU(1), 692 rows per level: 6.6 -> 4.0 ms at 2 rows), the solves on levels of
+// about twice the wavefronts (7-point 128^3 ILU(0), 5,489 rows: 4.35 -> 3.78 ms
+// forward at 3; block-diagonal, blocks of 64, 2,000 rows: 0.345 -> 0.297).
 enum class RowKernel { Numeric, Solve, Inverse };
 
 int32_t row_group(RowKernel kind, int64_t n, int64_t depth) {
-    if (depth <= 0 || kind != RowKernel::Inverse) return 1;
-    return std::max<int64_t>(n, 1) / depth >= 512 ? 2 : 1;
+    if (depth <= 0 || kind == RowKernel::Numeric) return 1;
+    const int64_t width = std::max<int64_t>(n, 1) / depth;
+    if (kind == RowKernel::Solve) return width >= 2000 ? 3 : 1;
+    return width >= 512 ? 2 : 1;
 }
 
 // Wavefronts of the batched kernels (a task is one row for 64 instances).
@@ -612,10 +616,24 @@ tpilu_status enqueue_numeric(tpilu_ctx ctx, tpilu_pattern pat, const double* a_v
 // Automatic choice: the shape of the smallest estimated time (one sweep, ns),
 // from the structure alone.  The estimates are fits to measurements on MI355X
 // (us per sweep, estimated / measured):
-//   chunks  a cost per dependency level by the longest row half (450 up to 4
-//           entries, 600 up to 8, 970 per 16 beyond) + 30 per chunk: 2-D 400^2
-//           ILU(1) 654 / 580, 7-point 64^3 ILU(1) 361 / 385, ILU(2) 816 / 827,
-//           27-point 50^3 ILU(0) 403 / 426
+//   chunks  a cost per dependency level by the longest row half (450 up
+//           to 4 entries, 600 up to 8, 970 per 16 beyond) + one per chunk (14 for
+//           no entries, 18 up to 4, 28 up to 8, 32 up to 16, 14 + 2.2 per entry of
+//           the rounds of 16 beyond): 7-point 100^3 ILU(0) 415 / 472, ILU(2) 1562 /
+//           1740, 27-point 90^3 ILU(0) 975 / 1083, 64 levels of 16,000 random rows
+//           of 8 entries 491 / 479, of 20 1473 / 1419
+//   lanes   on the whole device: 13 + 2.4 per entry of an average half for each 64
+//           rows, but no less than a level's wait (1850 + 150 per entry up to 8,
+//           400 beyond; 2400 where the rows depend on near neighbours only):
+//           diagonal n=8,000,000 1664 / 1755 (chunks 1755 / 2310), block-diagonal,
+//           blocks of 8 / 24 / 64: 134 / 136, 305 / 264, 177 / 163 (by chunks 198,
+//           476; a wavefront per row 369).  Only where a level fills the 128
+//           wavefronts or the rows are of that local kind: with fewer chunks a
+//           level it is the slower one (uniform random n=160,000 ILU(0), 114: 92,
+//           by chunks 81)
+//           Chunks and lanes both lose once the arrays pass the memory-side
+//           cache (14 and 11 more): 7-point 160^3 ILU(0) 2263 / 2380 and 1997 /
+//           2060, 100^3 ILU(2) by chunks 1781 / 1740
 //   blocks  230 per block + 118 per round of its walk, at least 0.115 per
 //           entry (one XCD's loads): random banded n=160,000 ILU(1) 1519 /
 //           1480, ILU(2) 3207 / 3200, n=10,000 ILU(2) 266 / 280, paper-scale
@@ -633,7 +651,20 @@ struct SolveShape {
 int64_t chunk_level_ns(int32_t half) {
     return half <= 4 ? 450 : half <= 8 ? 600 : 970 * std::max<int64_t>(1, ((int64_t)half + 15) / 16);
 }
-constexpr int64_t kChunkNs = 30;
+double chunk_ns(int32_t half) {
+    if (half > 16) return 14.0 + 2.2 * (double)(((int64_t)half + 15) / 16 * 16);
+    return half > 8 ? 32.0 : half > 4 ? 28.0 : half > 0 ? 18.0 : 14.0;
+}
+// the lane-per-row kernel: average entries of a row half, only near neighbours among them
+double lane_level_ns(double half, bool local) {
+    return local ? 2400.0 : 1850.0 + 150.0 * std::min(half, 8.0) + 400.0 * std::max(half - 8.0, 0.0);
+}
+constexpr double kLaneNs = 13.0, kLaneEntryNs = 2.4;
+constexpr double kFarChunkNs = 14.0, kFarLaneNs = 11.0;  // more for arrays beyond kFarBytes
+constexpr int64_t kFarBytes = 200000000;
+constexpr int64_t kLaneChunks = 120, kLaneChunksFar = 64;  // least chunks a level
+constexpr double kLaneGain = 0.95;
+constexpr int64_t kLaunchNs = 5000;  // the other kernels' launch over that of the lanes (diagonal n=16,000: 14 and 7 us)
 constexpr int64_t kBlockNs = 230, kBlockRoundNs = 118;
 constexpr double kBlockEntryNs = 0.115;
 constexpr int64_t kRowLevelXcdNs = 700, kRowLevelNs = 1150;
@@ -682,13 +713,26 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
         const int64_t blocks = (n + 63) / 64;
         const int64_t t_row = one_xcd ? depth * kRowLevelXcdNs
                                       : std::max(depth * kRowLevelNs, (int64_t)((double)n * kRowNs));
+        const int64_t nchunk = (backward ? pat->lsU : pat->lsL).nchunk;
+        const double avg = (double)half / (double)n;
+        const bool far = 12 * pat->nnz_f + 32 * n > kFarBytes;
         const int64_t t_chunks =
-            depth * chunk_level_ns(longest) + (backward ? pat->lsU : pat->lsL).nchunk * kChunkNs;
+            depth * chunk_level_ns(longest) +
+            (int64_t)((double)nchunk * (chunk_ns(longest) + (far ? kFarChunkNs : 0.0)));
+        const int32_t win = backward ? pat->bst.max_win_u : pat->bst.max_win_l;
+        const bool local = longest == win;  // (the longest row half, to go by, lies in its window)
+        const int64_t t_lanes =
+            local || nchunk >= depth * (far ? kLaneChunksFar : kLaneChunks)
+                ? (int64_t)std::max((double)nchunk * (kLaneNs + kLaneEntryNs * avg + (far ? kFarLaneNs : 0.0)),
+                                    (double)depth * lane_level_ns(avg, local))
+                : INT64_MAX;
         const int64_t rounds2 = (int64_t)(backward ? pat->bst.rounds_u : pat->bst.rounds_l);
-        const int64_t t_blocks = (backward ? pat->bst.max_win_u : pat->bst.max_win_l) > kWinEntries
+        const int64_t t_blocks = win > kWinEntries
                                      ? INT64_MAX
                                      : std::max(blocks * kBlockNs + rounds2 * kBlockRoundNs / 2,
                                                 (int64_t)((double)half * kBlockEntryNs));
+        if (t_lanes < t_blocks && (double)t_lanes < kLaneGain * (double)(std::min(t_row, t_chunks) + kLaunchNs))
+            return {-kLaneWaves, false};
         if (t_blocks < t_row && t_blocks <= t_chunks) return {kBlockGroups, true, SolveKind::Blocks};
         // chunks in work at a time: the ones of about eight levels (both sweeps,
         // 24 / 48 / 96 / 192 wavefronts: 7-point 64^3 ILU(0), 21 chunks a level, 0.64 /

@@ -112,6 +112,29 @@ def test_factorization(name, make, k):
     _compare(auto, asked, name)
 
 
+@pytest.mark.parametrize("name,make", [
+    ("diagonal", lambda: _diagonal(16000)), ("blocks of 8", lambda: _blocks(12500, 8)),
+    ("blocks of 24", lambda: _blocks(8000, 24)), ("blocks of 64", lambda: _blocks(2000, 64)),
+    ("layers 8000 x 3", lambda: _layers(64000, 8000, 3)), ("layers 8000 x 20", lambda: _layers(64000, 8000, 20)),
+    ("uniform", lambda: _uniform(50000, 12))])
+def test_solve(name, make):
+    A = make()
+    rp, ci, _, vF, _ = oracle.ilu(A, 0)
+    b = np.random.default_rng(2).standard_normal(A.n)
+    pat, f, bt, ctx = T.symbolic(g(A.rowptr), g(A.col), 0), g(vF), g(b), T.context(0)
+    x_ref, y_ref = oracle.apply(A.n, rp, ci, vF, b)
+    y, x = T.apply(pat, f, bt, return_x=True)
+    assert_bits_equal(x, x_ref, "x")
+    assert_bits_equal(y, y_ref, "y")
+    run = lambda: T.apply(pat, f, bt)  # noqa: E731
+    auto, asked = _least(run), []
+    for mode in (ctx.SOLVER_DEVICE, ctx.SOLVER_LANES):
+        ctx.set_solver(mode)
+        asked.append(_least(run))
+        assert_bits_equal(run(), y_ref, f"y, solver {mode}")
+    _compare(auto, asked, name)
+
+
 @pytest.mark.parametrize("name,make,k,batch", [
     ("uniform", lambda: _uniform(20000, 8), 0, 70), ("blocks of 8", lambda: _blocks(2500, 8), 0, 40),
     ("7-point", lambda: inputs.conv_diff_3d(16, 1.0, np.ones(3)), 1, 70)])
