@@ -31,7 +31,7 @@ __global__ __launch_bounds__(64) void k_spmv(int32_t n, const int64_t* __restric
         [&](int32_t i, double s) { y[i] = b_minus ? b_minus[i] - s : s; });
 }
 
-hipError_t launch_spmv(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const double* v,
+hipError_t launch_spmv(int32_t n, int64_t nnz, int32_t longest, const int64_t* rp, const int32_t* ci, const double* v,
                        const double* x, const double* b_minus, double* y, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     auto go = [&](auto kern, int rows) {
@@ -41,7 +41,15 @@ hipError_t launch_spmv(int32_t n, int64_t nnz, const int64_t* rp, const int32_t*
     // 8, 16 or 32 entries a round (us a call, launch included, random banded
     // 11.2 / 10.7 / 12.9; 7-point 110^3 30.5 / 32.7 / 54.3; 27-point 50^3 16.5 /
     // 15.0 / 11.3)
-    if (nnz <= 8 * (int64_t)n) go(k_spmv<8, 64>, 64);
+    // and fewer for the shortest rows (1 / 4 / 8: diagonal n=8,000,000, nnz = n, 46 /
+    // 69 / 101; bidiagonal n=4,000,000 34 / 32 / 38; tridiagonal n=1,000,000 14.5 /
+    // 12.1 / 13.2), unless a long row sets the time (one of 6,000 entries 765 with
+    // 4, 640 with 8, 351 with 32)
+    const bool uneven = longest >= 1024 && (int64_t)longest * 64 >= nnz;
+    if (nnz <= n) go(k_spmv<1, 64>, 64);
+    else if (uneven) go(k_spmv<32, 16>, 16);
+    else if (nnz <= 3 * (int64_t)n && longest <= 64) go(k_spmv<4, 64>, 64);
+    else if (nnz <= 8 * (int64_t)n) go(k_spmv<8, 64>, 64);
     else if (nnz <= 20 * (int64_t)n) go(k_spmv<16, 32>, 32);
     else go(k_spmv<32, 16>, 16);
     return hipGetLastError();

@@ -296,7 +296,8 @@ constexpr int kDotLanes = 16384;  // fixed shape of every inner product
 constexpr int kDotBlocks = 64;
 constexpr int kDotThreads = 256;
 
-hipError_t launch_spmv(int32_t n, int64_t nnz, const int64_t* rp, const int32_t* ci, const double* v,
+// longest: no row has more entries
+hipError_t launch_spmv(int32_t n, int64_t nnz, int32_t longest, const int64_t* rp, const int32_t* ci, const double* v,
                        const double* x, const double* b_minus, double* y, hipStream_t s);
 hipError_t launch_dot_partial(int64_t n, const double* x, const double* y, double* partial,
                               hipStream_t s);

@@ -1769,7 +1769,7 @@ extern "C" TPILU_API tpilu_status tpilu_spmv(tpilu_ctx ctx, tpilu_pattern pat, c
     tpilu_status st = check_common(ctx, pat, 1);
     if (st) return st;
     DeviceGuard dg(ctx->device);
-    HIPCHK(ctx, launch_spmv((int32_t)pat->n, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, nullptr, y, ctx->stream));
+    HIPCHK(ctx, launch_spmv((int32_t)pat->n, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, x, nullptr, y, ctx->stream));
     return TPILU_OK;
 }
 
@@ -1979,7 +1979,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
     int32_t it_host = 0;
     bool reset = true;
     for (;;) {
-        HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, w, s));
+        HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, x, b, w, s));
         HIPCHK(ctx, launch_dot_partial(n, w, w, partial, s));
         HIPCHK(ctx, launch_dot_final(partial, scal + 1, 1, s));
         double beta = 0.0;
@@ -1993,7 +1993,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
             tpilu_status se = enqueue_precond(ctx, pat, f_val, inverse, V + (size_t)j * nn, z, t, reset, iflags + 1);
             reset = false;
             if (se) return se;
-            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, z, nullptr, w, s));
             const GmStep step{n, V, w, H, cs, sn, g, m, j, tol, iflags, maxit, dhist, ctx->flags,
                               ++ctx->gm_launched, pat->ctl};
             HIPCHK(ctx, launch_gm_step(step, partial, s));
@@ -2024,7 +2024,7 @@ tpilu_status gmres_impl(tpilu_ctx ctx, tpilu_pattern pat, const double* a_val, c
         if (st) return st;
         HIPCHK(ctx, launch_axpy1(n, x, z, s));
     }
-    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, w, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, x, b, w, s));
     HIPCHK(ctx, launch_dot_partial(n, w, w, partial, s));
     HIPCHK(ctx, launch_dot_final(partial, scal + 2, 1, s));
     double rn = 0.0;
@@ -2099,7 +2099,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
     }
     const double tol = rtol * bnorm;
     // r = b - A x, rs = r, p = v = 0, rho = alpha = omega = 1
-    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, r, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, x, b, r, s));
     HIPCHK(ctx, launch_copy(rs, r, n, s));
     {
         const double init[8] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 0.0, 0.0};
@@ -2127,7 +2127,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
             st = enqueue_precond(ctx, pat, m_val, inv, p, ph, tmp, reset);
             reset = false;
             if (st) return st;
-            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, ph, nullptr, v, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, ph, nullptr, v, s));
             HIPCHK(ctx, launch_dot_partial(n, rs, v, pa, s));
             HIPCHK(ctx, launch_bi(kBiOpAlpha, n, 0, pa, nullptr, sc, nullptr, nullptr, nullptr, nullptr, nullptr,
                                   nullptr, s));
@@ -2154,7 +2154,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
             }
             st = enqueue_precond(ctx, pat, m_val, inv, sv, sh, tmp, false);
             if (st) return st;
-            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, sh, nullptr, t, s));
+            HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, sh, nullptr, t, s));
             HIPCHK(ctx, launch_dot_partial(n, t, sv, pa, s));
             HIPCHK(ctx, launch_dot_partial(n, t, t, pb, s));
             HIPCHK(ctx, launch_bi(kBiOpOmega, n, 0, pa, pb, sc, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -2185,7 +2185,7 @@ extern "C" TPILU_API tpilu_status tpilu_bicgstab(tpilu_ctx ctx, tpilu_pattern pa
         }
     }
     // true residual
-    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->rpA, pat->ciA, a_val, x, b, tmp, s));
+    HIPCHK(ctx, launch_spmv(ni, pat->nnz_a, pat->st.max_row, pat->rpA, pat->ciA, a_val, x, b, tmp, s));
     double rn = 0.0;
     st = nrm(tmp, &rn);
     if (st) return st;
