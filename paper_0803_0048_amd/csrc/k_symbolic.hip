@@ -699,6 +699,7 @@ hipError_t launch_a2f(int32_t n, const int64_t* rpA, const int32_t* ciA, const i
 // ------------------------------------------------------------------------------------
 constexpr int kSchedAhead = 4;    // rounds of candidates loaded together
 constexpr int kSchedQueue = 128;  // candidates that passed the filter, a ring
+constexpr size_t kSchedStaticLds = kSchedQueue * 9 + kWave * 4;  // qt, qq, qp, pcnt of k_sched
 
 // filter bits for rows of up to max_row entries (rows too long for the LDS
 // beside a larger one get a small one, and search nearly every candidate)
@@ -966,6 +967,9 @@ hipError_t launch_sched(int32_t n, const int64_t* rpF, const int32_t* ciF, const
                         int32_t stride) {
     const int32_t bits = sched_filter_bits(max_row);
     const size_t lds = (size_t)std::max(max_row, 1) * sizeof(int32_t) + (size_t)bits / 8;
+    // a workgroup's LDS, the queue and the counts included (a little more ends the
+    // queue instead of failing the launch)
+    if (lds + kSchedStaticLds > 160 * 1024) return hipErrorInvalidValue;
     stride = max(stride, 1);
     const int32_t split = mode == 3 ? kSchedSampleSplit : 1;
     const int64_t tasks = ((int64_t)n + stride - 1) / stride * split;
