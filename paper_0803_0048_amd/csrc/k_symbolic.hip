@@ -1267,6 +1267,10 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
         uint32_t polls = 0;
         uint64_t t0 = 0;
         int idle = 0;
+        // the first kLaneBatch dependencies not known yet; they stay as they are
+        // until one of them has come
+        int32_t id[kLaneBatch], c[kLaneBatch];
+        bool fresh = true;
         auto level_of = [&](int32_t c) {
             const uint32_t x = (uint32_t)(J.desc ? first - c : c - first);  // its lane, if below 64
             int32_t v;
@@ -1277,15 +1281,17 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
         for (;;) {
             bool prog = false;
             if (!done) {
-                // the first kLaneBatch dependencies not known yet, all loads in flight together
-                int32_t id[kLaneBatch], c[kLaneBatch], v[kLaneBatch];
-                uint64_t m = open;
+                if (fresh) {
+                    uint64_t m = open;
 #pragma unroll
-                for (int u = 0; u < kLaneBatch; ++u) {
-                    id[u] = m ? __builtin_ctzll(m) : -1;
-                    m &= m - 1ull;
-                    c[u] = id[u] >= 0 ? ciF[q + id[u]] : first;
+                    for (int u = 0; u < kLaneBatch; ++u) {
+                        id[u] = m ? __builtin_ctzll(m) : -1;
+                        m &= m - 1ull;
+                        c[u] = id[u] >= 0 ? ciF[q + id[u]] : first;
+                    }
+                    fresh = false;
                 }
+                int32_t v[kLaneBatch];  // all loads in flight together
 #pragma unroll
                 for (int u = 0; u < kLaneBatch; ++u) v[u] = id[u] >= 0 ? level_of(c[u]) : -1;
 #pragma unroll
@@ -1295,6 +1301,7 @@ __global__ __launch_bounds__(64) void k_depth_lanes(int32_t n, LevelJob j0, Leve
                         open &= ~(1ull << id[u]);
                         prog = true;
                     }
+                fresh = prog;
                 if (open == 0ull) {
                     q += kWave;
                     open = window(q);
