@@ -139,6 +139,11 @@ constexpr int64_t kFlowMaxWidth = 64;
 // / 13.8; 2-D 200^2 ILU(3), 4.6, 0.99 / 2.38; 7-point 16^3 ILU(1), 3.5, 0.12 /
 // 0.26).
 int64_t plan_updates(int config) { return config < 2 ? 0 : config == 2 ? 1 : 3; }
+// A wavefront has one row of more than 32 entries, as in the kernel for any row;
+// on levels of as many rows as there are wavefronts that one is no slower (blocks
+// of 20 / 24, 3,000 rows a level, 213 / 191 and 267 / 240 us; 27-point 110^3
+// ILU(1), 938, 7.8 / 11.5 ms).
+constexpr int64_t kPlanWideRows = 2000;
 constexpr int64_t kPlanFlowUpdates = 2;
 constexpr int64_t kBatchPlanTasks = 200;
 constexpr int32_t kAdjointWaves = 512;
@@ -1583,7 +1588,9 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         P->lsL.depth = P->depth_l;
         P->lsU.depth = P->depth_u;
     }
-    if (nupd < plan_updates(P->nplan.config) * nl_) P->nplan.config = -1;
+    if (nupd < plan_updates(P->nplan.config) * nl_ ||
+        (P->nplan.config == 3 && n >= kPlanWideRows * (int64_t)P->depth_l))
+        P->nplan.config = -1;
     if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return bail(ps);
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);

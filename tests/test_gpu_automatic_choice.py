@@ -95,7 +95,7 @@ def _compare(auto, asked, what):
     ("layers 30 x 8", lambda: _layers(20000, 30, 8), 0), ("band 300", lambda: _banded(60000, 300, 7), 0),
     ("band 100 ILU(1)", lambda: _banded(50000, 100, 4), 1), ("band 300 ILU(1)", lambda: _banded(60000, 300, 3), 1),
     ("diagonal", lambda: _diagonal(16000), 0), ("blocks of 8", lambda: _blocks(500, 8), 0),
-    ("uniform", lambda: _uniform(3000, 2), 1), ("2-D", lambda: inputs.conv_diff_2d(40, 1.0, 1.0, 2.0), 2)])
+    ("uniform", lambda: _uniform(3000, 2), 1), ("blocks of 24", lambda: _blocks(3000, 24), 0), ("2-D", lambda: inputs.conv_diff_2d(40, 1.0, 1.0, 2.0), 2)])
 def test_factorization(name, make, k):
     A = make()
     rp, ci, _, vF, _ = oracle.ilu(A, k)
