@@ -699,7 +699,8 @@ bool solve_auto(tpilu_ctx ctx) { return ctx->solver == 0 && ctx->placement == 0 
 
 bool solve_in_lds(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch) {
     const int32_t half = std::max(pat->st.max_lrow, pat->st.max_upart);
-    return batch == 1 && solve_auto(ctx) && pat->n <= kLdsSolveRows && half <= kLdsSolveHalf &&
+    return batch == 1 && solve_auto(ctx) && pat->n <= kLdsSolveRows && half <= kLdsSolveHalf && pat->lsL.rec &&
+           pat->lsU.rec &&
            pat->nnz_f * kLdsEntryNs <= ((int64_t)pat->depth_l + pat->depth_u) * chunk_level_ns(half);
 }
 
@@ -718,12 +719,14 @@ SolveShape solve_shape(tpilu_ctx ctx, tpilu_pattern pat, int32_t batch, bool bac
         const int64_t blocks = (n + 63) / 64;
         const int64_t t_row = one_xcd ? depth * kRowLevelXcdNs
                                       : std::max(depth * kRowLevelNs, (int64_t)((double)n * kRowNs));
-        const int64_t nchunk = (backward ? pat->lsU : pat->lsL).nchunk;
+        const LevelSched& ls = backward ? pat->lsU : pat->lsL;
+        const int64_t nchunk = ls.rec ? ls.nchunk : n / 64 + depth;
         const double avg = (double)half / (double)n;
         const bool far = 12 * pat->nnz_f + 32 * n > kFarBytes;
         const int64_t t_chunks =
-            depth * chunk_level_ns(longest) +
-            (int64_t)((double)nchunk * (chunk_ns(longest) + (far ? kFarChunkNs : 0.0)));
+            ls.rec ? depth * chunk_level_ns(longest) +
+                         (int64_t)((double)nchunk * (chunk_ns(longest) + (far ? kFarChunkNs : 0.0)))
+                   : INT64_MAX / 2;
         const int32_t win = backward ? pat->bst.max_win_u : pat->bst.max_win_l;
         const bool local = longest == win;  // (the longest row half, to go by, lies in its window)
         const int64_t t_lanes =
@@ -826,6 +829,15 @@ tpilu_status enqueue_apply(tpilu_ctx ctx, tpilu_pattern pat, const double* f_val
 
 // temporaries released when the enclosing call returns
 using TmpBufs = Arena;
+
+// rows from which the chunk heads are copied to arrays of their number (16 bytes a
+// row and list saved; three copies cost 15 us)
+constexpr int64_t kHeadsCopyRows = 1 << 16;
+// The plan of Phase II takes 72 to 2,368 bytes a row: from kPlanCheckBytes on it
+// is laid down only where it takes no more than one part in kPlanFreeParts of
+// the free device memory (a look at that costs some 20 us).
+constexpr size_t kPlanCheckBytes = size_t(64) << 20;
+constexpr size_t kPlanFreeParts = 16;
 
 // Per F slot, the level-order position of the row its column names, for the
 // one-CU solves.
@@ -1038,12 +1050,17 @@ tpilu_status build_numeric_plan(tpilu_ctx ctx, tpilu_pattern pat) {
     if (N.config < 0) return TPILU_OK;
     hipStream_t s = ctx->stream;
     const int32_t n = (int32_t)pat->n;
+    const size_t bytes = numeric_plan_bytes(N.config) * (size_t)n;
+    if (bytes >= kPlanCheckBytes) {
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / kPlanFreeParts) return TPILU_OK;
+    }
     N.nnz_u = pat->nnz_f - (int64_t)pat->st.nnz_l;
     const int64_t width = N.nparts / std::max<int64_t>(pat->depth_l, 1);
     N.one_xcd = width <= kPlanXcdParts && pat->depth_l >= kPlanXcdDepth;
     N.waves = !N.one_xcd ? 2048 : width <= kPlanXcdNarrow ? 128 : 256;
     N.rec = (int4*)pat->take(sizeof(int4) * (size_t)n);
-    uint8_t* plan = N.rec ? (uint8_t*)pat->take(numeric_plan_bytes(N.config) * (size_t)n) : nullptr;
+    uint8_t* plan = N.rec ? (uint8_t*)pat->take(bytes) : nullptr;
     if (!plan) return TPILU_OK;
     if (N.config <= 1 && N.nnz_u <= kLdsNumericU &&
         N.nparts <= std::max<int64_t>(kPlanLdsParts * pat->depth_l, kPlanLdsSmall)) {
@@ -1351,8 +1368,10 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     const int32_t ni = (int32_t)n;
     // ---- a2: level-of-fill pattern, count pass
     TmpBufs T(P->al);
-    // counts, tier lists, and the two level orders' temporaries (enqueue_levels)
-    T.reserve((size_t)n * (4 + 4 * kSymTiers + 1 + 2 * (8 + 8)) + 3 * 8 * scan_tmp_elems(n) + sizeof(Ctl) + 24 * 256);
+    // counts, tier lists, the two level orders' temporaries (enqueue_levels) and,
+    // for larger systems, their chunk heads
+    const bool keep_heads = n < kHeadsCopyRows;
+    T.reserve((size_t)n * (4 + 4 * kSymTiers + 1 + 2 * (8 + 8) + (keep_heads ? 0 : 3 * 16)) + 3 * 8 * scan_tmp_elems(n) + sizeof(Ctl) + 24 * 256);
     int32_t* cnt = (int32_t*)T.get(sizeof(int32_t) * (size_t)n);
     SymLists lists{};
     lists.n = ni;
@@ -1400,7 +1419,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     trace("symbolic: fill pass, nnz(F)", nnzf);
     // F's columns, levels, lsd and sptr; per row diagF, the levels' orders,
     // chunks and windows; a2f
-    P->arrays.reserve((size_t)nnzf * 17 + (size_t)n * (4 + 16 + 64 + 2) + (size_t)nnz * 4 + 16 * 256);
+    P->arrays.reserve((size_t)nnzf * 17 + (size_t)n * (4 + 16 + (keep_heads ? 64 : 32) + 2) + (size_t)nnz * 4 + 16 * 256);
     P->ciF = (int32_t*)P->take(sizeof(int32_t) * (size_t)nnzf);
     P->lvF = (uint8_t*)P->take((size_t)nnzf);
     P->diagF = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
@@ -1452,15 +1471,21 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     for (int q = 0; q < 2; ++q) {
         LevelSched& L = q == 0 ? P->lsL : P->lsU;
         ljobs[q].rec = (int4*)P->take(sizeof(int4) * (size_t)n);
-        ljobs[q].head = (int4*)P->take(sizeof(int4) * (size_t)n);  // at most one chunk per position
-        if (!ljobs[q].rec || !ljobs[q].head) return bail(fail(ctx, TPILU_E_NOMEM, "level chunks"));
+        // at most one chunk per position; what there is goes to the pattern afterwards
+        ljobs[q].head = (int4*)(keep_heads ? P->take(sizeof(int4) * (size_t)n) : T.get(sizeof(int4) * (size_t)n));
+        if (!ljobs[q].rec || !ljobs[q].head) {
+            // no memory for the chunks: the solves do without
+            ljobs[q].rec = ljobs[q].head = nullptr;
+            continue;
+        }
         ljobs[q].nchunk = &L.nchunk;
         L.rec = ljobs[q].rec;
         L.head = ljobs[q].head;
     }
-    P->nplan.config = numeric_plan_config(P->st.max_row, P->st.max_lrow);
+    P->nplan.config = ljobs[0].rec ? numeric_plan_config(P->st.max_row, P->st.max_lrow) : -1;
     if (P->nplan.config >= 0) {
-        ljobs[0].part = P->nplan.part = (int4*)P->take(sizeof(int4) * (size_t)n);
+        ljobs[0].part = P->nplan.part =
+            (int4*)(keep_heads ? P->take(sizeof(int4) * (size_t)n) : T.get(sizeof(int4) * (size_t)n));
         if (!P->nplan.part) P->nplan.config = -1;
     }
     if (P->nplan.config >= 0) {
@@ -1591,6 +1616,25 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     if (nupd < plan_updates(P->nplan.config) * nl_ ||
         (P->nplan.config == 3 && n >= kPlanWideRows * (int64_t)P->depth_l))
         P->nplan.config = -1;
+    if (!keep_heads) {
+        // the heads in arrays of their number: they came in arrays of n
+        auto own = [&](const int4*& p, int32_t count) -> hipError_t {
+            if (!p) return hipSuccess;
+            int4* q = (int4*)P->take(sizeof(int4) * (size_t)std::max(count, 1));
+            const hipError_t e =
+                q ? hipMemcpyAsync(q, p, sizeof(int4) * (size_t)count, hipMemcpyDeviceToDevice, s) : hipSuccess;
+            p = q;
+            return e;
+        };
+        HIPCHK(ctx, own(P->lsL.head, P->lsL.nchunk));
+        HIPCHK(ctx, own(P->lsU.head, P->lsU.nchunk));
+        const int4* part = P->nplan.config >= 0 ? P->nplan.part : nullptr;
+        HIPCHK(ctx, own(part, P->nplan.nparts));
+        P->nplan.part = const_cast<int4*>(part);
+        if (!P->lsL.head || !part) P->nplan.config = -1;
+        if (!P->lsL.head) P->lsL.rec = nullptr;
+        if (!P->lsU.head) P->lsU.rec = nullptr;
+    }
     if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return bail(ps);
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
     if (st != TPILU_OK) return bail(st);

@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -32,14 +33,14 @@ class _Capped:
     when memory is short, its error left behind.  (Only calls that cannot raise:
     a callback that raises leaves its result undefined.)"""
 
-    def __init__(self, cap):
-        self.cap, self.live, self.refused = cap, set(), []
+    def __init__(self, cap, but=()):
+        self.cap, self.but, self.live, self.refused = cap, but, set(), []
         self.hip = _hip()
         self.alloc, self.free = ALLOC_FN(self._alloc), FREE_FN(self._free)
 
     def _alloc(self, nbytes, user):
         p = C.c_void_p()
-        st = self.hip.hipMalloc(C.byref(p), nbytes if nbytes <= self.cap else 1 << 50)
+        st = self.hip.hipMalloc(C.byref(p), nbytes if nbytes <= self.cap and nbytes not in self.but else 1 << 50)
         if st != 0 or not p.value:
             self.refused.append(nbytes)
             return None
@@ -51,17 +52,12 @@ class _Capped:
         self.hip.hipFree(p)
 
 
-# the shared blocks of Phase I alone (the largest array of this pattern takes 2.2
-# MB), and with the plan's 3.6 MB allowed
-@pytest.mark.parametrize("cap", [5 << 19, 1 << 22])
-def test_phase_one_without_large_blocks(cap):
-    if not torch.cuda.is_available():
-        pytest.skip("no GPU")
-    log(f"[gpu] allocations of at most {cap} bytes")
-    A, k = I.conv_diff_2d(200, 1.0, 3.0, 2.0), 1
+def _solve(A, k, bud):
+    """Pattern, factor and solve through a context with that allocator, against
+    the oracle."""
     rpF, ciF, lvF, vF, _ = O.ilu(A, k)
     lib = T.load_library()
-    bud, h, p = _Capped(cap), C.c_void_p(), C.c_void_p()
+    h, p = C.c_void_p(), C.c_void_p()
     stream = C.c_void_p(torch.cuda.current_stream(0).cuda_stream)
     assert lib.tpilu_ctx_create(0, stream, C.cast(bud.alloc, C.c_void_p), C.cast(bud.free, C.c_void_p), None,
                                 C.byref(h)) == T.OK
@@ -69,7 +65,7 @@ def test_phase_one_without_large_blocks(cap):
     ptr = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
     try:
         st = lib.tpilu_symbolic(h, A.n, A.nnz, ptr(rp), ptr(ci), k, C.byref(p))
-        assert bud.refused, "no request was large enough"
+        assert bud.refused, "no request was refused"
         assert st == T.OK, (st, lib.tpilu_last_error(h), bud.refused)
         f = torch.empty(vF.size, dtype=torch.float64, device="cuda")
         bad = C.c_int64(-1)
@@ -85,3 +81,52 @@ def test_phase_one_without_large_blocks(cap):
     finally:
         torch.cuda.synchronize()
         lib.tpilu_ctx_destroy(h)
+
+
+def _need_gpu(what):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    log(f"[gpu] {what}")
+
+
+# the shared blocks of Phase I alone (the largest array of this pattern takes 2.2
+# MB), and with the plan's 2.9 MB allowed
+@pytest.mark.parametrize("cap", [5 << 19, 1 << 22])
+def test_phase_one_without_large_blocks(cap):
+    _need_gpu(f"allocations of at most {cap} bytes")
+    _solve(I.conv_diff_2d(200, 1.0, 3.0, 2.0), 1, _Capped(cap))
+
+
+@pytest.mark.parametrize("m,band", [(200, 0), (300, 0), (0, 40000)])
+def test_without_level_chunks(m, band):
+    """The arrays of 16 bytes a row (records, heads and parts of the level
+    orders, records of the plan) cannot be had."""
+    A = I.conv_diff_2d(m, 1.0, 3.0, 2.0) if m else I.random_banded(band, 5)
+    _need_gpu(f"n = {A.n} without level chunks")
+    sixteen = (16 * A.n + 255) // 256 * 256
+    _solve(A, 1, _Capped((8 if m else 40) * sixteen, {sixteen}))
+
+
+def test_plan_leaves_memory():
+    """With little memory free the plan of Phase II (208 bytes a row here) is not
+    laid down; the factor is the same."""
+    _need_gpu("plan with 2.5 GB free")
+    A = I.conv_diff_3d(100, 1.0, np.ones(3))
+    rp, ci, av = g(A.rowptr), g(A.col), g(A.val)
+    used, factors = [], []
+    torch.cuda.empty_cache()
+    for free in (None, 5 << 29):
+        rest = torch.empty(torch.cuda.mem_get_info()[0] - free, dtype=torch.uint8, device="cuda") if free else None
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        pat = T.symbolic(rp, ci, 1)
+        torch.cuda.synchronize()
+        used.append(before - torch.cuda.mem_get_info()[0])
+        del rest
+        torch.cuda.empty_cache()
+        factors.append(T.numeric(pat, av).cpu().numpy().view(np.uint64))
+        del pat
+    plan = 208 * A.n
+    log(f"pattern {used[0]} bytes, {used[1]} with little free")
+    assert plan * 0.9 < used[0] - used[1] < plan * 1.2, (used, plan)
+    assert np.array_equal(*factors)
