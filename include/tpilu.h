@@ -111,8 +111,9 @@ TPILU_API tpilu_status tpilu_ctx_set_grid(tpilu_ctx ctx, int32_t waves);
  * sweeps on one CU with x in its LDS for small systems of short rows; a lane
  * per row over chunks of one dependency level, on one XCD; a lane per row over
  * blocks of 64 consecutive rows, on one XCD, for rows that depend on few of
- * their near neighbours; else a wavefront per row, on the whole device or on
- * one XCD.  The first three only while placement and grid are automatic too),
+ * their near neighbours; a lane per row over the whole device for wide levels;
+ * else a wavefront per row, on the whole device or on one XCD.  The first four
+ * only while placement and grid are automatic too),
  * 1 = a wavefront per row (on the whole device or on
  * one XCD, see tpilu_ctx_set_placement), 2 = one workgroup on one CU (a lane
  * per row, rows handed over through an LDS ring; measured far slower than
@@ -127,11 +128,13 @@ TPILU_API tpilu_status tpilu_ctx_set_solver(tpilu_ctx ctx, int mode);
 
 /* Kernel of the single-instance numeric factorization: 0 = automatic (while
  * placement and grid are automatic too, several rows per wavefront with their
- * entries in registers for rows of at most 64 entries, of more than 16 only if
- * the pattern has an update per pivot; else the dataflow kernel when the
+ * entries in registers for rows of at most 64 entries, given enough updates per
+ * pivot (of more than 16 entries one, of more than 32 or 16 pivots three) and
+ * memory to spare for its plan; the dataflow kernel instead, or else, when the
  * pattern's rows fit its LDS staging, the strict lower part holds at least 4n
  * entries, an entry receives fewer than 12 updates on average and a dependency
- * level holds fewer than 64 rows on average; else the pivot-serial one),
+ * level holds fewer than 64 rows on average, and there are fewer than two
+ * updates per pivot or no plan; else the pivot-serial one),
  * 1 = dataflow (lanes own the entries of a row and take
  * their updates in ascending pivot order; a later tpilu_numeric fails with
  * TPILU_E_INVAL if the pattern's rows do not fit), 2 = pivot-serial (the
@@ -158,7 +161,7 @@ TPILU_API tpilu_status tpilu_ctx_set_fused(tpilu_ctx ctx, int on);
  * solve on one XCD when its device-wide shape would take at most 256
  * wavefronts, i.e. a dependency level holds fewer than 32 rows, or fewer than
  * 64 short ones, and a row half at most 128 entries on average, and the solves
- * of short halves by their level chunks: one CU, one XCD or the device),
+ * of short halves on one CU, one XCD or the device by their shape),
  * 1 = the whole device, 2 = one XCD (then also the batched factorization
  * and solves, and the dependency-level computation of tpilu_symbolic, one XCD
  * per dependency graph, when its nodes have long dependency lists; by blocks
@@ -184,9 +187,10 @@ TPILU_API tpilu_status tpilu_ctx_set_placement(tpilu_ctx ctx, int where);
  * a wavefront takes `rows` consecutive positions of the dependency-level
  * order from the shared counter and works through them in order.  0 =
  * automatic, else 1 to 64.  Automatic: 1 for the numeric factorization
- * and the solves (their kernels overlap a row's work with the wait on earlier
- * levels, which a group would serialise); for the inverses 1 or 2, by the
- * average rows per dependency level.  Same bits for every value;
+ * (its kernels overlap a row's work with the wait on earlier levels, which a
+ * group would serialise); by the average rows per dependency level 1 or 3 for
+ * the solves and 1 or 2 for the inverses.  The kernels with several rows per
+ * wavefront or a lane per row take their own groups.  Same bits for every value;
  * it only changes speed.  Returns TPILU_E_INVAL outside [0, 64]. */
 TPILU_API tpilu_status tpilu_ctx_set_group(tpilu_ctx ctx, int32_t rows);
 

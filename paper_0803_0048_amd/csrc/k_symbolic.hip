@@ -1017,7 +1017,7 @@ __global__ __launch_bounds__(64) void k_tsched(int32_t n, const int64_t* __restr
             // the row's pairs 64 at a time, the next ones loading meanwhile; a
             // pivot updates distinct slots, so the pivots of a round take turns
             // in LDS alone (a pivot at a time with its loads: 1.13 ms at random
-            // banded n=160,000 ILU(2), TSCHEDMS here)
+            // banded n=160,000 ILU(2), 0.71 here)
             const int64_t e1 = Sp[dl];
             int64_t e = Sp[0] + lane;
             int32_t h = 0, p = 0, q = 0;

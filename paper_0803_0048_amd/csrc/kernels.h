@@ -209,7 +209,6 @@ struct LevelSched {
     const int4* rec = nullptr;   // [n]
     const int4* head = nullptr;  // [nchunk]: first position, end, first chunk of the level, 0
     int32_t nchunk = 0;
-    int32_t depth = 0;
 };
 // head of chunk c, and the record of the calling lane's position in it (z =
 // -1: no position)

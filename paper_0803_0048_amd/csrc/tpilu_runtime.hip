@@ -1610,8 +1610,6 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     {
         tpilu_status ls = finish_levels(ctx, P, ljobs, 2, ldmax);
         if (ls != TPILU_OK) return bail(ls);
-        P->lsL.depth = P->depth_l;
-        P->lsU.depth = P->depth_u;
     }
     if (nupd < plan_updates(P->nplan.config) * nl_ ||
         (P->nplan.config == 3 && n >= kPlanWideRows * (int64_t)P->depth_l))
