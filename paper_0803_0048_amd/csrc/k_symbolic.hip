@@ -961,15 +961,21 @@ hipError_t launch_sched_copy(const SchedPool& pool, int64_t nseg, const int64_t*
     return hipGetLastError();
 }
 
+// a workgroup's LDS holds the columns of a row of max_row entries and the filter,
+// the queue and the counts included (a little more ends the queue instead of
+// failing the launch)
+bool sched_row_fits(int32_t max_row) {
+    return (size_t)std::max(max_row, 1) * sizeof(int32_t) + (size_t)sched_filter_bits(max_row) / 8 + kSchedStaticLds <=
+           160 * 1024;
+}
+
 hipError_t launch_sched(int32_t n, const int64_t* rpF, const int32_t* ciF, const int32_t* diagF,
                         int mode, int32_t* scount, int32_t* lsd, const int64_t* sptr,
                         int32_t* sq, int32_t* sp, int32_t max_row, hipStream_t s, const SchedPool* pool,
                         int32_t stride) {
     const int32_t bits = sched_filter_bits(max_row);
     const size_t lds = (size_t)std::max(max_row, 1) * sizeof(int32_t) + (size_t)bits / 8;
-    // a workgroup's LDS, the queue and the counts included (a little more ends the
-    // queue instead of failing the launch)
-    if (lds + kSchedStaticLds > 160 * 1024) return hipErrorInvalidValue;
+    if (!sched_row_fits(max_row)) return hipErrorInvalidValue;
     stride = max(stride, 1);
     const int32_t split = mode == 3 ? kSchedSampleSplit : 1;
     const int64_t tasks = ((int64_t)n + stride - 1) / stride * split;

@@ -68,6 +68,7 @@ struct SchedPool {
     uint32_t* overflow = nullptr;
     unsigned long long* sample = nullptr;
 };
+bool sched_row_fits(int32_t max_row);
 hipError_t launch_sched(int32_t n, const int64_t* rpF, const int32_t* ciF, const int32_t* diagF,
                         int mode, int32_t* scount, int32_t* lsd, const int64_t* sptr,
                         int32_t* sq, int32_t* sp, int32_t max_row, hipStream_t s,

@@ -1321,11 +1321,16 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->n = n;
     P->nnz_a = nnz;
     P->k = k;
-    bool forked = false;  // work on the second stream may still use P's arrays
-    auto bail = [&](tpilu_status st) {
-        if (forked) (void)hipStreamSynchronize(ctx->aux);
-        delete P;
-        return st;
+    // released by every way out but the good one, after the temporaries and the
+    // second stream's work on them (AuxJoin)
+    struct Owner {
+        tpilu_pattern p;
+        ~Owner() { delete p; }
+    } owner{P};
+    auto done = [&]() {
+        *out = P;
+        owner.p = nullptr;
+        return TPILU_OK;
     };
     P->arrays.reserve(Arena::up(sizeof(Ctl)) + Arena::up(64) + Arena::up(8 * (size_t)(n + 1)) +
                       Arena::up(4 * (size_t)nnz));
@@ -1333,7 +1338,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     uint32_t* vstat = (uint32_t*)P->take(64);
     P->rpA = (int64_t*)P->take(sizeof(int64_t) * (size_t)(n + 1));
     P->ciA = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1));
-    if (!P->ctl || !vstat || !P->rpA || !P->ciA) return bail(fail(ctx, TPILU_E_NOMEM, "pattern arrays"));
+    if (!P->ctl || !vstat || !P->rpA || !P->ciA) return fail(ctx, TPILU_E_NOMEM, "pattern arrays");
     {
         Ctl z{};
         z.bad_row = ~0ull;
@@ -1344,8 +1349,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         HIPCHK(ctx, hipMemcpyAsync(P->rpA, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
         P->rpF = P->rpA;
         HIPCHK(ctx, hipStreamSynchronize(s));
-        *out = P;
-        return TPILU_OK;
+        return done();
     }
     HIPCHK(ctx, hipMemcpyAsync(P->rpA, rowptr, sizeof(int64_t) * (size_t)(n + 1), hipMemcpyDeviceToDevice, s));
     if (nnz > 0)
@@ -1363,7 +1367,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         if (vs & kValBadCol) m += " column index out of range;";
         if (vs & kValUnsorted) m += " columns not strictly ascending;";
         if (vs & kValNoDiag) m += " diagonal entry missing;";
-        return bail(fail(ctx, TPILU_E_INVAL, m));
+        return fail(ctx, TPILU_E_INVAL, m);
     }
     const int32_t ni = (int32_t)n;
     // ---- a2: level-of-fill pattern, count pass
@@ -1380,7 +1384,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     lists.tier_of = (uint8_t*)T.get((size_t)n);
     int64_t* scan_tmp = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(n));
     if (!cnt || !lists.rows || !lists.count || !lists.tier_of || !scan_tmp)
-        return bail(fail(ctx, TPILU_E_NOMEM, "symbolic scratch"));
+        return fail(ctx, TPILU_E_NOMEM, "symbolic scratch");
     HIPCHK(ctx, launch_fill_i32(lists.count, 16, 0, s));
     HIPCHK(ctx, launch_route_rows(ni, P->rpA, P->ciA, cnt, k, lists, s));
     // the tiers follow each other without a look at their lists' lengths: a
@@ -1404,17 +1408,17 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         gcap = next_pow2(2 * (uint64_t)n + 2);
         ggrid = std::min(n_over2, 32);
         gscr = (int32_t*)T.get(sizeof(int32_t) * sym_global_scratch_ints(ni, gcap) * (size_t)ggrid);
-        if (!gscr) return bail(fail(ctx, TPILU_E_NOMEM, "symbolic global scratch"));
+        if (!gscr) return fail(ctx, TPILU_E_NOMEM, "symbolic global scratch");
         HIPCHK(ctx, launch_sym_rows(kSymGlobal, ni, P->rpA, P->ciA, k, lists, 0, cnt, nullptr, nullptr, nullptr,
                                     nullptr, gscr, gcap, ggrid, s));
     }
     P->rpF = (int64_t*)P->take(sizeof(int64_t) * (size_t)(n + 1));
-    if (!P->rpF) return bail(fail(ctx, TPILU_E_NOMEM, "rowptr"));
+    if (!P->rpF) return fail(ctx, TPILU_E_NOMEM, "rowptr");
     HIPCHK(ctx, launch_scan(cnt, n, P->rpF, scan_tmp, s));
     int64_t nnzf = 0;
     HIPCHK(ctx, hipMemcpyAsync(&nnzf, P->rpF + n, sizeof(nnzf), hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
-    if (nnzf >= (1ll << 31) - 1) return bail(fail(ctx, TPILU_E_INVAL, "nnz(F) exceeds 2^31"));
+    if (nnzf >= (1ll << 31) - 1) return fail(ctx, TPILU_E_INVAL, "nnz(F) exceeds 2^31");
     P->nnz_f = nnzf;
     trace("symbolic: fill pass, nnz(F)", nnzf);
     // F's columns, levels, lsd and sptr; per row diagF, the levels' orders,
@@ -1427,7 +1431,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->lsd = (int32_t*)P->take(sizeof(int32_t) * (size_t)nnzf);
     P->sptr = (int64_t*)P->take(sizeof(int64_t) * (size_t)(nnzf + 1));
     if (!P->ciF || !P->lvF || !P->diagF || !P->a2f || !P->lsd || !P->sptr)
-        return bail(fail(ctx, TPILU_E_NOMEM, "pattern arrays"));
+        return fail(ctx, TPILU_E_NOMEM, "pattern arrays");
     // fill pass
     for (int tier = 0; tier < kSymTiers; ++tier) {
         if (ntier[tier] == 0) continue;
@@ -1444,7 +1448,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     };
     Facts* facts = (Facts*)T.get(sizeof(Facts));
     P->wcntL = (uint8_t*)P->take((size_t)n * 2);
-    if (!facts || !P->wcntL) return bail(fail(ctx, TPILU_E_NOMEM, "stats"));
+    if (!facts || !P->wcntL) return fail(ctx, TPILU_E_NOMEM, "stats");
     P->wcntU = P->wcntL + n;
     HIPCHK(ctx, launch_fill_i32((int32_t*)facts, sizeof(Facts) / 4, 0, s));
     HIPCHK(ctx, launch_a2f(ni, P->rpA, P->ciA, P->rpF, P->ciF, P->a2f, &facts->missing, s));
@@ -1456,7 +1460,9 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->st = hf.st;
     P->bst = hf.bst;
     vs = hf.missing;
-    if (vs) return bail(fail(ctx, TPILU_E_INVAL, "internal: an entry of A is missing from F"));
+    if (vs) return fail(ctx, TPILU_E_INVAL, "internal: an entry of A is missing from F");
+    if (!sched_row_fits(P->st.max_row))
+        return fail(ctx, TPILU_E_DEVICE, "a row of F does not fit the LDS of the update schedule");
     // ---- dependency levels and the level-ordered schedules, on the second
     // stream: a latency-bound chain on a few wavefronts, overlapped with the
     // throughput-bound update schedules below
@@ -1464,7 +1470,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     P->depthU = P->depthL + n;
     P->permL = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
     P->permU = (int32_t*)P->take(sizeof(int32_t) * (size_t)n);
-    if (!P->depthL || !P->permL || !P->permU) return bail(fail(ctx, TPILU_E_NOMEM, "levels"));
+    if (!P->depthL || !P->permL || !P->permU) return fail(ctx, TPILU_E_NOMEM, "levels");
     const int64_t nl_ = (int64_t)P->st.nnz_l, nu_ = nnzf - nl_ - n;
     LevelSpec ljobs[2] = {{DepGraph{P->rpF, P->ciF, P->diagF, 0}, 0, nl_, P->depthL, P->permL, &P->depth_l},
                           {DepGraph{P->rpF, P->ciF, P->diagF, 1}, 1, nu_, P->depthU, P->permU, &P->depth_u}};
@@ -1504,9 +1510,8 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         HIPCHK(ctx, hipEventRecord(ctx->fork_ev, s));
         HIPCHK(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
         aux_join.a = ctx->aux;
-        forked = true;
         tpilu_status ls = enqueue_levels(ctx, P, ljobs, 2, ctx->aux, T, &ldmax);
-        if (ls != TPILU_OK) return bail(ls);
+        if (ls != TPILU_OK) return ls;
     }
     // ---- update schedule for Phase II: one search pass that counts and
     // stages the pairs in a pool (sized from a sample of the rows), a scan,
@@ -1517,7 +1522,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     int32_t* scount = (int32_t*)T.get(sizeof(int32_t) * (size_t)nnzf);
     int64_t* scan2 = (int64_t*)T.get(sizeof(int64_t) * scan_tmp_elems(nnzf));
     unsigned long long* sctr = (unsigned long long*)T.get(64);
-    if (!scount || !scan2 || !sctr) return bail(fail(ctx, TPILU_E_NOMEM, "schedule scratch"));
+    if (!scount || !scan2 || !sctr) return fail(ctx, TPILU_E_NOMEM, "schedule scratch");
     HIPCHK(ctx, launch_fill_i32((int32_t*)sctr, 16, 0, s));
     SchedPool pool{};
     pool.ctr = sctr;
@@ -1583,7 +1588,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
                       (flow ? 2 * Arena::up(4 * (size_t)nupd) + Arena::up(8 * (size_t)(nnzf + 1)) : 0));
     P->sq = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nupd, 1));
     P->sp = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nupd, 1));
-    if (!P->sq || !P->sp) return bail(fail(ctx, TPILU_E_NOMEM, "schedule"));
+    if (!P->sq || !P->sp) return fail(ctx, TPILU_E_NOMEM, "schedule");
     if (pooled)
         HIPCHK(ctx, launch_sched_copy(pool, n * kSchedSegs + (int64_t)pc[1], P->rpF, P->sptr, P->sq, P->sp, s));
     else
@@ -1595,7 +1600,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         P->tptr = (int64_t*)P->take(sizeof(int64_t) * (size_t)(nnzf + 1));
         P->tsl = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nupd, 1));
         P->tq = (int32_t*)P->take(sizeof(int32_t) * (size_t)std::max<int64_t>(nupd, 1));
-        if (!P->tptr || !P->tsl || !P->tq) return bail(fail(ctx, TPILU_E_NOMEM, "target-major schedule"));
+        if (!P->tptr || !P->tsl || !P->tq) return fail(ctx, TPILU_E_NOMEM, "target-major schedule");
         HIPCHK(ctx, launch_tsched(ni, P->rpF, P->diagF, P->sptr, P->sq, P->sp, 0, scount, nullptr, nullptr, nullptr,
                                   P->st.max_row, P->st.max_lrow, s));
         HIPCHK(ctx, launch_scan(scount, nnzf, P->tptr, scan2, s));
@@ -1609,7 +1614,7 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
     HIPCHK(ctx, hipStreamSynchronize(s));
     {
         tpilu_status ls = finish_levels(ctx, P, ljobs, 2, ldmax);
-        if (ls != TPILU_OK) return bail(ls);
+        if (ls != TPILU_OK) return ls;
     }
     if (nupd < plan_updates(P->nplan.config) * nl_ ||
         (P->nplan.config == 3 && n >= kPlanWideRows * (int64_t)P->depth_l))
@@ -1633,11 +1638,10 @@ extern "C" TPILU_API tpilu_status tpilu_symbolic(tpilu_ctx ctx, int64_t n, int64
         if (!P->lsL.head) P->lsL.rec = nullptr;
         if (!P->lsU.head) P->lsU.rec = nullptr;
     }
-    if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return bail(ps);
+    if (tpilu_status ps = build_numeric_plan(ctx, P); ps != TPILU_OK) return ps;
     tpilu_status st = read_ctl(ctx, P, nullptr, true);
-    if (st != TPILU_OK) return bail(st);
-    *out = P;
-    return TPILU_OK;
+    if (st != TPILU_OK) return st;
+    return done();
 }
 
 extern "C" TPILU_API tpilu_status tpilu_pattern_info(tpilu_pattern pat, tpilu_pattern_info_t* info) {
